@@ -59,8 +59,8 @@
  * kernel is one aligned 16-byte chunk:
  *   K page: chunk (j, hf, g, k8), j<8, hf<2, g<4, k8<8, at byte ((((j*2+hf)*4+g)*8)+k8)*16
  *           holds K[8hf+k8][32j+8g .. 32j+8g+7].
- *   V page: chunk (c, gp, m), c<16, gp<2, m<16, at byte (((c*2+gp)*16)+m)*16
- *           holds V[4gp..4gp+3][16c+m] followed by V[8+4gp..8+4gp+3][16c+m].
+ *   V page: chunk (w, c, gp, n), w<4, c<4, gp<2, n<16, at byte ((((w*4+c)*2+gp)*16)+n)*16
+ *           holds V[4gp..4gp+3][d] followed by V[8+4gp..8+4gp+3][d], d = 64w+4n+c.
  * oxy_gather_kv reads tokens back in the natural [token][256] order.
  */
 #ifndef OXY_H

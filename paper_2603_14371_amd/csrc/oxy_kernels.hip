@@ -19,9 +19,10 @@
 //       tile hf (0,1): A-row r is key 8hf + r%8 of page r/8, so lane (n = row, g) receives
 //       the logits of keys 8hf + 4(g%2) + e, e < 4, of page g/2
 //   O^T[d][row]   += sum_key V[key][d] * P[row][key]  A = V chunk, B = P
-//       lane (g) contracts exactly the eight keys it holds logits for, all of one page, so
-//       its V operand is ONE 16-byte chunk of that page and P needs no cross-lane movement
-//       -> lane (n = row, g) accumulates d = 16c+4g..16c+4g+3
+//       lane (g) contracts eight keys of one page, the same eight whose logits lane (g) of the
+//       first product holds: its V operand is ONE 16-byte chunk of that page, and P goes from
+//       wavefront to wavefront without moving between lanes.  A-row m of operand c is dim
+//       64w+4m+c -> lane (n = row, g) accumulates dims 64w+16g..64w+16g+15 over four operands
 // Both results keep "row = lane % 16", so the softmax state (m, l, rescale factor) is a
 // per-lane scalar.  The pool pages are stored in exactly the operand order these products
 // want (see oxy.h): every MFMA operand is one aligned 16-byte load.
@@ -30,12 +31,15 @@
 #include <hip/hip_ext.h>
 
 #include <mutex>
+#include <type_traits>
 
 namespace oxy {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 
 __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
@@ -45,8 +49,7 @@ __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
 // two floats -> packed bf16 pair, round to nearest even (inputs are finite here)
 __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
-  f32x2 f = {lo, hi};
+  const f32x2 f = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
 }
 
@@ -55,8 +58,7 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // two floats -> packed fp16 pair (round to nearest even)
 __device__ __forceinline__ uint32_t pack_f16(float lo, float hi) {
   typedef __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16 f16x2;
-  typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2_;
-  const f32x2_ f = {lo, hi};
+  const f32x2 f = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, f16x2));
 }
 __device__ __forceinline__ void unpack_f16(uint32_t u, float& lo, float& hi) {
@@ -85,17 +87,6 @@ __device__ __forceinline__ float row_sum4(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
-// max over the 16 lanes of a row (lanes 16r .. 16r+15): four DPP moves, no LDS round trip.
-// quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror: after each step twice
-// as many neighbouring lanes hold the same value, so the mirrors act like xor 4 and xor 8.
-__device__ __forceinline__ float lanes16_max(float x) {
-  x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, true)));
-  x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, true)));
-  x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, true)));
-  x = fmaxf(x, __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, true)));
-  return x;
-}
-
 // ------------------------------------------------------------------------------------------
 // page layout (see oxy.h)
 // ------------------------------------------------------------------------------------------
@@ -103,9 +94,13 @@ __device__ __forceinline__ float lanes16_max(float x) {
 __device__ __forceinline__ int k_chunk_offset(int j, int hf, int g, int k8) {
   return ((((j * 2 + hf) * 4 + g) * 8) + k8) * 16;
 }
-// V page: chunk (c, gp, m) holds V[4gp..4gp+3][16c+m] then V[8+4gp..8+4gp+3][16c+m]
-__device__ __forceinline__ int v_chunk_offset(int c, int gp, int m) {
-  return (((c * 2 + gp) * 16) + m) * 16;
+// V page: chunk (w, c, gp, n) holds V[4gp..4gp+3][d] then V[8+4gp..8+4gp+3][d], d = 64w+4n+c
+__device__ __forceinline__ int v_chunk_offset(int w, int c, int gp, int n) {
+  return ((((w * 4 + c) * 2 + gp) * 16) + n) * 16;
+}
+// the chunk of dim d
+__device__ __forceinline__ int v_chunk_of_dim(int d, int gp) {
+  return v_chunk_offset(d >> 6, d & 3, gp, (d >> 2) & 15);
 }
 __device__ __forceinline__ int v_slot_of_key(int key) { return ((key >> 3) << 2) | (key & 3); }
 
@@ -132,7 +127,7 @@ __device__ __forceinline__ void store_row(const RowPart& r, int32_t slot,
   char* kp = layer_base + (size_t)blk * kBlockBytes;
   char* vp = kp + kPageBytes;
   if (t < 32) *(u32x4*)(kp + k_chunk_offset(t >> 2, key >> 3, t & 3, key & 7)) = r.k;
-  *(uint16_t*)(vp + v_chunk_offset(t >> 4, (key >> 2) & 1, t & 15) + v_slot_of_key(key) * 2) = r.v;
+  *(uint16_t*)(vp + v_chunk_of_dim(t, (key >> 2) & 1) + v_slot_of_key(key) * 2) = r.v;
 }
 __device__ __forceinline__ void append_row(const uint16_t* __restrict__ k_row,
                                            const uint16_t* __restrict__ v_row, int32_t slot,
@@ -191,14 +186,14 @@ __global__ __launch_bounds__(256) void append_blocks_kernel(const uint16_t* __re
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int ci = t + 256 * i, c = ci >> 5, gp = (ci >> 4) & 1, m = ci & 15, d = 16 * c + m;
+    const int ci = t + 256 * i, gp = (ci >> 4) & 1, d = 64 * (ci >> 7) + 4 * (ci & 15) + ((ci >> 5) & 3);
     u32x4 out;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int k0 = (e < 2 ? 4 * gp : 8 + 4 * gp) + 2 * (e & 1);
       out[e] = (uint32_t)v_s[k0][d] | ((uint32_t)v_s[k0 + 1][d] << 16);
     }
-    *(u32x4*)(vp + v_chunk_offset(c, gp, m)) = out;
+    *(u32x4*)(vp + ci * 16) = out;
   }
 }
 
@@ -215,7 +210,7 @@ __global__ __launch_bounds__(256) void gather_inline_kernel(const char* __restri
     *(u32x4*)(k_out + (size_t)tok * kDim + t * 8) =
         *(const u32x4*)(kp + k_chunk_offset(t >> 2, key >> 3, t & 3, key & 7));
   v_out[(size_t)tok * kDim + t] =
-      *(const uint16_t*)(vp + v_chunk_offset(t >> 4, (key >> 2) & 1, t & 15) + v_slot_of_key(key) * 2);
+      *(const uint16_t*)(vp + v_chunk_of_dim(t, (key >> 2) & 1) + v_slot_of_key(key) * 2);
 }
 
 hipError_t launch_append(const void* k_new, const void* v_new, const int32_t* d_slots,
@@ -249,76 +244,47 @@ hipError_t launch_gather_inline(const void* layer_base, const InlineIds& slots, 
 // ------------------------------------------------------------------------------------------
 // attention work items
 // ------------------------------------------------------------------------------------------
-// LDS stage of the tile path: K page A, K page B, V page A, V page B.  K page B is skewed by
-// 128 bytes so that the 16 lanes served together (8 keys of page A, 8 of page B) hit
-// different banks.
-constexpr int kOffKA = 0;
-constexpr int kOffKB = kPageBytes + 128;
-constexpr int kOffVA = 2 * kPageBytes + 256;
-constexpr int kOffVB = kOffVA + kPageBytes;
-constexpr int kStageBytes = kOffVB + kPageBytes;      // 33024
-constexpr int kMergeStride = kDim + 4;                // floats per row in the LDS merge buffer
-constexpr int kEpilogueStride = kDim * 2 + 16;        // bytes per fp16 row in the tile epilogue
-constexpr int kSmemBytes = 4 * 16 * kMergeStride * 4; // 66560 >= 2 * kStageBytes
-static_assert(2 * kStageBytes <= kSmemBytes, "two stages must fit");
 constexpr float kGrow = 8.f;  // the reference max only moves when a logit exceeds it by 2^8
+constexpr int kMaxGroups = 4; // groups of 16 query rows (two tokens) in one work item
 
-// One 32-key step of the online softmax for the 16 rows of a wavefront.  s0/s1 hold the raw
-// dot products of this lane's row with keys pos + 16(g/2) + 8hf + 4(g%2) + e (hf = 0 / 1).
-// m is the reference max of the row in the scaled log2 domain.  It only moves when a logit
-// exceeds it by more than kGrow, so the 64-register rescale of acc is rare; P is then at most
-// 2^kGrow, well inside fp32/bf16 range.  P is returned as hi+lo bf16: a single bf16 rounding
-// (2^-9 relative) is too coarse for queries that see only a handful of keys.
-__device__ __forceinline__ void softmax_step(const f32x4 s0, const f32x4 s1, const bool need_mask,
-                                             const int pos, const int kv_end, const int qpos,
-                                             const int g, const float sl2, float& m, float& l,
-                                             f32x4 (&acc)[16], u32x4& pf, u32x4& pl) {
-  const float ninf = -__builtin_inff();
-  float t[8];
+// LDS of a work item: nothing of K and V, only what the four wavefronts exchange.  Every u32x4
+// entry is one lane's 16-byte MFMA operand, stored and read back at the lane's own position.
+struct __align__(16) WorkLds {
+  u32x4 q[kMaxGroups][8][64];      // query fragments (B operand of S^T), the same for all wavefronts
+  u32x4 p[4][kMaxGroups][2][64];   // [32-key step of the round][group][hi / lo]: P of all 128 keys
+  float mx[kMaxGroups][16][4];     // largest logit of a row among each wavefront's 32 keys
+  int slot[2 * kMaxGroups];        // split result of each token
+  float ls[kMaxGroups][64][4];     // sum of a lane's P over each wavefront's keys
+};
+
+// The descriptor is read with scalar loads: it is not written during a launch and every address
+// is wave-uniform, so records, token ids and block ids land in scalar registers, take no part in
+// the order in which the vector loads of queries and pages complete, and need no lane reads.
+typedef const __attribute__((address_space(4))) int32_t* DescPtr;
+typedef int32_t i32x8 __attribute__((ext_vector_type(8)));
+typedef const __attribute__((address_space(4))) i32x8* DescPtr8;
+
+// A record: 8 header words, 8 query token ids (the last one repeated), the block ids of the
+// split's first 16 pages (the last one repeated).  All but the last eight words are requested
+// at once at the start of the kernel.
+struct WorkItem {
+  DescPtr rec, tbl;
+  i32x8 toks, pages;
+  int n_tok, kv_begin, kv_end, q0, part_idx;
+};
+// query token of this lane's row in group r
+__device__ __forceinline__ int token_of(const WorkItem& wi, const int r, const int second) {
+  return second ? wi.toks[2 * r + 1] : wi.toks[2 * r];
+}
+// First split result of token lane % (2*G) of the item.  It is needed at the very end only, but
+// requested at the start (a full memory latency in front of the stores otherwise) and kept in LDS
+// meanwhile: four groups leave no registers for it.
+template <int G>
+__device__ __forceinline__ int request_slot(const AttnArgs& a, const WorkItem& wi, const int lane) {
+  int tok = wi.toks[0];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    t[e] = s0[e] * sl2;
-    t[4 + e] = s1[e] * sl2;
-  }
-  if (need_mask) {  // wave-uniform: only the last step of a split or the causal diagonal
-    const int k0 = pos + 16 * (g >> 1) + 4 * (g & 1);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int ka = k0 + e, kb = k0 + 8 + e;
-      t[e] = (ka < kv_end && ka <= qpos) ? t[e] : ninf;
-      t[4 + e] = (kb < kv_end && kb <= qpos) ? t[4 + e] : ninf;
-    }
-  }
-  float mx = fmaxf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])),
-                   fmaxf(fmaxf(t[4], t[5]), fmaxf(t[6], t[7])));
-  mx = row_max4(mx);
-  const bool grow = mx > m + kGrow;   // also true for the first finite logit (m = -inf)
-  if (__any(grow)) {
-    const float m_new = grow ? mx : m;
-    const float alpha = grow ? fast_exp2(m - m_new) : 1.f;   // m = -inf gives 0
-    l *= alpha;
-    // a wavefront whose rows have seen no finite logit yet (the first step of every work item)
-    // holds zeros: scaling them changes nothing
-    if (__any(m != ninf)) {
-#pragma unroll
-      for (int c = 0; c < 16; ++c) acc[c] *= alpha;
-    }
-    m = m_new;
-  }
-  const float m_use = (m == ninf) ? 0.f : m;
-  float p[8], sum = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    p[e] = fast_exp2(t[e] - m_use);
-    sum += p[e];
-  }
-  l += sum;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    pf[i] = pack_bf16(p[2 * i], p[2 * i + 1]);
-    pl[i] = pack_bf16(p[2 * i] - __uint_as_float(pf[i] << 16),
-                      p[2 * i + 1] - __uint_as_float(pf[i] & 0xffff0000u));
-  }
+  for (int i = 1; i < 2 * G; ++i) tok = lane % (2 * G) == i ? wi.toks[i] : tok;
+  return a.part_off[tok];
 }
 
 // Values of keys at or beyond kv_end may be stale bits (never-written slots, freed blocks):
@@ -334,585 +300,618 @@ __device__ __forceinline__ u32x4 value_mask(const int left, const int g) {
   return mask;
 }
 
-
-struct WorkItem {
-  int n_tok, kv_begin, kv_end, q0, part_idx;
-  const int32_t* tbl;
-  int rec;   // this lane's word of the 32-word record (lanes 32..63 mirror 0..31)
-};
-
-// Block ids of the split, one per lane: the first 16 pages are words 16..31 of the record itself
-// (no dependent load), all pages (a split has at most 64) come from the block table.  The table load is
-// issued whether or not the split has more than 16 pages: a load under a condition would make
-// the compiler wait for EVERYTHING in flight wherever the two paths meet again (it counts
-// outstanding loads per control-flow path), and that wait would sit in front of the first pages.
-struct SplitIds {
-  int lo, hi;
-};
-__device__ __forceinline__ SplitIds split_block_ids(const WorkItem& wi, const int lane, const int npg) {
-  SplitIds ids;
-  ids.lo = wi.rec;
-  ids.hi = wi.tbl[(wi.kv_begin >> 4) + (lane < npg ? lane : npg - 1)];
-  return ids;
+// Softmax scale in the log2 domain, as a positive factor: the largest logit of a row is then the
+// scale times its largest dot product, and one fused multiply-add takes a dot product to its
+// exponent.  A negative scale goes into the sign of the queries (see query_sign); a zero one is
+// taken as 2^-120, which gives the same uniform weights and keeps -inf (a masked key) what it is.
+__device__ __forceinline__ float log2_scale(const AttnArgs& a) {
+  const float x = fabsf(a.scale * 1.4426950408889634f);
+  return x == 0.f ? 0x1p-120f : x;
 }
-// pi is wave-uniform
-__device__ __forceinline__ int block_of(const SplitIds& ids, const int pi) {
-  return pi < kWorkInlinePages ? __builtin_amdgcn_readlane(ids.lo, 16 + pi)
-                               : __builtin_amdgcn_readlane(ids.hi, pi);
+// flips the signs of eight bf16 query elements where the scale is negative
+__device__ __forceinline__ u32x4 query_sign(const AttnArgs& a, const u32x4 q) {
+  const uint32_t flip = a.scale < 0.f ? 0x80008000u : 0u;
+  return q ^ (u32x4){flip, flip, flip, flip};
 }
-
-// ---- tile path: <= 8 query tokens (64 rows); the four wavefronts share every KV page through
-// LDS (double-buffered, one barrier per 32-key step) and own 16 rows each.
-// kFresh: the keys are rows of this step's k_new / v_new (row0 + own position) instead of pool
-// pages; they are brought into the same register image, so everything after the fetch is shared.
-// The pool receives those rows from the merge launch of the same layer (nothing reads them from
-// the pool during this launch, and the tiles are the last workgroups of a small launch to end).
-template <bool kFresh>
-__device__ __forceinline__ void tile_path(const AttnArgs& a, const WorkItem& wi, char* smem,
-                                          const int row0) {
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it scalar
+// largest of a lane's eight dot products
+__device__ __forceinline__ float row_max8(const f32x4 s0, const f32x4 s1) {
+  return fmaxf(fmaxf(fmaxf(s0[0], s0[1]), fmaxf(s0[2], s0[3])),
+               fmaxf(fmaxf(s1[0], s1[1]), fmaxf(s1[2], s1[3])));
+}
+// P = 2^(sl2 * s - m) of a lane's eight dot products as hi + lo bf16 (a single bf16 rounding, 2^-9
+// relative, is too coarse for queries that see only a handful of keys); returns their fp32 sum.
+__device__ __forceinline__ float softmax_weights(const f32x4 s0, const f32x4 s1, const float sl2,
+                                                 const float m, u32x4& hi, u32x4& lo) {
+  float p[8], sum = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    p[e] = fast_exp2(__builtin_fmaf(e < 4 ? s0[e & 3] : s1[e & 3], sl2, -m));
+    sum += p[e];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    hi[i] = pack_bf16(p[2 * i], p[2 * i + 1]);
+    lo[i] = pack_bf16(p[2 * i] - __uint_as_float(hi[i] << 16),
+                      p[2 * i + 1] - __uint_as_float(hi[i] & 0xffff0000u));
+  }
+  return sum;
+}
+// One wavefront's 64 dims of a group's split result.  A split result leaves as (m, l, four
+// exponents) and acc * 2^(14 - exponent) in fp16: half the bytes of fp32, with the exponent of the
+// largest value per row and 64 dims, so that the rounding does not depend on the magnitude of the
+// values.  acc[c][e] = dim 16g + 4e + c of the 64: a lane's sixteen values are consecutive.  slot: split result of this lane's token.
+__device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi, const int slot,
+                                           const f32x4 (&acc)[4], const int group, const int wv,
+                                           const int lane) {
   const int n = lane & 15, g = lane >> 4;
-  const int ts = 2 * wv + (n >> 3), h = n & 7;
-  const bool row_valid = ts < wi.n_tok;
-  const bool wave_active = 2 * wv < wi.n_tok;
-  // token ids sit in words 8..15 of the record: this wavefront's two, and the tile's first for
-  // rows past its tokens (wave-uniform lane reads instead of a shuffle through LDS)
-  const int tok_a = __builtin_amdgcn_readlane(wi.rec, 8 + 2 * wv);
-  const int tok_b = __builtin_amdgcn_readlane(wi.rec, 9 + 2 * wv);
-  const int tok_z = __builtin_amdgcn_readlane(wi.rec, 8);
-  const int tok = row_valid ? ((n >> 3) ? tok_b : tok_a) : tok_z;
-  const int qpos = wi.q0 + ts;
-  // first partial slot of this wavefront's two tokens (words past the tile's tokens repeat its
-  // last one): needed only at the end, loaded now (two scalar loads) so that the epilogue does
-  // not wait for them
-  const int part_a = a.part_off[tok_a] + wi.part_idx, part_b = a.part_off[tok_b] + wi.part_idx;
-  u32x4 qf[8];
-  float m = -__builtin_inff(), l = 0.f;
-  f32x4 acc[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) acc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  const float sl2 = a.scale * 1.4426950408889634f;
-  const char* __restrict__ base = (const char*)a.layer_base;
-  const int nsteps = (wi.kv_end - wi.kv_begin + 31) >> 5;
-
-  // Each thread moves 8 x 16 B per step: K page A (2), K page B (2), V page A (2), V page B (2).
-  // Two steps are kept in flight in registers on top of the step being computed from LDS.
-  u32x4 st0[8], st1[8];
-  // block ids of the whole split, one per lane (a split has at most 64 pages): fetched once,
-  // then read with v_readlane, so no step waits on a scalar load before issuing its pages
-  const int npg = ((wi.kv_end + 15) >> 4) - (wi.kv_begin >> 4);
-  const SplitIds ids = split_block_ids(wi, lane, npg);
-  // Every fetch issues exactly eight loads and no fetch is conditional: the compiler counts
-  // outstanding loads per control-flow path, and a conditional load would make it wait for
-  // everything at the next join.  A step past the end re-reads one hot 4 KiB (eight times the
-  // same 16 B per thread); a missing page B re-reads page A.  Neither is ever used.
-  // kFresh only: the V part of a step in two halves, so that the loads of several steps can be
-  // issued before the first transpose waits for any of them.
-  // r[e] = dims vdim..vdim+3 of key e of this thread's chunks (keys 4gp+e, then 8+4gp+e-4).
-  typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
-  auto fetch_fresh_k = [&](const int s, u32x4 (&st)[8]) {
-    const int pos0 = wi.kv_begin + 32 * s, last = wi.kv_end - 1;
-    const uint16_t* kn = (const uint16_t*)a.k_new + (size_t)row0 * kDim;
-    const int kkey = ((tid >> 5) & 1) * 8 + (tid & 7);
-    const int kdim = (tid >> 6) * 32 + ((tid >> 3) & 3) * 8;
-#pragma unroll
-    for (int pgi = 0; pgi < 2; ++pgi) {
-      const uint16_t* ksrc = kn + (size_t)min(pos0 + 16 * pgi + kkey, last) * kDim + kdim;
-      st[2 * pgi] = *(const u32x4*)ksrc;
-      st[2 * pgi + 1] = *(const u32x4*)(ksrc + 128);
-    }
-  };
-  auto fresh_v_load = [&](const int s, u32x2 (&r)[8]) {
-    const uint16_t* vn = (const uint16_t*)a.v_new + (size_t)row0 * kDim;
-    const int q = tid & 127, gp = (q >> 2) & 1, last = wi.kv_end - 1;
-    const int vpos = wi.kv_begin + 32 * s + 16 * (tid >> 7) + 4 * gp;
-    const int vdim = 16 * (q >> 3) + 4 * (q & 3);
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      r[e] = *(const u32x2*)(vn + (size_t)min(vpos + (e < 4 ? e : e + 4), last) * kDim + vdim);
-  };
-  auto fresh_v_assemble = [&](const u32x2 (&r)[8], u32x4 (&st)[8]) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {   // chunk j = dim vdim + j: halfword j of every key
-      u32x4 c;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const uint32_t lo = r[2 * w][j >> 1], hi = r[2 * w + 1][j >> 1];
-        c[w] = (j & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
-      }
-      st[4 + j] = c;
-    }
-  };
-  auto fetch = [&](const int s, u32x4 (&st)[8]) {
-    const bool real = s < nsteps;
-    if constexpr (kFresh) {
-      // K: thread tid holds chunks tid and tid+256 of each page as everywhere (a K chunk = 8 dims
-      // of one key = one 16-byte load from the row).  V: a chunk is one dim of 8 keys, so here a
-      // thread takes FOUR NEIGHBOURING chunks (dims d..d+3, same eight keys) of ONE page: eight
-      // 8-byte loads and a 4x8 transpose in registers instead of thirty-two 2-byte gathers.
-      // Thread tid: page tid / 128, chunks 4q..4q+3 with q = tid % 128 (see commit / sanitize).
-      // Positions at or beyond the split's end re-read its last row; they are masked like stale
-      // slots.  A step past the end loads nothing: the rows sit in L2 and a fresh tile has few
-      // steps, so the wait that a conditional load costs is cheap.
-      if (!real) return;
-      fetch_fresh_k(s, st);
-      u32x2 r[8];
-      fresh_v_load(s, r);
-      fresh_v_assemble(r, st);
-      return;
-    }
-    const int pi = real ? 2 * s : 0;                      // page index inside the split
-    const int o = real ? 1 : 0;
-    const int blk_a = block_of(ids, pi);
-    const int blk_b = block_of(ids, (real && pi + 1 < npg) ? pi + 1 : pi);
-    const char* pa = base + (size_t)blk_a * kBlockBytes + tid * 16;
-    const char* pb = base + (size_t)blk_b * kBlockBytes + tid * 16;
-    st[0] = *(const u32x4*)(pa);
-    st[1] = *(const u32x4*)(pa + o * 4096);
-    st[2] = *(const u32x4*)(pb);
-    st[3] = *(const u32x4*)(pb + o * 4096);
-    st[4] = *(const u32x4*)(pa + o * kPageBytes);
-    st[5] = *(const u32x4*)(pa + o * (kPageBytes + 4096));
-    st[6] = *(const u32x4*)(pb + o * kPageBytes);
-    st[7] = *(const u32x4*)(pb + o * (kPageBytes + 4096));
-  };
-  // Values of keys beyond the split's end are zero-selected once, on their way into LDS (only
-  // the last step of a split can have any); the asm statement keeps this a real branch.
-  // Thread tid holds V chunks tid and tid+256 of each page: chunk ci = (c, gp, m) with gp =
-  // (ci >> 4) & 1, i.e. keys 4gp..4gp+3 and 8+4gp..8+4gp+3 of that page.
-  auto sanitize = [&](const int s, u32x4 (&st)[8]) {
-    const int left = wi.kv_end - (wi.kv_begin + 32 * s);
-    if (s < nsteps && left < 32) {
-      asm volatile("" ::: "memory");
-      if constexpr (kFresh) {   // four chunks of page tid / 128, all with the same eight keys
-        const int k0 = 16 * (tid >> 7) + 4 * (((tid & 127) >> 2) & 1);
-        u32x4 mask;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          mask[i] = (k0 + 2 * i < left ? 0xffffu : 0u) | (k0 + 2 * i + 1 < left ? 0xffff0000u : 0u);
-          mask[2 + i] = (k0 + 8 + 2 * i < left ? 0xffffu : 0u) | (k0 + 9 + 2 * i < left ? 0xffff0000u : 0u);
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) st[4 + j] &= mask;
-        return;
-      }
-      const int gp = (tid >> 4) & 1;
-#pragma unroll
-      for (int pgi = 0; pgi < 2; ++pgi) {
-        const int k0 = 16 * pgi + 4 * gp;
-        u32x4 mask;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          mask[i] = (k0 + 2 * i < left ? 0xffffu : 0u) | (k0 + 2 * i + 1 < left ? 0xffff0000u : 0u);
-          mask[2 + i] = (k0 + 8 + 2 * i < left ? 0xffffu : 0u) | (k0 + 9 + 2 * i < left ? 0xffff0000u : 0u);
-        }
-        st[4 + 2 * pgi] &= mask;
-        st[5 + 2 * pgi] &= mask;
-      }
-    }
-  };
-  auto commit = [&](const int stage, const u32x4 (&st)[8]) {
-    char* dst = smem + stage * kStageBytes + tid * 16;
-    *(u32x4*)(dst + kOffKA) = st[0];
-    *(u32x4*)(dst + kOffKA + 4096) = st[1];
-    *(u32x4*)(dst + kOffKB) = st[2];
-    *(u32x4*)(dst + kOffKB + 4096) = st[3];
-    if constexpr (kFresh) {   // chunks 4q..4q+3 of page tid / 128
-      char* vd = smem + stage * kStageBytes + ((tid >> 7) ? kOffVB : kOffVA) + (tid & 127) * 64;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) *(u32x4*)(vd + j * 16) = st[4 + j];
-      return;
-    }
-    *(u32x4*)(dst + kOffVA) = st[4];
-    *(u32x4*)(dst + kOffVA + 4096) = st[5];
-    *(u32x4*)(dst + kOffVB) = st[6];
-    *(u32x4*)(dst + kOffVB + 4096) = st[7];
-  };
-  // per-lane LDS offsets of this lane's operands: K of key n%8 in page n/8, V of page g/2
-  const int lds_k = ((n >> 3) ? kOffKB : kOffKA) + (g * 8 + (n & 7)) * 16;
-  const int lds_v = ((g >> 1) ? kOffVB : kOffVA) + ((g & 1) * 16 + n) * 16;
-  auto compute = [&](const int s) {
-    const int pos = wi.kv_begin + 32 * s;
-    const int left = wi.kv_end - pos;
-    const char* sk = smem + (s & 1) * kStageBytes;
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      s0 = mfma16(*(const u32x4*)(sk + lds_k + j * 1024), qf[j], s0);
-      s1 = mfma16(*(const u32x4*)(sk + lds_k + j * 1024 + 512), qf[j], s1);
-    }
-    // eight operand reads ahead of the products: left to itself the compiler keeps two in
-    // flight, and every product then waits a full LDS round trip
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
-    u32x4 pf, pl;
-    softmax_step(s0, s1, left < 32 || pos + 31 > wi.q0, pos, wi.kv_end, qpos, g, sl2, m, l, acc,
-                 pf, pl);
-#pragma unroll
-    for (int c = 0; c < 16; ++c) {   // V was sanitised on its way into LDS
-      const u32x4 v = *(const u32x4*)(sk + lds_v + c * 512);
-      acc[c] = mfma16(v, pl, mfma16(v, pf, acc[c]));
-    }
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 1);   // as above: eight reads ahead
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 1);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 16, 1);
-  };
-  // body(s, cur, nxt): cur's content (step s) already sits in LDS, nxt holds step s+1 in
-  // flight.  The scheduling barriers keep the order "issue s+2, compute s, then wait for s+1",
-  // otherwise the wait would be hoisted above the compute.
-  auto body = [&](const int s, u32x4 (&cur)[8], u32x4 (&nxt)[8]) {
-    fetch(s + 2, cur);
-    __builtin_amdgcn_sched_barrier(0);
-    if (wave_active && s < nsteps) compute(s);
-    __builtin_amdgcn_sched_barrier(0);
-    if (s + 1 < nsteps) {   // after the last step only the barrier is left: the epilogue reuses LDS
-      sanitize(s + 1, nxt);
-      commit((s + 1) & 1, nxt);
-    }
-    __syncthreads();
-  };
-  auto load_q = [&]() {
-    const char* qrow = (const char*)a.q + ((size_t)tok * kHeads + h) * (kDim * 2);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      // unconditional (a row past the tile's tokens re-reads its last token's row, see `tok`)
-      // and zeroed afterwards: see split_block_ids for why no load sits under a condition
-      const u32x4 z = {0, 0, 0, 0};
-      const u32x4 x = *(const u32x4*)(qrow + j * 64 + g * 16);
-      qf[j] = row_valid ? x : z;
-    }
-  };
-  if constexpr (kFresh) {
-    // Step 0 first: its rows have to pass through the transpose, LDS and a barrier before the
-    // first product, the query rows only have to be in registers by then.  Every load of steps
-    // 0 and 1 goes out before the first transpose waits for its rows.
-    u32x2 r0[8], r1[8];
-    fetch_fresh_k(0, st0);
-    fresh_v_load(0, r0);
-    __builtin_amdgcn_sched_barrier(0);
-    load_q();
-    __builtin_amdgcn_sched_barrier(0);
-    if (nsteps > 1) {
-      fetch_fresh_k(1, st1);
-      fresh_v_load(1, r1);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    fresh_v_assemble(r0, st0);
-    if (nsteps > 1) fresh_v_assemble(r1, st1);
-  } else {
-    // the query rows are requested first: loads complete in order per wavefront, and the
-    // first product should wait for step 0 only, not for step 1 as well
-    load_q();
-    __builtin_amdgcn_sched_barrier(0);
-    fetch(0, st0);
-    fetch(1, st1);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  sanitize(0, st0);
-  commit(0, st0);
-  __syncthreads();
-  for (int s = 0; s < nsteps; s += 2) {   // steps in pairs: the two register stages swap roles
-    body(s, st0, st1);
-    if (s + 1 < nsteps) body(s + 1, st1, st0);
-  }
-  l = row_sum4(l);
-  // The partial leaves as (m, l, scale, acc / scale in fp16): half the bytes of fp32, and the
-  // per-row scale (max |acc| of the row) keeps it independent of the magnitude of the values.
   float amax = 0.f;
 #pragma unroll
-  for (int c = 0; c < 16; ++c)
+  for (int c = 0; c < 4; ++c)
 #pragma unroll
     for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fabsf(acc[c][e]));
   amax = row_max4(amax);
-  const float inv = amax > 0.f ? 1.f / amax : 0.f;
-  // Each lane holds 4-dim pieces of its row; written as they are, a store would touch 16 rows
-  // with 32 bytes each.  The rows go through LDS instead (the stages are free after the loop's
-  // last barrier; every wavefront uses a region of its own, so no barrier is needed) and leave
-  // as whole rows: 32 lanes x 16 bytes per row.
-  typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
-  char* ep = smem + wv * (16 * kEpilogueStride);
+  // biased exponent of amax, kept where 2^(14 - exponent) is a normal number
+  const int eb = max(24, min(253, (int)(__float_as_uint(amax) >> 23)));
+  const float up = __uint_as_float((uint32_t)(127 + 14 + 126 - eb) << 23);
+  const int ex = eb - 126;
+  u32x4 o[2];
 #pragma unroll
-  for (int c = 0; c < 16; ++c) {
-    const u32x2 v = {pack_f16(acc[c][0] * inv, acc[c][1] * inv),
-                     pack_f16(acc[c][2] * inv, acc[c][3] * inv)};
-    *(u32x2*)(ep + n * kEpilogueStride + (16 * c + 4 * g) * 2) = v;
+  for (int e = 0; e < 4; ++e) {
+    o[e >> 1][2 * (e & 1)] = pack_f16(acc[0][e] * up, acc[1][e] * up);
+    o[e >> 1][2 * (e & 1) + 1] = pack_f16(acc[2][e] * up, acc[3][e] * up);
   }
-  asm volatile("" ::: "memory");   // the reads below are of another type: keep them behind the writes
-  const int slot_lane = (n >> 3) ? part_b : part_a;   // of this lane's row n
-  if (row_valid && g == 0)
-    *(f32x4*)(a.part_ml + ((size_t)slot_lane * kHeads + h) * 4) = (f32x4){m, l, amax, 0.f};
+  // Lane g of a row holds 16-byte pieces 2g and 2g+1 of the row's eight: exchanged so that the
+  // four lanes of a row store pieces 0..3 together and then 4..7, 64 contiguous bytes each time.
 #pragma unroll
-  for (int it = 0; it < 8; ++it) {
-    const int row = 2 * it + (lane >> 5);              // row of this wavefront's 16
-    const int slot_row = (it >> 2) ? part_b : part_a;  // rows 0..7: first token, 8..15: second
-    const u32x4 v = *(const u32x4*)(ep + row * kEpilogueStride + (lane & 31) * 16);
-    if (2 * wv + (row >> 3) < wi.n_tok)
-      *(u32x4*)(a.part_acc + ((size_t)slot_row * kHeads + (row & 7)) * kDim + (lane & 31) * 8) = v;
+  for (int i = 0; i < 4; ++i) {
+    const auto x = __builtin_amdgcn_permlane16_swap(o[0][i], o[1][i], false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(x[0], x[1], false, false);
+    o[0][i] = y[0];
+    o[1][i] = y[1];
+  }
+  if (2 * group + (n >> 3) < wi.n_tok) {
+    const size_t row = (size_t)slot * kHeads + (n & 7);
+    u32x4* dst = (u32x4*)(a.part_acc + row * kDim + 64 * wv + 8 * g);
+    dst[0] = o[0];
+    dst[4] = o[1];
+    if (g == 0) ((int8_t*)(a.part_ml + row * 4 + 2))[wv] = (int8_t)ex;
   }
 }
 
-// ---- stream path: <= 2 query tokens (16 rows, the decode case).  Nothing is shared, so the
-// four wavefronts take the 32-key steps of the split round-robin, stream their pages straight
-// into registers one step ahead, and combine their four results through LDS.
-// kOwnPages: the key range lies in the item's own pages, which no other workgroup of the launch
-// reads (and which receive the item's new rows when the append is folded in); otherwise the
-// pages are a prefix's and other workgroups read them too.
-template <bool kOwnPages>
-__device__ __forceinline__ void stream_path(const AttnArgs& a, const WorkItem& wi, char* smem,
-                                            float (*sml)[16][2], char* qs) {
-  constexpr bool appends = kOwnPages;
-  const int tid = threadIdx.x, lane = tid & 63;
+// Bound by the memory pipeline of the CU where a launch is large (128 KiB of pages per workgroup and
+// round, two workgroups per CU), by the length of this chain where it is small.
+//
+// One work item: up to 2*G query tokens (G groups of 16 rows) against one split of a KV source,
+// taken in rounds of 128 keys.  In a round wavefront w
+//   1. holds the K operands of keys 32w..32w+31 in registers and computes S^T for all rows,
+//   2. publishes each row's largest logit, and after a barrier takes the row's largest of all 128,
+//   3. writes its P (hi + lo bf16, relative to the common reference max) to LDS,
+//   4. after a second barrier contracts ALL 128 keys for dims 64w..64w+63, whose V operands it
+//      loaded itself.
+// K and V thus go from memory to registers exactly once per work item and never through LDS; what
+// the wavefronts exchange is P (2 KiB per group and step).  The accumulator is 16 registers per
+// group, no combination of per-wavefront accumulators follows, and a work item of eight tokens fits
+// the registers of two workgroups per CU.  (Before: work items of up to two tokens kept a
+// 64-register accumulator per wavefront and combined the four through 66 KiB of LDS, 1.1 us of a
+// 4 us work item, now 0.4; larger ones staged K and V in LDS, where each of the four wavefronts
+// read all of both.  Work-item launch of 64 requests on 2048-token prefixes 20.7 -> 19.4 us, of
+// one request on 832 tokens 5.5 -> 5.0 us.)
+//
+// A row's arithmetic does not depend on G or on the other rows: a query may be evaluated alone or
+// beside any others and gives the same bits.
+//
+// kOwnPages: a decode item's own pages, read by this work item alone (non-temporal loads, so that
+// they do not push shared pages out of the L2), which also writes the item's new rows when the
+// append is folded in.  Otherwise the pages are a prefix's or a multi-token item's, and other work
+// items read them too.
+template <int G, bool kOwnPages>
+__device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
+  int tid = threadIdx.x;
+  // keeps what is computed from the thread id inside this instance: shared with the other
+  // instances of the kernel it would have to live across all of them, which costs G = 4 spills
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: keep it scalar
   const int n = lane & 15, g = lane >> 4;
-  const int ts = n >> 3, h = n & 7;
-  const bool row_valid = ts < wi.n_tok;
-  const int tok_a = __builtin_amdgcn_readlane(wi.rec, 8), tok_b = __builtin_amdgcn_readlane(wi.rec, 9);
-  const int tok = (row_valid && ts) ? tok_b : tok_a;
-  const int qpos = wi.q0 + ts;
-  // In the epilogue thread tid writes 16 dims of row tid / 16; the first partial slot of that
-  // row's token is loaded now so that the epilogue does not wait for it.
-  const int otok = ((wv >> 1) && wi.n_tok > 1) ? tok_b : tok_a;
-  const int part_base = a.part_off[otok];
-  float m = -__builtin_inff(), l = 0.f;
-  f32x4 acc[16];
-#pragma unroll
-  for (int c = 0; c < 16; ++c) acc[c] = (f32x4){0.f, 0.f, 0.f, 0.f};
-  const float sl2 = a.scale * 1.4426950408889634f;
+  const int h = n & 7, sub = n >> 3;
+  const float ninf = -__builtin_inff();
+  const float sl2 = log2_scale(a);
   const char* __restrict__ base = (const char*)a.layer_base;
   const int nsteps = (wi.kv_end - wi.kv_begin + 31) >> 5;
-
-  u32x4 kr[16], vr[16];   // kr[2j+hf]: K chunk of (j, hf); vr[c]: V chunk of block c
+  const int rounds = (nsteps + 3) >> 2;
   const int npg = ((wi.kv_end + 15) >> 4) - (wi.kv_begin >> 4);
-  const SplitIds ids = split_block_ids(wi, lane, npg);
-  const int lane_k = (g * 8 + (n & 7)) * 16;
-  const int lane_v = kPageBytes + ((g & 1) * 16 + n) * 16;
-  // A wavefront has at most one step in flight beyond the one it computes, and it waits for all
-  // of it before the next product, so (unlike the tile path) nothing is lost when the load of
-  // a step past the end is simply skipped; a missing page B re-reads page A and is masked.
-  // Own pages are read once per launch, by this workgroup alone: their loads carry the
-  // non-temporal hint, so that they do not push the pages that other workgroups share out of
-  // the L2.
+
+
+  u32x4 kr[16];      // kr[2j+hf]: K operand (j, hf) of this wavefront's 32 keys
+  u32x4 vr[4][4];    // vr[s][c]: V operand c of this wavefront's 64 dims, step s of the round
   auto page_load = [](const char* p) {
     if constexpr (kOwnPages) return __builtin_nontemporal_load((const u32x4*)p);
     return *(const u32x4*)p;
   };
-  auto load_k_at = [&](const int s) {
-    const int pi = 2 * s;
-    const int blk_a = block_of(ids, pi);
-    const int blk_b = block_of(ids, pi + 1 < npg ? pi + 1 : pi);
-    const char* p = base + (size_t)((n >> 3) ? blk_b : blk_a) * kBlockBytes + lane_k;
+  // A step past the split's end re-reads a page of the split; its logits are masked and its V
+  // operands are not used.  The block ids of the first two rounds are in the record (no dependent
+  // load in front of the first pages), those of later rounds in the block table.
+  // Lane offsets are formed anew at every use (the asm statements): hoisted out of the rounds as
+  // 64-bit addresses they cost four groups the registers that they do not have.
+  auto load_k_of = [&](const int blk_a, const int blk_b) {
+    int off = (g * 8 + (n & 7)) * 16;
+    asm volatile("" : "+v"(off));
+    const char* p = base + (size_t)((n >> 3) ? blk_b : blk_a) * kBlockBytes + off;
 #pragma unroll
     for (int i = 0; i < 16; ++i) kr[i] = page_load(p + i * 512);
   };
-  auto load_v_at = [&](const int s) {
-    const int pi = 2 * s;
-    const int blk_a = block_of(ids, pi);
-    const int blk_b = block_of(ids, pi + 1 < npg ? pi + 1 : pi);
-    const char* p = base + (size_t)((g >> 1) ? blk_b : blk_a) * kBlockBytes + lane_v;
+  auto load_v_of = [&](const i32x8 blks) {
+    int off = kPageBytes + v_chunk_offset(wv, 0, g & 1, n);
+    asm volatile("" : "+v"(off));
 #pragma unroll
-    for (int c = 0; c < 16; ++c) vr[c] = page_load(p + c * 512);
+    for (int s = 0; s < 4; ++s) {
+      const char* p = base + (size_t)((g >> 1) ? blks[2 * s + 1] : blks[2 * s]) * kBlockBytes + off;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) vr[s][c] = page_load(p + c * 512);
+    }
   };
-  auto load_k = [&](const int s) {
-    if (s < nsteps) load_k_at(s);
+  auto load_k = [&](const int round) {
+    if (round < 2) {
+      const DescPtr id = wi.rec + 16 + 8 * round + 2 * wv;
+      load_k_of(id[0], id[1]);
+    } else {
+      const DescPtr ids = wi.tbl + (wi.kv_begin >> 4);
+      const int pi = 8 * round + 2 * wv;
+      load_k_of(ids[min(pi, npg - 1)], ids[min(pi + 1, npg - 1)]);
+    }
   };
-  auto load_v = [&](const int s) {
-    if (s < nsteps) load_v_at(s);
+  auto load_v = [&](const int round) {
+    if (round < 2) {
+      load_v_of(*(DescPtr8)(wi.rec + 16 + 8 * round));
+    } else {
+      const DescPtr ids = wi.tbl + (wi.kv_begin >> 4);
+      i32x8 blks;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) blks[i] = ids[min(8 * round + i, npg - 1)];
+      load_v_of(blks);
+    }
   };
-  // Folded append: the query tokens of a streaming item are its new rows.  Those inside this
-  // split's key range are written to the pool by this workgroup (no other workgroup reads
+
+  // Folded append: the query tokens of an item on its own pages are its new rows.  Those inside
+  // this split's key range are written to the pool by this workgroup (no other workgroup reads
   // them in this launch), and a workgroup barrier orders the writes before the page loads that
-  // cover them.  The first new row sits in step `first_new`: when that step is loaded after the
-  // barrier below anyway, the stores wait there; otherwise they go out, with a barrier of their
-  // own, before the first page load.
+  // cover them.  The first new row sits in step `first_new`: when that step belongs to a later
+  // round, its loads come after the barriers of the first one anyway; otherwise the rows go out,
+  // with a barrier of their own, before the first page load.
   RowPart rows[2];
-  int32_t slot2 = 0;   // lane j % 2: pool slot of the record's token j
+  int32_t row_slot[2] = {0, 0};
   bool row_mine[2] = {false, false};
   bool early = false;
-  const bool fold = a.k_new && appends;
+  const bool fold = kOwnPages && a.k_new;
   if (fold) {
     const int pos0 = (wi.q0 == kNoCausal ? 0 : wi.q0);
+    const int ta = wi.toks[0], tb = wi.toks[1];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const int pos = pos0 + t;
       row_mine[t] = t < wi.n_tok && pos >= wi.kv_begin && pos < wi.kv_end;
-      const int tk = __builtin_amdgcn_readlane(wi.rec, 8 + t);
+      const int tk = t ? tb : ta;
       rows[t] = load_row((const uint16_t*)a.k_new + (size_t)tk * kDim,
                          (const uint16_t*)a.v_new + (size_t)tk * kDim, tid);
     }
-    slot2 = a.d_slots[(lane & 1) ? tok_b : tok_a];   // one load per lane, read with v_readlane
+    row_slot[0] = ((DescPtr)a.d_slots)[ta];
+    row_slot[1] = ((DescPtr)a.d_slots)[tb];
     const int first_new = (max(pos0, wi.kv_begin) - wi.kv_begin) >> 5;
     early = first_new < 4;
     if (early) {
 #pragma unroll
       for (int t = 0; t < 2; ++t)
         if (row_mine[t])
-          store_row(rows[t], __builtin_amdgcn_readlane(slot2, t), (char*)a.layer_base, tid);
+          store_row(rows[t], row_slot[t], (char*)a.layer_base, tid);
       __syncthreads();
     }
   }
-  // The 16 query rows are the same for all four wavefronts: their MFMA fragments live in LDS
-  // (registers are needed for the pages in flight).  The query loads are issued BEFORE the first
-  // pages: loads complete in order per wavefront, so the barrier below then waits for the
-  // queries only, not for the slowest wavefront's first 32 KiB.
-  u32x4 qtmp[2];
+  // The query loads are issued BEFORE the first pages: loads complete in order per wavefront, so
+  // the barrier below waits for the queries only, not for the slowest wavefront's first 32 KiB.
+  int slot_req;
   {
-    const char* qrow = (const char*)a.q + ((size_t)tok * kHeads + h) * (kDim * 2);
-    const u32x4 z = {0, 0, 0, 0};
+    u32x4 qtmp[G][2];
 #pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {   // unconditional, zeroed afterwards (see split_block_ids)
-      const u32x4 x = *(const u32x4*)(qrow + (2 * wv + jj) * 64 + g * 16);
-      qtmp[jj] = row_valid ? x : z;
+    for (int r = 0; r < G; ++r) {
+      const char* qrow = (const char*)a.q + ((size_t)token_of(wi, r, sub) * kHeads + h) * (kDim * 2);
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj)   // unconditional, zeroed afterwards
+        qtmp[r][jj] = *(const u32x4*)(qrow + (2 * wv + jj) * 64 + g * 16);
+    }
+    slot_req = request_slot<G>(a, wi, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    load_k_of(wi.rec[16 + 2 * wv], wi.rec[17 + 2 * wv]);
+    load_v_of(wi.pages);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+      const u32x4 z = {0, 0, 0, 0};
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj)
+        sm.q[r][2 * wv + jj][lane] = 2 * r + sub < wi.n_tok ? query_sign(a, qtmp[r][jj]) : z;
     }
   }
-  int s = wv;
-  // The first step's loads are unconditional as well: a wavefront without a step of its own
-  // (a split of fewer than four steps) re-reads the split's last step and never uses it.  With
-  // the number of loads in flight known, the store of the queries below waits for the queries
-  // only, and the barrier after it no longer ties the four wavefronts to the slowest first step.
-  load_k_at(s < nsteps ? s : nsteps - 1);
-  load_v_at(s < nsteps ? s : nsteps - 1);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int jj = 0; jj < 2; ++jj) *(u32x4*)(qs + (2 * wv + jj) * 1024 + lane * 16) = qtmp[jj];
+  if (tid < 2 * G) sm.slot[tid] = slot_req + wi.part_idx;
   if (fold && !early) {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
       if (row_mine[t])
-        store_row(rows[t], __builtin_amdgcn_readlane(slot2, t), (char*)a.layer_base, tid);
+        store_row(rows[t], row_slot[t], (char*)a.layer_base, tid);
   }
   __syncthreads();
-  const char* qf = qs + lane * 16;
-  for (; s < nsteps; s += 4) {
-    const int pos = wi.kv_begin + 32 * s;
+
+  float m[G], l[G];   // reference max (scaled log2 domain) of this lane's row, and the sum of P
+  f32x4 acc[G][4];    // over this wavefront's keys; acc[r][c][e] = dim 64w + 16g + 4e + c
+#pragma unroll
+  for (int r = 0; r < G; ++r) {
+    m[r] = ninf;
+    l[r] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[r][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+
+  // kLast: the split's last round, the only one with steps past the end or a partial step.  It is
+  // a copy of its own so that the loads of the other rounds sit under no condition.
+  auto round_body = [&](const int round, auto last) {
+    constexpr bool kLast = decltype(last)::value;
+    int lane_now = tid & 63;   // likewise, for the mask limits and LDS addresses
+    asm volatile("" : "+v"(lane_now));
+    const int lane = lane_now, n = lane & 15, g = lane >> 4, sub = n >> 3;
+    const int pos = wi.kv_begin + 32 * (4 * round + wv);
     const int left = wi.kv_end - pos;
-    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+    const bool need_mask = (kLast && left < 32) || pos + 31 > wi.q0;
+    constexpr int kAhead = G == 4 ? 2 : 4;
+    f32x4 s0[G], s1[G];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const u32x4 q = *(const u32x4*)(qf + j * 1024);
-      s0 = mfma16(kr[2 * j], q, s0);
-      s1 = mfma16(kr[2 * j + 1], q, s1);
-    }
-    // four query reads ahead of the products (see the tile path)
-    __builtin_amdgcn_sched_group_barrier(0x100, 4, 2);
+    for (int r = 0; r < G; ++r) {
+      s0[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      s1[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 2);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 2);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 8, 2);
-    u32x4 pf, pl;
-    softmax_step(s0, s1, left < 32 || pos + 31 > wi.q0, pos, wi.kv_end, qpos, g, sl2, m, l, acc,
-                 pf, pl);
-    __builtin_amdgcn_sched_barrier(0);  // the next K pages reuse kr[]: issue only after S
-    load_k(s + 4);
-    __builtin_amdgcn_sched_barrier(0);
-    if (left < 32) {   // wave-uniform; only the last step of a split (asm: keep it a branch)
-      asm volatile("" ::: "memory");
-      const u32x4 mask = value_mask(left, g);
-#pragma unroll
-      for (int c = 0; c < 16; ++c) vr[c] &= mask;
-    }
-#pragma unroll
-    for (int c = 0; c < 16; ++c) acc[c] = mfma16(vr[c], pl, mfma16(vr[c], pf, acc[c]));
-    __builtin_amdgcn_sched_barrier(0);  // likewise vr[]
-    load_v(s + 4);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  l = row_sum4(l);
-  // combine the four wavefronts' results (log-sum-exp rule) and write one partial
-  float* sm = (float*)smem;
-#pragma unroll
-  for (int c = 0; c < 16; ++c)
-    *(f32x4*)(sm + (wv * 16 + n) * kMergeStride + 16 * c + 4 * g) = acc[c];
-  if (g == 0) {
-    sml[wv][n][0] = m;
-    sml[wv][n][1] = l;
-  }
-  __syncthreads();
-  // thread tid: row tid / 16, dims [8t, 8t+8) and [128+8t, 128+8t+8) with t = tid % 16, so that
-  // the 16 threads of a row write 256 contiguous bytes per store
-  const int r = tid >> 4, seg = (tid & 15) * 8;
-  if ((r >> 3) < wi.n_tok) {
-    const float ninf = -__builtin_inff();
-    float big = ninf;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) big = fmaxf(big, sml[w][r][0]);
-    float wgt[4], total = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      wgt[w] = (sml[w][r][0] == ninf) ? 0.f : fast_exp2(sml[w][r][0] - big);
-      total = __builtin_fmaf(wgt[w], sml[w][r][1], total);
-    }
-    const size_t slot = (size_t)part_base + wi.part_idx;
-    uint16_t* dst = a.part_acc + (slot * kHeads + (r & 7)) * kDim + seg;
-    f32x4 o[4];
-    float amax = 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int d = seg + 4 * (q & 1) + 128 * (q >> 1);
-      o[q] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const f32x4 x = *(const f32x4*)(sm + (w * 16 + r) * kMergeStride + d);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[q][e] = __builtin_fmaf(wgt[w], x[e], o[q][e]);
+      for (int j = 0; j < 8; ++j) {
+        const u32x4 q = sm.q[r][j][lane];
+        s0[r] = mfma16(kr[2 * j], q, s0[r]);
+        s1[r] = mfma16(kr[2 * j + 1], q, s1[r]);
       }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) amax = fmaxf(amax, fabsf(o[q][e]));
     }
-    // row scale over the 16 threads that hold this row (the branch is uniform per wavefront)
-    amax = lanes16_max(amax);
-    const float inv = amax > 0.f ? 1.f / amax : 0.f;
-    const u32x4 lo = {pack_f16(o[0][0] * inv, o[0][1] * inv), pack_f16(o[0][2] * inv, o[0][3] * inv),
-                      pack_f16(o[1][0] * inv, o[1][1] * inv), pack_f16(o[1][2] * inv, o[1][3] * inv)};
-    const u32x4 hi = {pack_f16(o[2][0] * inv, o[2][1] * inv), pack_f16(o[2][2] * inv, o[2][3] * inv),
-                      pack_f16(o[3][0] * inv, o[3][1] * inv), pack_f16(o[3][2] * inv, o[3][3] * inv)};
-    *(u32x4*)(dst) = lo;
-    *(u32x4*)(dst + 128) = hi;
-    if ((tid & 15) == 0)
-      *(f32x4*)(a.part_ml + (slot * kHeads + (r & 7)) * 4) = (f32x4){big, total, amax, 0.f};
+    // a few query reads ahead of the products: more would cost registers that four groups do
+    // not leave, fewer make every pair of products wait a full LDS round trip
+    __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+    for (int i = 0; i < 8 * G - kAhead; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kAhead, 0);
+    if (need_mask) {   // wave-uniform: only the end of a split or the causal diagonal
+      const int k0 = pos + 16 * (g >> 1) + 4 * (g & 1);
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        const int end = min(wi.kv_end, wi.q0 + 2 * r + sub + 1) - k0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s0[r][e] = e < end ? s0[r][e] : ninf;
+          s1[r][e] = 8 + e < end ? s1[r][e] : ninf;
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+      const float mx = row_max4(row_max8(s0[r], s1[r]) * sl2);
+      if (g == 0) sm.mx[r][n][wv] = mx;
+    }
+    __syncthreads();
+    // Online softmax.  The reference max only moves when a logit exceeds it by more than kGrow,
+    // so the rescale of acc is rare; P is then at most 2^kGrow, well inside fp32/bf16 range.  P
+    // travels as hi+lo bf16: a single bf16 rounding (2^-9 relative) is too coarse for queries that
+    // see only a handful of keys.
+    float mx[G];
+    bool grow = false;   // true for the first finite logit too (m = -inf)
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+      const f32x4 mw = *(const f32x4*)sm.mx[r][n];
+      mx[r] = fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3]));
+      grow |= mx[r] > m[r] + kGrow;
+    }
+    if (__any(grow)) {
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        const bool up = mx[r] > m[r] + kGrow;
+        const float alpha = up ? fast_exp2(m[r] - mx[r]) : 1.f;   // m = -inf gives 0
+        l[r] *= alpha;
+        if (round > 0) {   // acc holds zeros before
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[r][c] *= alpha;
+        }
+        m[r] = up ? mx[r] : m[r];
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < G; ++r) {
+      u32x4 hi, lo;
+      l[r] += softmax_weights(s0[r], s1[r], sl2, (m[r] == ninf) ? 0.f : m[r], hi, lo);
+      sm.p[wv][r][0][lane] = hi;
+      sm.p[wv][r][1][lane] = lo;
+      if constexpr (kLast) sm.ls[r][lane][wv] = l[r];
+    }
+    __builtin_amdgcn_sched_barrier(0);   // the next K operands reuse kr[]
+    if constexpr (!kLast) load_k(round + 1);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();
+    // With one group all P operands are requested at once, in front of the branches of a last
+    // round; with more the products of one group hide the reads of the next.
+    u32x4 ph[4], pl[4];
+    if constexpr (G == 1) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        ph[s] = sm.p[s][0][0][lane];
+        pl[s] = sm.p[s][0][1][lane];
+      }
+    }
+    auto contract = [&](const int s) {
+#pragma unroll
+      for (int r = 0; r < G; ++r) {
+        const u32x4 hi = G == 1 ? ph[s] : sm.p[s][r][0][lane];
+        const u32x4 lo = G == 1 ? pl[s] : sm.p[s][r][1][lane];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(vr[s][c], hi, acc[r][c]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(vr[s][c], lo, acc[r][c]);
+      }
+    };
+    if constexpr (!kLast) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) contract(s);
+      __builtin_amdgcn_sched_barrier(0);   // likewise vr[]
+      load_v(round + 1);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      const int nv = nsteps - 4 * round;   // 1..4 steps
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        if (s < nv) {
+          const int left_s = wi.kv_end - (wi.kv_begin + 32 * (4 * round + s));
+          if (left_s < 32) {
+            const u32x4 mask = value_mask(left_s, g);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) vr[s][c] &= mask;
+          }
+          contract(s);
+        }
+    }
+  };
+  for (int round = 0; round + 1 < rounds; ++round) round_body(round, std::false_type());
+  round_body(rounds - 1, std::true_type());
+
+#pragma unroll
+  for (int r = 0; r < G; ++r) {
+    const int slot = sm.slot[2 * r + sub];
+    store_part(a, wi, slot, acc[r], r, wv, lane);
+    if (wv == r) {   // wave-uniform: the sums of the groups are shared out
+      const f32x4 lw = *(const f32x4*)sm.ls[r][lane];
+      const float total = row_sum4((lw[0] + lw[1]) + (lw[2] + lw[3]));
+      if (g == 0 && 2 * r + sub < wi.n_tok)
+        *(f32x2*)(a.part_ml + ((size_t)slot * kHeads + h) * 4) = (f32x2){m[r], total};
+    }
   }
 }
 
-__global__ __launch_bounds__(256, 2) void attn_kernel(const AttnArgs a) {
-  __shared__ __align__(16) char smem[kSmemBytes];
-  __shared__ float sml[4][16][2];
-  __shared__ __align__(16) char qs[16 * kDim * 2];
-  // one 128-byte load brings the whole record; its fields are read out lane-wise
-  WorkItem wi;
-  wi.rec = a.work[(size_t)blockIdx.x * kWorkWords + (threadIdx.x & 31)];
-  wi.n_tok = __builtin_amdgcn_readlane(wi.rec, W_N_TOK);
-  wi.tbl = a.tables + __builtin_amdgcn_readlane(wi.rec, W_TBL_OFF);
-  wi.kv_begin = __builtin_amdgcn_readlane(wi.rec, W_KV_BEGIN);
-  wi.kv_end = __builtin_amdgcn_readlane(wi.rec, W_KV_END);
-  wi.q0 = __builtin_amdgcn_readlane(wi.rec, W_CAUSAL_Q0);
-  wi.part_idx = __builtin_amdgcn_readlane(wi.rec, W_PART_IDX);
-  const int path_word = __builtin_amdgcn_readlane(wi.rec, W_PATH);
-  const int path = path_word & kPathMask;
-  if (path == PATH_TILE) {
-    __builtin_amdgcn_s_setprio(2);   // compute-heavy: issue ahead of co-resident streaming waves
-    if (a.k_new && (path_word & kPathFresh))
-      tile_path<true>(a, wi, smem, path_word >> kPathRowShift);
-    else
-      tile_path<false>(a, wi, smem, 0);
-  } else if (path == PATH_STREAM) {
-    if (path_word & kPathAppends)
-      stream_path<true>(a, wi, smem, sml, qs);
-    else
-      stream_path<false>(a, wi, smem, sml, qs);
-  } else {
-    return;   // padding record
+// Own phase of an item whose history was empty before the step (an action chunk): up to eight
+// tokens whose keys are this step's new rows.  With the append folded in they are read from
+// k_new / v_new, and the pool receives them from the merge launch of the same layer.  A split is one 32-key step
+// or a few, so the wavefronts share the rows out, not the keys: wavefront w computes the logits
+// and P of tokens 2w and 2w+1, with the K operands brought in by all four through LDS, and contracts
+// all tokens' P for its 64 dims as in `attend`.  (Each wavefront by itself, all of K, Q and V in its
+// own registers and no barrier, waits for four times the loads: 4.3 us until the logits are there
+// against 1.8 us for a single wavefront.)
+// Every sum is taken in the order of `attend`, rounds of 128 keys included, so that a folded
+// append and a separate one give the same bits.  kOneStep: the split is one step, and everything
+// it needs is requested at once; otherwise a step's operands are requested when it is their turn.
+// kRows: the keys are rows of k_new / v_new (row0 + own position); otherwise (the append went
+// before, one step only) they are read from the pages.
+template <bool kOneStep, bool kRows>
+__device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& wi, WorkLds& sm,
+                                             const int row0) {
+  static_assert(kOneStep || kRows, "several steps from pages go through attend");
+  constexpr int kSteps = kOneStep ? 1 : 4;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n = lane & 15, g = lane >> 4, h = n & 7, sub = n >> 3;
+  const float ninf = -__builtin_inff();
+  const float sl2 = log2_scale(a);
+  const int nsteps = (wi.kv_end - wi.kv_begin + 31) >> 5, last = wi.kv_end - 1;
+  const int n_groups = (wi.n_tok + 1) >> 1;
+  const uint16_t* kn = (const uint16_t*)a.k_new + (size_t)row0 * kDim + 64 * wv + 8 * g;
+  const uint16_t* vn = (const uint16_t*)a.v_new + (size_t)row0 * kDim + 64 * wv + 4 * n;
+  const int blk_a = wi.pages[0], blk_b = wi.pages[1];
+  const char* __restrict__ pages = (const char*)a.layer_base;
+  u32x4 (*ks)[64] = &sm.q[0][0];   // K operands of the step (the query rows stay in registers)
+
+  u32x4 kr[4], qf[8], vpage[4];
+  u32x2 vr[8];   // [key]: dims 64w+4n..+3 of this lane's eight keys, as they lie in the row
+  // this wavefront's quarter of the step's K operands: dims 64w..64w+63.  Positions at or beyond
+  // the split's end re-read its last row and are masked.
+  auto load_k = [&](const int s) {
+    if constexpr (!kRows) {
+      const char* p = pages + (size_t)(sub ? blk_b : blk_a) * kBlockBytes + (g * 8 + h) * 16;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) kr[i] = *(const u32x4*)(p + (4 * wv + i) * 512);
+      return;
+    }
+    const int pos = wi.kv_begin + 32 * s + 16 * sub + h;
+    const uint16_t* r0 = kn + (size_t)min(pos, last) * kDim;
+    const uint16_t* r1 = kn + (size_t)min(pos + 8, last) * kDim;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      kr[2 * j] = *(const u32x4*)(r0 + 32 * j);
+      kr[2 * j + 1] = *(const u32x4*)(r1 + 32 * j);
+    }
+  };
+  auto load_v = [&](const int s) {
+    if constexpr (!kRows) {
+      const char* p = pages + (size_t)((g >> 1) ? blk_b : blk_a) * kBlockBytes + kPageBytes +
+                      v_chunk_offset(wv, 0, g & 1, n);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) vpage[c] = *(const u32x4*)(p + c * 512);
+      return;
+    }
+    const int pos = wi.kv_begin + 32 * s + 16 * (g >> 1) + 4 * (g & 1);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      vr[e] = *(const u32x2*)(vn + (size_t)min(pos + (e < 4 ? e : e + 4), last) * kDim);
+  };
+  if constexpr (kOneStep) load_k(0);
+  {   // wavefronts past the item's tokens hold its last token's rows and store nothing
+    const char* qrow = (const char*)a.q + ((size_t)token_of(wi, wv, sub) * kHeads + h) * (kDim * 2);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) qf[j] = *(const u32x4*)(qrow + j * 64 + g * 16);
   }
+  const int slot_req = request_slot<kMaxGroups>(a, wi, lane);
+  if constexpr (kOneStep) load_v(0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) qf[j] = query_sign(a, qf[j]);
+  float m_own = ninf, l[4] = {0.f, 0.f, 0.f, 0.f};   // of this wavefront's row n
+  f32x4 acc[kMaxGroups][4];
+#pragma unroll
+  for (int r = 0; r < kMaxGroups; ++r)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[r][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  for (int first = 0; first < (kOneStep ? 1 : nsteps); first += 4) {
+    f32x4 s0[kSteps], s1[kSteps];
+    float mx = ninf;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s)
+      if (kOneStep || first + s < nsteps) {
+        if constexpr (!kOneStep) {
+          __syncthreads();   // the previous step's operands are used up, the previous round's P too
+          load_k(first + s);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ks[4 * wv + i][lane] = kr[i];
+        if (kOneStep || s == 0)
+          if (threadIdx.x < 8) sm.slot[lane] = slot_req + wi.part_idx;
+        __syncthreads();
+        s0[s] = s1[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          s0[s] = mfma16(ks[2 * j][lane], qf[j], s0[s]);
+          s1[s] = mfma16(ks[2 * j + 1][lane], qf[j], s1[s]);
+        }
+        const int pos = wi.kv_begin + 32 * (first + s);
+        const int end = min(wi.kv_end, wi.q0 + 2 * wv + sub + 1) - (pos + 16 * (g >> 1) + 4 * (g & 1));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          s0[s][e] = e < end ? s0[s][e] : ninf;
+          s1[s][e] = 8 + e < end ? s1[s][e] : ninf;
+        }
+        mx = fmaxf(mx, row_max4(row_max8(s0[s], s1[s]) * sl2));
+      }
+    const bool up = mx > m_own + kGrow;
+    const float alpha = up ? fast_exp2(m_own - mx) : 1.f;
+    m_own = up ? mx : m_own;
+    if constexpr (!kOneStep) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) l[s] *= alpha;
+      if (g == 0) sm.mx[wv][n][0] = alpha;
+    }
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s)
+      if (kOneStep || first + s < nsteps) {
+        u32x4 hi, lo;
+        l[s] += softmax_weights(s0[s], s1[s], sl2, (m_own == ninf) ? 0.f : m_own, hi, lo);
+        sm.p[s][wv][0][lane] = hi;
+        sm.p[s][wv][1][lane] = lo;
+      }
+    __syncthreads();
+    if constexpr (!kOneStep) {
+#pragma unroll
+      for (int r = 0; r < kMaxGroups; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[r][c] *= sm.mx[r][n][0];
+    }
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s)
+      if (kOneStep || first + s < nsteps) {
+        if constexpr (!kOneStep) load_v(first + s);
+        const u32x4 mask = value_mask(wi.kv_end - (wi.kv_begin + 32 * (first + s)), g);
+        u32x4 v[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if constexpr (kRows) {   // dim 64w+4n+c: halfword c of every key
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const uint32_t x = vr[2 * i][c >> 1], y = vr[2 * i + 1][c >> 1];
+              v[c][i] = (c & 1) ? ((x >> 16) | (y & 0xffff0000u)) : ((x & 0xffffu) | (y << 16));
+            }
+          } else {
+            v[c] = vpage[c];
+          }
+          v[c] &= mask;
+        }
+#pragma unroll
+        for (int r = 0; r < kMaxGroups; ++r)
+          if (r < n_groups) {
+            const u32x4 hi = sm.p[s][r][0][lane], lo = sm.p[s][r][1][lane];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(v[c], hi, acc[r][c]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(v[c], lo, acc[r][c]);
+          }
+      }
+  }
+  const float total = row_sum4((l[0] + l[1]) + (l[2] + l[3]));
+  const int own_slot = sm.slot[2 * wv + sub];
+  if (g == 0 && 2 * wv + sub < wi.n_tok) {
+    *(f32x2*)(a.part_ml + ((size_t)own_slot * kHeads + h) * 4) = (f32x2){m_own, total};
+  }
+#pragma unroll
+  for (int r = 0; r < kMaxGroups; ++r) store_part(a, wi, sm.slot[2 * r + sub], acc[r], r, wv, lane);
+}
+
+__device__ __forceinline__ void attend_fresh_any(const AttnArgs& a, const WorkItem& wi, WorkLds& sm,
+                                                 const int row0) {
+  if (wi.kv_end - wi.kv_begin <= 32)
+    attend_fresh<true, true>(a, wi, sm, row0);
+  else
+    attend_fresh<false, true>(a, wi, sm, row0);
+}
+
+__device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
+  if (wi.n_tok <= 2)
+    attend<1, false>(a, wi, sm);
+  else if (wi.n_tok <= 4)
+    attend<2, false>(a, wi, sm);
+  else
+    attend<4, false>(a, wi, sm);
+}
+
+__global__ __launch_bounds__(256, 2) void attn_kernel(const AttnArgs a) {
+  __shared__ WorkLds sm;
+  WorkItem wi;
+  wi.rec = (DescPtr)a.work + (size_t)blockIdx.x * kWorkWords;
+  const i32x8 head = ((DescPtr8)wi.rec)[0];
+  wi.toks = ((DescPtr8)wi.rec)[1];
+  wi.pages = ((DescPtr8)wi.rec)[2];
+  // wanted here, in one go, and not one after the other where they are used first
+  asm volatile("" ::"s"(head), "s"(wi.toks), "s"(wi.pages), "s"(a.q), "s"(a.layer_base), "s"(a.tables),
+               "s"(a.part_off), "s"(a.part_acc), "s"(a.part_ml), "s"(a.k_new), "s"(a.v_new),
+               "s"(a.scale));
+  wi.n_tok = head[W_N_TOK];
+  wi.tbl = (DescPtr)a.tables + head[W_TBL_OFF];
+  wi.kv_begin = head[W_KV_BEGIN];
+  wi.kv_end = head[W_KV_END];
+  wi.q0 = head[W_CAUSAL_Q0];
+  wi.part_idx = head[W_PART_IDX];
+  const int path_word = head[W_PATH];
+  if ((path_word & kPathMask) == PATH_NOOP) return;   // padding record
+  if (path_word & kPathAppends)                       // one or two tokens on their own pages
+    attend<1, true>(a, wi, sm);
+  else if (a.k_new && (path_word & kPathFresh))
+    attend_fresh_any(a, wi, sm, path_word >> kPathRowShift);
+  else if ((path_word & kPathFresh) && wi.kv_end - wi.kv_begin <= 32)
+    attend_fresh<true, false>(a, wi, sm, 0);
+  else
+    attend_shared(a, wi, sm);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -931,6 +930,7 @@ constexpr int kMergeAhead = 16;   // partials whose loads are all issued before 
 __device__ __forceinline__ void merge_block(const AttnArgs& a, const int tok) {
   const int t = threadIdx.x;
   const int h = t >> 5, d0 = (t & 31) * 8;
+  const int ex_shift = 24 - 8 * (d0 >> 6);
   const int np = a.n_parts[tok];
   const size_t base = (size_t)a.part_off[tok];
   const float* ml = a.part_ml + (base * kHeads + h) * 4;
@@ -952,10 +952,11 @@ __device__ __forceinline__ void merge_block(const AttnArgs& a, const int tok) {
   for (int p = kMergeAhead; p < np; ++p) big = fmaxf(big, ml[(size_t)p * kHeads * 4]);
   float total = 0.f;
   float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto add = [&](const f32x4& mls, const u32x4& v) {   // mls = (m, l, scale, -)
+  auto add = [&](const f32x4& mls, const u32x4& v) {   // mls = (m, l, exponents of the 64-dim parts, -)
     const float wgt = (mls[0] == ninf) ? 0.f : fast_exp2(mls[0] - big);
     total = __builtin_fmaf(wgt, mls[1], total);
-    const float ws = wgt * mls[2];
+    const int ex = (int32_t)(__float_as_uint(mls[2]) << ex_shift) >> 24;   // signed byte d0 / 64
+    const float ws = __builtin_amdgcn_ldexpf(wgt, ex - 14);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       float lo, hi;

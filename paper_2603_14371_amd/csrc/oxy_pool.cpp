@@ -586,12 +586,11 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     //   prefix phase, shorter prefix -> streaming path: a decode item (<= 2 new tokens) on its
     //                   own, the other queries (an action chunk) two tokens at a time.  With a
     //                   short prefix the launch is bound by latency, CUs are idle, and the
-    //                   re-reads hit L2; four steps in flight per workgroup beat a tile's two;
+    //                   re-reads hit L2;
     //   own phase    -> items with <= 2 new tokens (decode) stream their own pages; larger
     //                   items (action chunks, multi-token decode) use tiles: 8 tokens on a long
-    //                   KV source, 4 (two wavefronts compute, all four move pages) on one of at
-    //                   most 1024 tokens, where few workgroups exist anyway and a step is
-    //                   bound by the tile's own LDS reads and arithmetic.
+    //                   KV source, 4 on one of at most 1024 tokens, where few workgroups exist
+    //                   anyway and a wavefront's time goes with the number of query rows.
     auto tile_tok_for = [](int32_t source_len) { return source_len <= 1024 ? 4 : 8; };
     constexpr int32_t kStreamPrefixMax = 1024;
     struct Group {
@@ -665,8 +664,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         else
           foldable = false;   // old and new keys in one tile: only the separate append covers it
       }
-      // a short chunk on an empty history (see below): single 32-key steps, so all four
-      // wavefronts of a tile get rows (8 tokens) -- half as many workgroups to place
+      // a short chunk on an empty history (see below): single 32-key steps whose wavefronts share
+      // the rows out (8 tokens), half as many workgroups to place
       const bool short_chunk = n_new > 2 && pl.old_len == 0 && pl.new_len <= 64 && !c.split_tokens;
       const int32_t step_tok = n_new <= 2 ? 2 : (short_chunk ? 8 : tile_tok_for(pl.new_len));
       int32_t split = n_new <= 2 ? stream_split_for(c, pl.new_len) : tile_split_for(c, pl.new_len);
@@ -711,7 +710,11 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const bool fresh = (r[oxy::W_PATH] & oxy::kPathFresh) != 0;
         const bool shares = fresh ? false : (tile || !(r[oxy::W_PATH] & oxy::kPathAppends));
         recs[i].idx = i;
-        recs[i].cost = tile ? 2 * steps : steps;
+        // A fresh tile of one step (three barriers, eight tokens' stores) ends about when a 4-step
+        // streaming item does: dealt out behind those and in front of the 2-step ones it does not
+        // become somebody's second workgroup on a CU (8 requests + one chunk: 230 us a step with
+        // cost 2, 216 with 3, 228 with 5, 239 with 8).
+        recs[i].cost = fresh ? 2 * steps + 1 : tile ? 2 * steps : steps;
         recs[i].tile = tile && !fresh;
         recs[i].key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
                              : -(int64_t)i - 1;

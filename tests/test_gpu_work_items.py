@@ -1,0 +1,66 @@
+"""Work items at the sizes where their tiling can go wrong: key ranges around one 32-key step, one
+round of 128 keys and several rounds, one to nine query tokens per item, both append forms; the
+softmax scale's sign and zero; values far from magnitude one."""
+import numpy as np
+import pytest
+
+from paper_2603_14371_amd import synth
+from paper_2603_14371_amd.synth import ACTION, DECODE, _TraceBuilder, _workload
+from parity_util import run_both
+
+pytestmark = pytest.mark.gpu
+
+
+def _step(prefix_len, chunk, hist, n_new, n_layers=1):
+    b = _TraceBuilder()
+    pid = b.prefix(prefix_len)
+    act, dec = b.stream(pid, ACTION), b.stream(pid, DECODE)
+    if hist:
+        b.step([(dec, hist)], attend=False)
+    b.step([(act, chunk), (dec, n_new)])
+    return _workload("work_items", 5150, n_layers, 512, b.trace)
+
+
+# the tolerance is the suite's own (bf16 outputs, see parity_util)
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+@pytest.mark.parametrize("prefix_len,chunk,hist,n_new,split", [
+    (1, 1, 0, 1, 0), (31, 3, 31, 1, 0), (33, 4, 126, 2, 0), (127, 5, 127, 2, 128),
+    (128, 6, 128, 1, 128), (129, 7, 255, 2, 256), (160, 8, 256, 1, 256), (383, 9, 383, 3, 384),
+    (385, 2, 384, 8, 384), (1025, 9, 513, 9, 0), (2048, 65, 1023, 1, 1024), (1040, 130, 40, 5, 512),
+])
+def test_edges_of_steps_rounds_and_tiles(prefix_len, chunk, hist, n_new, split, fold):
+    w = _step(prefix_len, chunk, hist, n_new)
+    gw, _, _, _ = run_both(w, poison=True, split_tokens=split, stream_split_tokens=split,
+                           max_partials=8192, fold_append=fold)
+    gw.close()
+
+
+@pytest.mark.parametrize("scale", [-1.0 / 16, 0.0])
+def test_softmax_scale_may_be_negative_or_zero(scale):
+    w = _step(150, 9, 140, 1)
+    w["scale"] = scale
+    gw, _, _, _ = run_both(w, poison=True, fold_append=True)
+    gw.close()
+
+
+@pytest.mark.parametrize("power", [-60, 60])
+def test_magnitude_of_the_values_does_not_enter_the_rounding(power):
+    """Values times a power of two give exactly the outputs times that power: split results carry
+    their own exponents (all intermediate values stay normal at these powers)."""
+    from paper_2603_14371_amd.harness import GpuWorld
+    w = _step(300, 9, 140, 1)
+    src = synth.DataSource(w["seed"])
+
+    def scaled(recipe, layer, what, n):
+        bits = src(recipe, layer, what, n)
+        if what != "v":
+            return bits
+        return np.where((bits & 0x7F80) != 0, bits + np.int32(power * 128), bits).astype(np.uint16)
+    outs = []
+    for data in (src, scaled):
+        gw = GpuWorld(w, data, poison=True)
+        outs.append(gw.run(w["trace"])[-1]["O"][0].astype(np.int32))
+        gw.close()
+    nonzero = (outs[0] & 0x7F80) != 0
+    assert nonzero.mean() > 0.99
+    assert np.array_equal(outs[0][nonzero] + power * 128, outs[1][nonzero])
