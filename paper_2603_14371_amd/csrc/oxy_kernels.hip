@@ -213,6 +213,26 @@ __global__ __launch_bounds__(256) void gather_inline_kernel(const char* __restri
       *(const uint16_t*)(vp + v_chunk_of_dim(t, (key >> 2) & 1) + v_slot_of_key(key) * 2);
 }
 
+// Descriptor upload: pinned host memory -> device memory, read over the bus by the kernel itself.
+// A copy of this size (8 to 100 KiB) is bound by its hand-over: hipMemcpyAsync gives one of more
+// than 16 KiB to a copy engine, and the two queues then wait for each other's signals (fixed cost of
+// a step with a 33 KiB descriptor 30 us, of one with 8 KiB, which is copied by a kernel, 12 us).
+__global__ __launch_bounds__(256) void upload_kernel(const int32_t* __restrict__ src,
+                                                     int32_t* __restrict__ dst, int32_t n_words) {
+  const int i = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (i + 4 <= n_words) {
+    *(u32x4*)(dst + i) = __builtin_nontemporal_load((const u32x4*)(src + i));
+  } else {
+    for (int k = i; k < n_words; ++k) dst[k] = src[k];
+  }
+}
+
+hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words, hipStream_t s) {
+  if (n_words <= 0) return hipErrorInvalidValue;
+  upload_kernel<<<(n_words + 1023) / 1024, 256, 0, s>>>(pinned, device, n_words);
+  return hipGetLastError();
+}
+
 hipError_t launch_append(const void* k_new, const void* v_new, const int32_t* d_slots,
                          int32_t n_tokens, void* layer_base, hipStream_t s) {
   if (n_tokens <= 0) return hipSuccess;
