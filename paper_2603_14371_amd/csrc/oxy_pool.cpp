@@ -584,9 +584,9 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     //                   share tiles of 8 tokens (64 MFMA rows), which fetch the prefix pages once
     //                   for all of them;
     //   prefix phase, shorter prefix -> streaming path: a decode item (<= 2 new tokens) on its
-    //                   own, the other queries (an action chunk) two tokens at a time.  With a
-    //                   short prefix the launch is bound by latency, CUs are idle, and the
-    //                   re-reads hit L2;
+    //                   own, the other queries (an action chunk) two tokens at a time; in a
+    //                   launch of many items all of a prefix's queries in tiles (see `width`).
+    //                   A query's arithmetic is the same in an item of any width;
     //   own phase    -> items with <= 2 new tokens (decode) stream their own pages; larger
     //                   items (action chunks, multi-token decode) use tiles: 8 tokens on a long
     //                   KV source, 4 on one of at most 1024 tokens, where few workgroups exist
@@ -601,6 +601,26 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     };
     std::vector<Group> groups;   // in order of first appearance; a batch touches few prefixes
     groups.reserve(16);
+    // How an item's own phase is cut, from the item alone.
+    struct OwnCut {
+      bool causal, streams, fresh, short_chunk;
+      int32_t n_new, tile, split;   // new tokens, query tokens per work item, keys per split
+    };
+    auto own_cut = [&](const Plan& pl) {
+      OwnCut o;
+      o.n_new = pl.new_len - pl.old_len;
+      o.causal = pl.s->kind == OXY_KIND_DECODE;
+      o.streams = o.n_new <= 2;
+      o.fresh = !o.streams && pl.old_len == 0;
+      // A short chunk on an empty history (an action chunk, Sec. 3.2) is cut into single 32-key
+      // steps whose wavefronts share the rows out (8 tokens): its tiles start last (their keys are
+      // this step's new rows) and would otherwise be the workgroups the launch ends with.
+      o.short_chunk = o.fresh && pl.new_len <= 64 && !c.split_tokens;
+      o.tile = o.streams ? 2 : o.short_chunk ? 8 : tile_tok_for(pl.new_len);
+      o.split = o.streams ? stream_split_for(c, pl.new_len)
+                          : o.short_chunk ? 32 : tile_split_for(c, pl.new_len);
+      return o;
+    };
     for (const Plan& pl : plan) {
       const int32_t pid = pl.s->prefix_id;
       if (pid == -1) continue;
@@ -622,6 +642,50 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       else
         for (int32_t t = 0; t < n_new; ++t) g->toks.push_back(pl.tok0 + t);
     }
+    // Width of the items on short prefixes: pairs and single decode items (shortest chains, one
+    // workgroup per CU) while the launch has a resident slot for every item (two workgroups on
+    // each of 256 CUs), else tiles of 4, else of 8 tokens with the decode items among them.  Eight
+    // 50-token chunks on 832 tokens, six layers: pairs (1512 items) 145.7 us, 4 tokens 134.6, 8
+    // tokens (504) 135.0; one chunk + one request, 18 layers (202 items of pairs): pairs 189.8 us,
+    // 4 tokens 203.5, 8 tokens 246.3.
+    int32_t width = 2;
+    {
+      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0;
+      for (const Plan& pl : plan) {
+        const OwnCut o = own_cut(pl);
+        for (int32_t t0 = 0; t0 < o.n_new; t0 += o.tile) {
+          const int32_t n = std::min(o.tile, o.n_new - t0);
+          const int32_t hi = o.causal ? pl.old_len + t0 + n : pl.new_len;
+          other += (hi + o.split - 1) / o.split;
+        }
+      }
+      for (const Group& g : groups) {
+        const int32_t split = tile_split_for(c, g.px->len);
+        const int64_t ns = (g.px->len + split - 1) / split;
+        int64_t n_tok = (int64_t)g.toks.size();
+        if (g.px->len > kStreamPrefixMax) {
+          const int32_t tile = tile_tok_for(g.px->len);
+          other += ns * ((n_tok + tile - 1) / tile);
+          continue;
+        }
+        pairs += ns * ((n_tok + 1) / 2 + (int64_t)g.solo.size());
+        for (const auto& so : g.solo) n_tok += so.second;
+        by4 += ns * ((n_tok + 3) / 4);
+        by8 += ns * ((n_tok + 7) / 8);
+      }
+      // the limit holds for the narrowest form, whatever width the launch ends up with
+      if (pairs + other > c.max_work_items)
+        return fail(OXY_ERR_WORKSPACE, "batch_build: %lld work items > max_work_items %d",
+                    (long long)(pairs + other), c.max_work_items);
+      constexpr int64_t kResident = 512;
+      if (pairs + other > kResident) width = by4 + other > kResident && by8 < by4 ? 8 : 4;
+    }
+    if (width > 2)
+      for (Group& g : groups) {
+        for (const auto& so : g.solo)
+          for (int32_t t = 0; t < so.second; ++t) g.toks.push_back(so.first + t);
+        g.solo.clear();
+      }
     for (const Group& g : groups) {
       const Prefix& px = *g.px;
       const int32_t tbl_off = tbl_words;
@@ -629,15 +693,14 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       tbl_words += blocks_for(px.len);
       const int32_t split = tile_split_for(c, px.len);
       const int32_t nsplit = (px.len + split - 1) / split;
-      const bool pairs = px.len <= kStreamPrefixMax;   // short prefix: pairs on the streaming path
-      const int32_t tile_tok = pairs ? 2 : tile_tok_for(px.len);
+      const int32_t tile_tok = px.len <= kStreamPrefixMax ? width : tile_tok_for(px.len);
       for (size_t t0 = 0; t0 < g.toks.size(); t0 += tile_tok) {
         const int32_t n = (int32_t)std::min<size_t>(tile_tok, g.toks.size() - t0);
         const int32_t tok_off = (int32_t)toks.size();
         toks.insert(toks.end(), g.toks.begin() + t0, g.toks.begin() + t0 + n);
         for (int32_t s = 0; s < nsplit; ++s)
           add_work(tok_off, n, tbl_off, s * split, std::min(px.len, (s + 1) * split),
-                   oxy::kNoCausal, s, pairs ? oxy::PATH_STREAM : oxy::PATH_TILE);
+                   oxy::kNoCausal, s, tile_tok == 2 ? oxy::PATH_STREAM : oxy::PATH_TILE);
       }
       for (int32_t t : g.toks) n_parts[t] = nsplit;
       for (const auto& so : g.solo) {
@@ -653,37 +716,26 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       const int32_t tbl_off = tbl_words;
       table_refs.push_back({tbl_off, &pl.s->blocks, blocks_for(pl.new_len)});
       tbl_words += blocks_for(pl.new_len);
-      const int32_t n_new = pl.new_len - pl.old_len;
-      const bool causal = pl.s->kind == OXY_KIND_DECODE;
-      int32_t path = n_new <= 2 ? (oxy::PATH_STREAM | oxy::kPathAppends) : oxy::PATH_TILE;
-      if ((path & oxy::kPathMask) == oxy::PATH_TILE) {
-        if (pl.old_len == 0) {
-          path |= oxy::kPathFresh | (pl.tok0 << oxy::kPathRowShift);
-          for (int32_t t = 0; t < n_new; ++t) fresh_toks.push_back(pl.tok0 + t);
-        }
-        else
-          foldable = false;   // old and new keys in one tile: only the separate append covers it
+      const OwnCut cut = own_cut(pl);
+      const int32_t n_new = cut.n_new, step_tok = cut.tile, split = cut.split;
+      int32_t path = cut.streams ? (oxy::PATH_STREAM | oxy::kPathAppends) : oxy::PATH_TILE;
+      if (cut.fresh) {
+        path |= oxy::kPathFresh | (pl.tok0 << oxy::kPathRowShift);
+        for (int32_t t = 0; t < n_new; ++t) fresh_toks.push_back(pl.tok0 + t);
+      } else if (!cut.streams) {
+        foldable = false;   // old and new keys in one tile: only the separate append covers it
       }
-      // a short chunk on an empty history (see below): single 32-key steps whose wavefronts share
-      // the rows out (8 tokens), half as many workgroups to place
-      const bool short_chunk = n_new > 2 && pl.old_len == 0 && pl.new_len <= 64 && !c.split_tokens;
-      const int32_t step_tok = n_new <= 2 ? 2 : (short_chunk ? 8 : tile_tok_for(pl.new_len));
-      int32_t split = n_new <= 2 ? stream_split_for(c, pl.new_len) : tile_split_for(c, pl.new_len);
-      // A short chunk on an empty history (an action chunk, Sec. 3.2) is cut into single 32-key
-      // steps: its tiles start last (their keys are this step's new rows) and would otherwise
-      // be the workgroups the launch ends with.  Depends on the item alone, like every split.
-      if (short_chunk) split = 32;
       for (int32_t t0 = 0; t0 < n_new; t0 += step_tok) {
         const int32_t n = std::min(step_tok, n_new - t0);
         const int32_t tok_off = (int32_t)toks.size();
         for (int32_t t = 0; t < n; ++t) toks.push_back(pl.tok0 + t0 + t);
         const int32_t q0 = pl.old_len + t0;
-        const int32_t kv_hi = causal ? q0 + n : pl.new_len;
+        const int32_t kv_hi = cut.causal ? q0 + n : pl.new_len;
         const int32_t nsplit = (kv_hi + split - 1) / split;
         const int32_t base = n_parts[pl.tok0 + t0];
         for (int32_t s = 0; s < nsplit; ++s)
           add_work(tok_off, n, tbl_off, s * split, std::min(kv_hi, (s + 1) * split),
-                   causal ? q0 : oxy::kNoCausal, base + s, path);
+                   cut.causal ? q0 : oxy::kNoCausal, base + s, path);
         for (int32_t t = 0; t < n; ++t) n_parts[pl.tok0 + t0 + t] += nsplit;
       }
     }

@@ -64,3 +64,44 @@ def test_magnitude_of_the_values_does_not_enter_the_rounding(power):
     nonzero = (outs[0] & 0x7F80) != 0
     assert nonzero.mean() > 0.99
     assert np.array_equal(outs[0][nonzero] + power * 128, outs[1][nonzero])
+
+
+@pytest.mark.parametrize("n_prefix,prefix_len,width", [(3, 832, 4), (9, 832, 8), (9, 190, 4)])
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+def test_items_in_a_launch_of_many_equal_items_alone(n_prefix, prefix_len, width, fold):
+    """A launch of many work items stacks a short prefix's queries in wider items; every query's
+    bits are those of its item in a batch of its own."""
+    from paper_2603_14371_amd import binding as B
+    from paper_2603_14371_amd.harness import GpuWorld
+    b = _TraceBuilder()
+    pids = [b.prefix(prefix_len) for _ in range(n_prefix)]
+    acts = [b.stream(p, ACTION) for p in pids]
+    decs = [b.stream(pids[i % 2], DECODE) for i in range(5)]
+    b.step([(d, 20 + 31 * i) for i, d in enumerate(decs)], attend=False)
+    items = [(a, 50) for a in acts] + [(d, 1 + i % 2) for i, d in enumerate(decs)]
+    n_tok = sum(n for _, n in items)
+    w = _workload("many_items", 5152, 1, 1024, b.trace)
+    gw = GpuWorld(w, synth.DataSource(w["seed"]), max_q_tokens=512, max_append_tokens=512,
+                  max_partials=16384, fold_append=fold, poison=True)
+    gw.run(w["trace"])
+    data = {"tag": 900, "tok0": 0, "n_total": n_tok}
+    alone, t0 = [], 0
+    for sid, n in items:
+        r = gw.step({"op": "step", "items": [(sid, n)], "data": dict(data, tok0=t0)})
+        alone.append((r["O"][0], r["LSE"][0]))
+        if sid in decs:
+            B.oxy_stream_rewind(gw.pool, sid, B.oxy_stream_info(gw.pool, sid)[2] - n)
+        t0 += n
+    batch = B.oxy_batch_build(gw.pool, items, 0, gw._stream())
+    work = B.oxy_batch_work(batch)
+    B.oxy_batch_destroy(batch)
+    for sid, n in items:
+        if sid in decs:
+            B.oxy_stream_rewind(gw.pool, sid, B.oxy_stream_info(gw.pool, sid)[2] - n)
+    prefix_phase = work[(work[:, 5] == 0x3fffffff) & (work[:, 4] > 50)]
+    assert set(int(x) for x in prefix_phase[:, 1]) >= {width}
+    assert int(prefix_phase[:, 1].max()) == width
+    r = gw.step({"op": "step", "items": items, "data": data})
+    gw.close()
+    assert np.array_equal(np.concatenate([o for o, _ in alone]), r["O"][0])
+    assert np.array_equal(np.concatenate([l for _, l in alone]), r["LSE"][0])
