@@ -48,8 +48,10 @@ hipError_t launch_append(const void* k_new, const void* v_new, const int32_t* d_
 hipError_t launch_append_inline(const void* k_new, const void* v_new, const InlineIds& blocks,
                                 int32_t pos0, int32_t n_tokens, void* layer_base, int32_t n_layers,
                                 size_t src_layer_stride, size_t pool_layer_stride, hipStream_t s);
-// Gather rows back to natural order; slot ids passed by value (<= kMaxInlineBlocks per call).
-hipError_t launch_gather_inline(const void* layer_base, const InlineIds& slots, int32_t n,
+// Gather rows back to natural order.  Run i (< n_runs <= kMaxRuns) is 1..16 consecutive slots of one
+// block: v[i] = its first slot, v[kMaxRuns + i] = (row of k_out / v_out << 4) | (length - 1).
+constexpr int kMaxRuns = kMaxInlineBlocks / 2;
+hipError_t launch_gather_inline(const void* layer_base, const InlineIds& runs, int32_t n_runs,
                                 void* k_out, void* v_out, hipStream_t s);
 
 struct AttnArgs {

@@ -1316,13 +1316,23 @@ int32_t oxy_gather_kv(oxy_pool* p, int32_t layer, const int64_t* slots, int32_t 
   for (int32_t i = 0; i < n; ++i)
     if (slots[i] < 0 || slots[i] >= n_slots)
       return fail(OXY_ERR_INVALID_ARG, "gather_kv: slot %lld out of range", (long long)slots[i]);
-  for (int32_t done = 0; done < n; done += oxy::kMaxInlineBlocks) {
-    int32_t m = std::min(oxy::kMaxInlineBlocks, n - done);
+  // consecutive slots of one block travel as one run (see launch_gather_inline)
+  for (int32_t done = 0; done < n;) {
     oxy::InlineIds ids;
-    for (int32_t i = 0; i < m; ++i) ids.v[i] = (int32_t)slots[done + i];
-    hipError_t e = oxy::launch_gather_inline(layer_base(p, layer), ids, m,
-                                             (char*)k_out + (size_t)done * oxy::kDim * 2,
-                                             (char*)v_out + (size_t)done * oxy::kDim * 2,
+    int32_t n_runs = 0;
+    const int32_t first = done;
+    while (n_runs < oxy::kMaxRuns && done < n) {
+      const int64_t slot = slots[done];
+      int32_t len = 1;
+      while (done + len < n && slot % kPage + len < kPage && slots[done + len] == slot + len) ++len;
+      ids.v[n_runs] = (int32_t)slot;
+      ids.v[oxy::kMaxRuns + n_runs] = (done - first) << 4 | (len - 1);
+      ++n_runs;
+      done += len;
+    }
+    hipError_t e = oxy::launch_gather_inline(layer_base(p, layer), ids, n_runs,
+                                             (char*)k_out + (size_t)first * oxy::kDim * 2,
+                                             (char*)v_out + (size_t)first * oxy::kDim * 2,
                                              (hipStream_t)hip_stream);
     if (e != hipSuccess) return hip_fail(e, "gather_kv: launch");
   }

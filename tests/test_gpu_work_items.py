@@ -105,3 +105,25 @@ def test_items_in_a_launch_of_many_equal_items_alone(n_prefix, prefix_len, width
     gw.close()
     assert np.array_equal(np.concatenate([o for o, _ in alone]), r["O"][0])
     assert np.array_equal(np.concatenate([l for _, l in alone]), r["LSE"][0])
+
+
+@pytest.mark.parametrize("pick", ["in_order", "reversed", "every_third", "repeated", "shuffled"])
+def test_gather_of_any_slot_list(pick):
+    """Read-back accepts slots in any order and any number of times: whole blocks, parts of a block
+    and single tokens, more runs than one launch carries."""
+    from paper_2603_14371_amd.harness import GpuWorld
+    b = _TraceBuilder()
+    dec = b.stream(-1, DECODE)
+    op = b.step([(dec, 611)], attend=False)
+    w = _workload("gather", 5153, 1, 64, b.trace, free_order=np.random.default_rng(3).permutation(64))
+    src = synth.DataSource(w["seed"])
+    gw = GpuWorld(w, src, poison=True)
+    gw.run(w["trace"])
+    k, v = (src(op["data"], 0, what, 611) for what in "kv")
+    n = np.arange(611)
+    order = {"in_order": n, "reversed": n[::-1], "every_third": n[5::3], "repeated": np.repeat(n, 2),
+             "shuffled": np.random.default_rng(4).permutation(611)}[pick]
+    slots = gw.stream_slots(dec)
+    gk, gv = gw.gather(0, [slots[i] for i in order])
+    gw.close()
+    assert np.array_equal(gk, k[order]) and np.array_equal(gv, v[order])
