@@ -931,10 +931,12 @@ __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem&
     attend<4, false>(a, wi, sm);
 }
 
-__global__ __launch_bounds__(256, 2) void attn_kernel(const AttnArgs a) {
+// `work` travels in front of the argument block because the first arguments are preloaded into
+// scalar registers (see build.py): the record's address then waits for no load.
+__global__ __launch_bounds__(256, 2) void attn_kernel(const int32_t* work, const AttnArgs a) {
   __shared__ WorkLds sm;
   WorkItem wi;
-  wi.rec = (DescPtr)a.work + (size_t)blockIdx.x * kWorkWords;
+  wi.rec = (DescPtr)work + (size_t)blockIdx.x * kWorkWords;
   const i32x8 head = ((DescPtr8)wi.rec)[0];
   wi.toks = ((DescPtr8)wi.rec)[1];
   wi.pages = ((DescPtr8)wi.rec)[2];
@@ -972,13 +974,15 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(const AttnArgs a) {
 // ------------------------------------------------------------------------------------------
 constexpr int kMergeAhead = 16;   // partials whose loads are all issued before anything is used
 
-// One workgroup per token; thread t owns head t/32 and eight consecutive output dims.
-__device__ __forceinline__ void merge_block(const AttnArgs& a, const int tok) {
+// One workgroup per token; thread t owns head t/32 and eight consecutive output dims.  n_parts and
+// part_off are preloaded arguments (see attn_kernel).
+__device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_t* part_off,
+                                            const AttnArgs& a, const int tok) {
   const int t = threadIdx.x;
   const int h = t >> 5, d0 = (t & 31) * 8;
   const int ex_shift = 24 - 8 * (d0 >> 6);
-  const int np = a.n_parts[tok];
-  const size_t base = (size_t)a.part_off[tok];
+  const int np = ((DescPtr)n_parts)[tok];
+  const size_t base = (size_t)((DescPtr)part_off)[tok];
   const float* ml = a.part_ml + (base * kHeads + h) * 4;
   const uint16_t* src = a.part_acc + (base * kHeads + h) * kDim + d0;
   const size_t stride = (size_t)kHeads * kDim;
@@ -1024,15 +1028,20 @@ __device__ __forceinline__ void merge_block(const AttnArgs& a, const int tok) {
     a.lse[(size_t)tok * kHeads + h] = (big + __builtin_amdgcn_logf(total)) * 0.6931471805599453f;
 }
 
-__global__ __launch_bounds__(256) void merge_kernel(const AttnArgs a) { merge_block(a, blockIdx.x); }
+__global__ __launch_bounds__(256) void merge_kernel(const int32_t* n_parts, const int32_t* part_off,
+                                                    const AttnArgs a) {
+  merge_block(n_parts, part_off, a, blockIdx.x);
+}
 
 // merge of one layer and, in the same launch, an append that touches other memory than the
 // merge: the next layer's new rows (cross-layer fusion), or this layer's rows of the items whose
 // tiles read their keys from k_new / v_new (nx.tok_list names their tokens)
-__global__ __launch_bounds__(256) void merge_append_kernel(const AttnArgs a, const AppendArgs nx) {
+__global__ __launch_bounds__(256) void merge_append_kernel(const int32_t* n_parts,
+                                                           const int32_t* part_off, const AttnArgs a,
+                                                           const AppendArgs nx) {
   const int n_merge = a.n_q;
   if ((int)blockIdx.x < n_merge) {
-    merge_block(a, blockIdx.x);
+    merge_block(n_parts, part_off, a, blockIdx.x);
   } else {
     const int i = blockIdx.x - n_merge;
     const int tok = nx.tok_list ? nx.tok_list[i] : i;
@@ -1046,9 +1055,9 @@ hipError_t launch_attention_work(const AttnArgs& a, hipStream_t s, hipEvent_t st
                                  hipEvent_t stop) {
   if (a.n_work <= 0 || a.n_q <= 0) return hipErrorInvalidValue;
   if (start || stop)
-    hipExtLaunchKernelGGL(attn_kernel, dim3(a.n_work), dim3(256), 0, s, start, stop, 0, a);
+    hipExtLaunchKernelGGL(attn_kernel, dim3(a.n_work), dim3(256), 0, s, start, stop, 0, a.work, a);
   else
-    attn_kernel<<<a.n_work, 256, 0, s>>>(a);
+    attn_kernel<<<a.n_work, 256, 0, s>>>(a.work, a);
   return hipGetLastError();
 }
 
@@ -1059,14 +1068,16 @@ hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStr
   if (next && next->n_tokens > 0) {
     const dim3 grid(a.n_q + next->n_tokens);
     if (timed)
-      hipExtLaunchKernelGGL(merge_append_kernel, grid, dim3(256), 0, s, start, stop, 0, a, *next);
+      hipExtLaunchKernelGGL(merge_append_kernel, grid, dim3(256), 0, s, start, stop, 0, a.n_parts,
+                            a.part_off, a, *next);
     else
-      merge_append_kernel<<<grid, 256, 0, s>>>(a, *next);
+      merge_append_kernel<<<grid, 256, 0, s>>>(a.n_parts, a.part_off, a, *next);
   } else {
     if (timed)
-      hipExtLaunchKernelGGL(merge_kernel, dim3(a.n_q), dim3(256), 0, s, start, stop, 0, a);
+      hipExtLaunchKernelGGL(merge_kernel, dim3(a.n_q), dim3(256), 0, s, start, stop, 0, a.n_parts,
+                            a.part_off, a);
     else
-      merge_kernel<<<a.n_q, 256, 0, s>>>(a);
+      merge_kernel<<<a.n_q, 256, 0, s>>>(a.n_parts, a.part_off, a);
   }
   return hipGetLastError();
 }
