@@ -991,11 +991,15 @@ __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_
   u32x4 x[kMergeAhead];
   f32x4 w[kMergeAhead];
 #pragma unroll
-  for (int u = 0; u < kMergeAhead; ++u) {
-    const int p = u < np ? u : 0;
-    x[u] = *(const u32x4*)(src + (size_t)p * stride);
-    w[u] = *(const f32x4*)(ml + (size_t)p * kHeads * 4);
-  }
+  for (int u0 = 0; u0 < kMergeAhead; u0 += 4)
+    if (u0 < np) {   // wave-uniform; everything in flight is waited for below in any case
+#pragma unroll
+      for (int u = u0; u < u0 + 4; ++u) {
+        const int p = u < np ? u : 0;
+        x[u] = *(const u32x4*)(src + (size_t)p * stride);
+        w[u] = *(const f32x4*)(ml + (size_t)p * kHeads * 4);
+      }
+    }
   float big = ninf;
 #pragma unroll
   for (int u = 0; u < kMergeAhead; ++u) big = fmaxf(big, u < np ? w[u][0] : ninf);
