@@ -693,52 +693,60 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
         pl[s] = sm.p[s][0][1][lane];
       }
     }
-    auto contract = [&](const int s) {
+    auto contract = [&](const int s, const int r) {
+      const u32x4 hi = G == 1 ? ph[s] : sm.p[s][r][0][lane];
+      const u32x4 lo = G == 1 ? pl[s] : sm.p[s][r][1][lane];
 #pragma unroll
-      for (int r = 0; r < G; ++r) {
-        const u32x4 hi = G == 1 ? ph[s] : sm.p[s][r][0][lane];
-        const u32x4 lo = G == 1 ? pl[s] : sm.p[s][r][1][lane];
+      for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(vr[s][c], hi, acc[r][c]);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(vr[s][c], hi, acc[r][c]);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(vr[s][c], lo, acc[r][c]);
-      }
+      for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(vr[s][c], lo, acc[r][c]);
     };
     if constexpr (!kLast) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) contract(s);
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int r = 0; r < G; ++r) contract(s, r);
       __builtin_amdgcn_sched_barrier(0);   // likewise vr[]
       load_v(round + 1);
       __builtin_amdgcn_sched_barrier(0);
     } else {
       const int nv = nsteps - 4 * round;   // 1..4 steps
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-        if (s < nv) {
-          const int left_s = wi.kv_end - (wi.kv_begin + 32 * (4 * round + s));
-          if (left_s < 32) {
-            const u32x4 mask = value_mask(left_s, g);
+      for (int s = 0; s < 4; ++s) {
+        const int left_s = wi.kv_end - (wi.kv_begin + 32 * (4 * round + s));
+        if (s < nv && left_s < 32) {
+          const u32x4 mask = value_mask(left_s, g);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) vr[s][c] &= mask;
-          }
-          contract(s);
+          for (int c = 0; c < 4; ++c) vr[s][c] &= mask;
         }
+        if (G == 1 && s < nv) contract(s, 0);
+      }
+      // Several groups: group by group, so that a group's scaling and stores fall into the
+      // products of the next (8 chunks on 2048 tokens 164.1 -> 160.2 us for six layers).
+      auto finish = [&](auto full) {
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            if (G > 1 && (decltype(full)::value || s < nv)) contract(s, r);
+          const int slot = sm.slot[2 * r + sub];
+          store_part(a, wi, slot, acc[r], r, wv, lane);
+          if (wv == r) {   // wave-uniform: the sums of the groups are shared out
+            const f32x4 lw = *(const f32x4*)sm.ls[r][lane];
+            const float total = row_sum4((lw[0] + lw[1]) + (lw[2] + lw[3]));
+            if (g == 0 && 2 * r + sub < wi.n_tok)
+              *(f32x2*)(a.part_ml + ((size_t)slot * kHeads + (n & 7)) * 4) = (f32x2){m[r], total};
+          }
+        }
+      };
+      if (G > 1 && nv == 4)
+        finish(std::true_type());
+      else
+        finish(std::false_type());
     }
   };
   for (int round = 0; round + 1 < rounds; ++round) round_body(round, std::false_type());
   round_body(rounds - 1, std::true_type());
-
-#pragma unroll
-  for (int r = 0; r < G; ++r) {
-    const int slot = sm.slot[2 * r + sub];
-    store_part(a, wi, slot, acc[r], r, wv, lane);
-    if (wv == r) {   // wave-uniform: the sums of the groups are shared out
-      const f32x4 lw = *(const f32x4*)sm.ls[r][lane];
-      const float total = row_sum4((lw[0] + lw[1]) + (lw[2] + lw[3]));
-      if (g == 0 && 2 * r + sub < wi.n_tok)
-        *(f32x2*)(a.part_ml + ((size_t)slot * kHeads + h) * 4) = (f32x2){m[r], total};
-    }
-  }
 }
 
 // Own phase of an item whose history was empty before the step (an action chunk): up to eight
