@@ -20,8 +20,8 @@ constexpr int kMaxInlineBlocks = 512;             // block ids passed by value t
 // work record fields (words 0..7)
 enum { W_TOK_OFF = 0, W_N_TOK, W_TBL_OFF, W_KV_BEGIN, W_KV_END, W_CAUSAL_Q0, W_PART_IDX, W_PATH };
 // paths
-enum { PATH_STREAM = 0,  // <=2 query tokens (16 rows): 4 wavefronts split the keys, KV to registers
-       PATH_TILE = 1,    // <=8 query tokens (64 rows): 4 wavefronts share the keys through LDS
+enum { PATH_STREAM = 0,  // <=2 query tokens (16 rows)
+       PATH_TILE = 1,    // up to 8 query tokens (64 rows)
        PATH_NOOP = 2 };  // padding that keeps the index -> XCD pattern of the work list intact
 // The path sits in the low four bits of word W_PATH.  kPathFresh marks an own-phase tile of an
 // item whose own history was empty before this step: all of its keys are rows of this step's
@@ -63,8 +63,9 @@ struct AttnArgs {
   const int32_t* tables;
   const int32_t* part_off;  // [n_q]
   const int32_t* n_parts;   // [n_q]
-  uint16_t* part_acc;       // [n_partials][8][256] fp16: accumulator / row scale
-  float* part_ml;           // [n_partials][8][4]: reference max (log2 domain), sum, row scale, -
+  uint16_t* part_acc;       // [n_partials][8][256] fp16: accumulator * 2^(14 - exponent)
+  float* part_ml;           // [n_partials][8][4]: reference max (log2 domain), sum, the exponents of
+                            // the row's four 64-dim parts (int8 each), -
   int32_t n_work;
   int32_t n_q;
   float scale;
