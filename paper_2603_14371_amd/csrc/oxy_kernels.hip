@@ -440,8 +440,9 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
 // the registers of two workgroups per CU.  (Before: work items of up to two tokens kept a
 // 64-register accumulator per wavefront and combined the four through 66 KiB of LDS, 1.1 us of a
 // 4 us work item, now 0.4; larger ones staged K and V in LDS, where each of the four wavefronts
-// read all of both.  Work-item launch of 64 requests on 2048-token prefixes 20.7 -> 19.4 us, of
-// one request on 832 tokens 5.5 -> 5.0 us.)
+// read all of both.  Work-item launch of one request on 832 tokens 5.44 -> 4.79 us, of eight requests
+// and a chunk 7.8 -> 7.05, of eight chunks on 2048 tokens 23.3 -> 20.6, of 64 requests and two
+// chunks on 2048-token prefixes 20.55 -> 20.27, kernel trace.)
 //
 // A row's arithmetic does not depend on G or on the other rows: a query may be evaluated alone or
 // beside any others and gives the same bits.
