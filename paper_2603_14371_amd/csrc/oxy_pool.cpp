@@ -960,12 +960,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       ds.event_pending = false;
     }
     memcpy(ds.staging, h.data(), h.size() * 4);
-    hipError_t e =
-        oxy::launch_upload
-            ? oxy::launch_upload(ds.staging, (int32_t*)ds.d_base, (int32_t)h.size(),
-                                 (hipStream_t)hip_stream)
-            : hipMemcpyAsync(ds.d_base, ds.staging, h.size() * 4, hipMemcpyHostToDevice,
-                             (hipStream_t)hip_stream);
+    hipError_t e = oxy::launch_upload(ds.staging, (int32_t*)ds.d_base, (int32_t)h.size(),
+                                      (hipStream_t)hip_stream);
     if (e == hipSuccess) e = hipEventRecord(ds.uploaded, (hipStream_t)hip_stream);
     if (e != hipSuccess) {
       // a failing call changes no pool state: lengths back, blocks back in reverse order of

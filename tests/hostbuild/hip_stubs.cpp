@@ -1,8 +1,9 @@
 // CPU stand-ins for the HIP runtime calls and kernel launchers the host library uses, so that
 // oxy_pool.cpp and oxy_sched.cpp can be compiled with gcc under AddressSanitizer /
 // UndefinedBehaviorSanitizer and run on a machine without a GPU.  "Device" memory is host
-// memory here; launches do nothing.  oxy_stub_fail_next(skip, k) makes k device-facing calls fail
-// after `skip` more successful ones, which is how the tests force the error paths from the host.
+// memory here; the descriptor upload copies, the other launches do nothing.
+// oxy_stub_fail_next(skip, k) makes k device-facing calls fail after `skip` more successful ones,
+// which is how the tests force the error paths from the host.
 #include "../../paper_2603_14371_amd/csrc/oxy_internal.h"
 
 #include <cstdlib>
@@ -47,11 +48,6 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return outcome(); }
-hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind, hipStream_t) {
-  hipError_t e = outcome();
-  if (e == hipSuccess) memcpy(dst, src, n);   // the sanitizer checks both ranges
-  return e;
-}
 // recorded launch sequences: a stream, a graph and an instantiated graph are small heap objects,
 // so that the sanitizer sees every leak, double free and use after free of the host logic
 hipError_t hipGetLastError(void) { return hipSuccess; }
@@ -100,6 +96,12 @@ hipError_t hipMemsetAsync(void* dst, int v, size_t n, hipStream_t) {
 }
 
 namespace oxy {
+hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words, hipStream_t) {
+  if (n_words <= 0 || ((uintptr_t)pinned | (uintptr_t)device) % 16) return hipErrorInvalidValue;
+  hipError_t e = outcome();
+  if (e == hipSuccess) memcpy(device, pinned, (size_t)n_words * 4);   // the sanitizer checks both ranges
+  return e;
+}
 hipError_t launch_append(const void*, const void*, const int32_t*, int32_t, void*, hipStream_t) {
   return outcome();
 }
