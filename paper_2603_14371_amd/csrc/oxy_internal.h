@@ -35,8 +35,9 @@ struct InlineIds {
 };
 
 // Copies a batch descriptor from pinned host memory (16-byte aligned, as the device address is) on
-// stream s.
-hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words, hipStream_t s);
+// stream s; `done` is complete when the staging buffer has been read.
+hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words, hipStream_t s,
+                         hipEvent_t done);
 // Scatter n_tokens rows of K and V (natural [token][256] bf16) into the slots of one layer.
 hipError_t launch_append(const void* k_new, const void* v_new, const int32_t* d_slots,
                          int32_t n_tokens, void* layer_base, hipStream_t s);

@@ -961,8 +961,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     }
     memcpy(ds.staging, h.data(), h.size() * 4);
     hipError_t e = oxy::launch_upload(ds.staging, (int32_t*)ds.d_base, (int32_t)h.size(),
-                                      (hipStream_t)hip_stream);
-    if (e == hipSuccess) e = hipEventRecord(ds.uploaded, (hipStream_t)hip_stream);
+                                      (hipStream_t)hip_stream, ds.uploaded);
     if (e != hipSuccess) {
       // a failing call changes no pool state: lengths back, blocks back in reverse order of
       // their pops (which restores the free stack exactly)

@@ -47,7 +47,6 @@ hipError_t hipEventDestroy(hipEvent_t e) {
   return hipSuccess;
 }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return outcome(); }
 // recorded launch sequences: a stream, a graph and an instantiated graph are small heap objects,
 // so that the sanitizer sees every leak, double free and use after free of the host logic
 hipError_t hipGetLastError(void) { return hipSuccess; }
@@ -96,8 +95,9 @@ hipError_t hipMemsetAsync(void* dst, int v, size_t n, hipStream_t) {
 }
 
 namespace oxy {
-hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words, hipStream_t) {
-  if (n_words <= 0 || ((uintptr_t)pinned | (uintptr_t)device) % 16) return hipErrorInvalidValue;
+hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words, hipStream_t,
+                         hipEvent_t done) {
+  if (!done || n_words <= 0 || ((uintptr_t)pinned | (uintptr_t)device) % 16) return hipErrorInvalidValue;
   hipError_t e = outcome();
   if (e == hipSuccess) memcpy(device, pinned, (size_t)n_words * 4);   // the sanitizer checks both ranges
   return e;

@@ -123,7 +123,7 @@ def _fuzz_script(seed, n_ops, nb=200, inject=False):
                 probe.__dict__ = _clone(model)
                 st, _ = _try(lambda: probe.batch_build(items))
                 if st == 0:
-                    script.append([9, int(rng.integers(0, 2)), 1])   # the upload, or its event
+                    script.append([9, 0, 1])                      # the upload
                     script.append([8, flags, len(items)] + flat + [ERR_DEVICE, 0])
                     script.append([9, 0, 0])
                     n_injected += 1
@@ -163,7 +163,7 @@ def test_random_sequences_under_asan_ubsan(replay_exe, tmp_path, seed):
 
 def test_device_failures_leave_the_pool_unchanged(replay_exe, tmp_path):
     """A HIP call that fails inside oxy_prefix_append (the launch) or oxy_batch_build (the
-    descriptor upload or its event) gives OXY_ERR_DEVICE and changes no block, refcount, length or
+    descriptor upload) gives OXY_ERR_DEVICE and changes no block, refcount, length or
     free-stack position."""
     script, n = _fuzz_script(3001, 900, inject=True)
     assert n > 25
