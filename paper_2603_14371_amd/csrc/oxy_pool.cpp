@@ -292,7 +292,8 @@ int32_t oxy_pool_create(const oxy_pool_config* cfg, oxy_pool** out) {
         return fail(OXY_ERR_INVALID_ARG, "pool_create: out of host memory");
       }
     } else {
-      hipError_t e = hipHostMalloc((void**)&s.staging, p->desc_words * 4, hipHostMallocDefault);
+      // coherent by request: a kernel reads the buffer, and the default follows HIP_HOST_COHERENT
+      hipError_t e = hipHostMalloc((void**)&s.staging, p->desc_words * 4, hipHostMallocCoherent);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&s.uploaded, hipEventDisableTiming);
       if (e != hipSuccess) {
         oxy_pool_destroy(p);

@@ -30,7 +30,10 @@ static hipError_t outcome() {
 
 extern "C" {
 const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "no error" : "stubbed failure"; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned int) {
+// Staging memory is written by the host and read by kernels, launch after launch: it has to be
+// allocated as coherent, whatever the environment says about allocations that leave it open.
+hipError_t hipHostMalloc(void** p, size_t n, unsigned int flags) {
+  if (!(flags & hipHostMallocCoherent)) return hipErrorInvalidValue;
   *p = malloc(n ? n : 1);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }
