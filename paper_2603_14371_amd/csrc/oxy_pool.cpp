@@ -849,6 +849,9 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
           }
         }
       order.resize(last_real);
+      // The limit counts work items: where the padding does not fit, it is left out.
+      if (order.size() > (size_t)c.max_work_items)
+        order.erase(std::remove(order.begin(), order.end(), -1), order.end());
     }
   }
   const int32_t n_work = (int32_t)order.size();

@@ -259,6 +259,54 @@ def test_workspace_limits_are_reported_not_overrun():
     B.oxy_pool_destroy(pool)
 
 
+def _random_batch(rng, max_work_items):
+    """A pool with random prefixes and histories, and a batch over them (None if it is refused)."""
+    pool = _host_pool(4096, n_layers=1, max_work_items=max_work_items)
+    pids = []
+    for _ in range(int(rng.integers(1, 5))):
+        pids.append(B.oxy_prefix_create(pool))
+        B.oxy_prefix_append(pool, pids[-1], 0, 0, 0, int(rng.choice([64, 190, 832, 1024])), 0, 0)
+    items, hist = [], []
+    for _ in range(int(rng.integers(1, 13))):
+        sid = B.oxy_stream_create(pool, int(rng.choice(pids)), B.KIND_DECODE)
+        hist.append((sid, int(rng.integers(1, 900))))
+        items.append((sid, int(rng.choice([1, 1, 1, 2, 5]))))
+    for pid in pids[:int(rng.integers(0, 3))]:
+        items.append((B.oxy_stream_create(pool, pid, B.KIND_ACTION), int(rng.integers(3, 24))))
+    B.oxy_batch_destroy(B.oxy_batch_build(pool, hist, B.BATCH_APPEND_ONLY, 0))
+    try:
+        return pool, B.oxy_batch_build(pool, items, 0, 0)
+    except B.OxyError as e:
+        assert e.code == B.ERR_WORKSPACE and "work items" in str(e)
+        return pool, None
+
+
+def _close(pool, batch):
+    if batch is not None:
+        B.oxy_batch_destroy(batch)
+    B.oxy_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_the_work_item_limit_counts_work_items_and_not_padding(seed):
+    """Padding records keep the work list's order on the XCDs; a pool whose limit is exactly the
+    batch's work items takes it without them, and one less refuses it."""
+    def records(batch):
+        work = B.oxy_batch_work(batch)
+        return sorted(tuple(int(x) for x in r) for r in work[work[:, 7] != 2])
+
+    pool, batch = _random_batch(np.random.default_rng(7000 + seed), 0)
+    want = records(batch)
+    _close(pool, batch)
+    pool, batch = _random_batch(np.random.default_rng(7000 + seed), len(want))
+    assert batch is not None, "refused with max_work_items %d" % len(want)
+    assert records(batch) == want and len(B.oxy_batch_work(batch)) == len(want)
+    _close(pool, batch)
+    pool, batch = _random_batch(np.random.default_rng(7000 + seed), len(want) - 1)
+    assert batch is None
+    _close(pool, batch)
+
+
 def test_prefix_append_layers_indexes_like_per_layer_appends():
     pool = _host_pool(64, n_layers=3)
     model = PoolModel(64, 16, 3)
