@@ -892,9 +892,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   b->n_tokens = (int32_t)n_tokens;
   b->n_work = n_work;
   b->n_partials = (int32_t)n_partials;
-  b->off_slots = 0;
   b->append_foldable = foldable;
-  // Sections in the order slots | work | part_off | n_parts | fresh tokens | token lists | tables: the block
+  // Sections in the order work | slots | part_off | n_parts | fresh tokens | token lists | tables: the block
   // tables, whose size changes whenever a stream takes a new block, come last, so that the
   // device addresses of all sections stay the same from step to step while the shape of the
   // batch (tokens, work items, tile token lists) does -- a recorded launch sequence
@@ -903,8 +902,9 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   // once): the launch shape then changes only every 64 work items, not whenever a history
   // crosses a split boundary.
   b->n_launch = std::max(n_work, std::min((n_work + 63) / 64 * 64, c.max_work_items));
-  b->off_work = b->off_slots + (int32_t)n_tokens;
-  b->off_part_off = b->off_work + b->n_launch * oxy::kWorkWords;
+  b->off_work = 0;   // first: every record is one whole 128-byte line
+  b->off_slots = b->off_work + b->n_launch * oxy::kWorkWords;
+  b->off_part_off = b->off_slots + (int32_t)n_tokens;
   b->off_n_parts = b->off_part_off + (int32_t)part_off.size();
   b->n_fresh = (int32_t)fresh_toks.size();
   b->off_fresh = b->off_n_parts + (int32_t)n_parts.size();

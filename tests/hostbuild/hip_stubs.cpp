@@ -115,15 +115,19 @@ hipError_t launch_append_inline(const void*, const void*, const InlineIds&, int3
 hipError_t launch_gather_inline(const void*, const InlineIds&, int32_t, void*, void*, hipStream_t) {
   return outcome();
 }
-hipError_t launch_attention(const AttnArgs&, hipStream_t) { return outcome(); }
+// the work items load whole eight-word parts of their records
+static hipError_t attention_outcome(const AttnArgs& a) {
+  return (uintptr_t)a.work % (4 * kWorkWords) ? hipErrorInvalidValue : outcome();
+}
+hipError_t launch_attention(const AttnArgs& a, hipStream_t) { return attention_outcome(a); }
 hipError_t static_scratch(uint16_t** part_acc, float** part_ml) {
   static char buf[64];
   *part_acc = (uint16_t*)buf;
   *part_ml = (float*)buf;
   return hipSuccess;
 }
-hipError_t launch_attention_work(const AttnArgs&, hipStream_t, hipEvent_t, hipEvent_t) {
-  return outcome();
+hipError_t launch_attention_work(const AttnArgs& a, hipStream_t, hipEvent_t, hipEvent_t) {
+  return attention_outcome(a);
 }
 hipError_t launch_merge_append(const AttnArgs&, const AppendArgs*, hipStream_t, hipEvent_t,
                                hipEvent_t) {
