@@ -15,7 +15,7 @@ constexpr int kNoCausal = 0x3fffffff;
 constexpr int kWorkWords = 32;             // one 128-byte line per work record
 constexpr int kWorkInlineToks = 8;         // words 8..15: query token ids of the tile
 constexpr int kWorkInlinePages = 16;       // words 16..31: block ids of the first 16 pages
-constexpr int kMaxInlineBlocks = 512;             // block ids passed by value to append/gather
+constexpr int kMaxInlineBlocks = 512;             // block ids passed by value to an append
 
 // work record fields (words 0..7)
 enum { W_TOK_OFF = 0, W_N_TOK, W_TBL_OFF, W_KV_BEGIN, W_KV_END, W_CAUSAL_Q0, W_PART_IDX, W_PATH };
@@ -47,10 +47,16 @@ hipError_t launch_append(const void* k_new, const void* v_new, const int32_t* d_
 hipError_t launch_append_inline(const void* k_new, const void* v_new, const InlineIds& blocks,
                                 int32_t pos0, int32_t n_tokens, void* layer_base, int32_t n_layers,
                                 size_t src_layer_stride, size_t pool_layer_stride, hipStream_t s);
-// Gather rows back to natural order.  Run i (< n_runs <= kMaxRuns) is 1..16 consecutive slots of one
-// block: v[i] = its first slot, v[kMaxRuns + i] = (row of k_out / v_out << 4) | (length - 1).
-constexpr int kMaxRuns = kMaxInlineBlocks / 2;
-hipError_t launch_gather_inline(const void* layer_base, const InlineIds& runs, int32_t n_runs,
+// Gather rows back to natural order, at most kMaxRuns runs and kMaxGatherRows rows a launch.  Run i is
+// 1..16 consecutive slots of one block: slot[i] = its first slot, where[i] = (row of k_out / v_out
+// << 4) | (length - 1).  16 bits for `where` leave room for 512 runs in the 4 KiB of arguments that a
+// launch takes: a list of single slots then needs no more launches than one with a slot each would.
+constexpr int kMaxRuns = 512, kMaxGatherRows = 4096;
+struct GatherRuns {
+  int32_t slot[kMaxRuns];
+  uint16_t where[kMaxRuns];
+};
+hipError_t launch_gather_inline(const void* layer_base, const GatherRuns& runs, int32_t n_runs,
                                 void* k_out, void* v_out, hipStream_t s);
 
 struct AttnArgs {

@@ -200,22 +200,28 @@ __global__ __launch_bounds__(256) void append_blocks_kernel(const uint16_t* __re
 // Reads runs of tokens back in natural order, one workgroup per run (at most the 16 tokens of a
 // block; see oxy_internal.h for the encoding).  Every V chunk holds one dim of eight keys, so a
 // token alone touches all of its V page: the page is read once as whole chunks, turned through
-// LDS, and only the run's rows are written.  (One workgroup per token read 256 two-byte pieces
-// per row: the 1337 tokens of four histories took three launches of 2.8 us, now one of 3.4 us.)
+// LDS, and only the run's rows are written; of a page the chunks with a key of the run are read (a
+// single token's are half of them).  (One workgroup per token read 256 two-byte pieces per row: the
+// 1337 tokens of four histories took three launches of 2.8 us, now one of 3.4 us.  A list of as many
+// scattered single slots takes three launches as before; the C call waited for is 23.5 us against 21.7.)
 __global__ __launch_bounds__(256) void gather_inline_kernel(const char* __restrict__ layer_base,
-                                                            const InlineIds runs,
+                                                            const GatherRuns runs,
                                                             uint16_t* __restrict__ k_out,
                                                             uint16_t* __restrict__ v_out) {
   __shared__ __align__(16) uint16_t v_s[kPage][kDim + 8];   // +8: rows start in different banks
   const int t = threadIdx.x;
-  const int slot = runs.v[blockIdx.x], where = runs.v[kMaxRuns + blockIdx.x];
+  const int slot = runs.slot[blockIdx.x], where = runs.where[blockIdx.x];
   const int key0 = slot & 15, len = (where & 15) + 1;
   const size_t out0 = (size_t)(where >> 4);
   const char* kp = layer_base + (size_t)(slot >> 4) * kBlockBytes;
   const char* vp = kp + kPageBytes;
+  // chunks with a key of the run: keys 4gp..4gp+3 and 8+4gp..8+4gp+3 (gp = (t >> 4) & 1 for both)
+  const int lo = 4 * ((t >> 4) & 1), hi = lo + 8, end = key0 + len;
+  const bool wanted = (key0 < lo + 4 && end > lo) || (key0 < hi + 4 && end > hi);
   u32x4 v[2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) v[i] = *(const u32x4*)(vp + (t + 256 * i) * 16);
+  for (int i = 0; i < 2; ++i)
+    if (wanted) v[i] = *(const u32x4*)(vp + (t + 256 * i) * 16);
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int idx = t + 256 * i, key = idx >> 5, cd = idx & 31;
@@ -228,7 +234,7 @@ __global__ __launch_bounds__(256) void gather_inline_kernel(const char* __restri
     const int ci = t + 256 * i, gp = (ci >> 4) & 1, d = 64 * (ci >> 7) + 4 * (ci & 15) + ((ci >> 5) & 3);
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-      v_s[(e < 4 ? 4 * gp : 4 + 4 * gp) + e][d] = (uint16_t)(v[i][e >> 1] >> (16 * (e & 1)));
+      if (wanted) v_s[(e < 4 ? 4 * gp : 4 + 4 * gp) + e][d] = (uint16_t)(v[i][e >> 1] >> (16 * (e & 1)));
   }
   __syncthreads();
 #pragma unroll
@@ -285,7 +291,7 @@ hipError_t launch_append_inline(const void* k_new, const void* v_new, const Inli
   return hipGetLastError();
 }
 
-hipError_t launch_gather_inline(const void* layer_base, const InlineIds& runs, int32_t n_runs,
+hipError_t launch_gather_inline(const void* layer_base, const GatherRuns& runs, int32_t n_runs,
                                 void* k_out, void* v_out, hipStream_t s) {
   if (n_runs <= 0) return hipSuccess;
   gather_inline_kernel<<<n_runs, 256, 0, s>>>((const char*)layer_base, runs, (uint16_t*)k_out,

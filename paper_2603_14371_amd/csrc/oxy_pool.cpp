@@ -1317,19 +1317,20 @@ int32_t oxy_gather_kv(oxy_pool* p, int32_t layer, const int64_t* slots, int32_t 
       return fail(OXY_ERR_INVALID_ARG, "gather_kv: slot %lld out of range", (long long)slots[i]);
   // consecutive slots of one block travel as one run (see launch_gather_inline)
   for (int32_t done = 0; done < n;) {
-    oxy::InlineIds ids;
+    oxy::GatherRuns runs;
     int32_t n_runs = 0;
-    const int32_t first = done;
-    while (n_runs < oxy::kMaxRuns && done < n) {
+    const int32_t first = done, end = std::min(n, done + oxy::kMaxGatherRows);
+    while (n_runs < oxy::kMaxRuns && done < end) {
       const int64_t slot = slots[done];
+      const int32_t most = std::min(end - done, kPage - (int32_t)(slot & (kPage - 1)));
       int32_t len = 1;
-      while (done + len < n && slot % kPage + len < kPage && slots[done + len] == slot + len) ++len;
-      ids.v[n_runs] = (int32_t)slot;
-      ids.v[oxy::kMaxRuns + n_runs] = (done - first) << 4 | (len - 1);
+      while (len < most && slots[done + len] == slot + len) ++len;
+      runs.slot[n_runs] = (int32_t)slot;
+      runs.where[n_runs] = (uint16_t)((done - first) << 4 | (len - 1));
       ++n_runs;
       done += len;
     }
-    hipError_t e = oxy::launch_gather_inline(layer_base(p, layer), ids, n_runs,
+    hipError_t e = oxy::launch_gather_inline(layer_base(p, layer), runs, n_runs,
                                              (char*)k_out + (size_t)first * oxy::kDim * 2,
                                              (char*)v_out + (size_t)first * oxy::kDim * 2,
                                              (hipStream_t)hip_stream);

@@ -14,6 +14,8 @@ static long g_calls = 0;
 // after `skip` further successful calls, the next k device-facing calls fail
 extern "C" void oxy_stub_fail_next(int skip, int k) { g_fail_skip = skip, g_fail_next = k; }
 extern "C" long oxy_stub_calls() { return g_calls; }
+static long g_gathers = 0;
+extern "C" long oxy_stub_gathers() { return g_gathers; }
 
 static hipError_t outcome() {
   ++g_calls;
@@ -112,7 +114,21 @@ hipError_t launch_append_inline(const void*, const void*, const InlineIds&, int3
                                 int32_t, size_t, size_t, hipStream_t) {
   return outcome();
 }
-hipError_t launch_gather_inline(const void*, const InlineIds&, int32_t, void*, void*, hipStream_t) {
+// decodes the runs: row i of the outputs gets the number of the slot that would be copied there
+hipError_t launch_gather_inline(const void*, const GatherRuns& runs, int32_t n_runs, void* k_out,
+                                void* v_out, hipStream_t) {
+  if (n_runs < 1 || n_runs > kMaxRuns) return hipErrorInvalidValue;
+  ++g_gathers;
+  for (int32_t i = 0; i < n_runs; ++i) {
+    const int32_t slot = runs.slot[i], row = runs.where[i] >> 4, len = (runs.where[i] & 15) + 1;
+    if (slot % kPage + len > kPage || row + len > kMaxGatherRows) return hipErrorInvalidValue;   // a run stays in its block
+    for (int32_t j = 0; j < len; ++j) {
+      int32_t* k = (int32_t*)((char*)k_out + (size_t)(row + j) * kDim * 2);
+      int32_t* v = (int32_t*)((char*)v_out + (size_t)(row + j) * kDim * 2);
+      if (*k != -1 || *v != -1) return hipErrorInvalidValue;       // each row once
+      *k = *v = slot + j;
+    }
+  }
   return outcome();
 }
 // the work items load whole eight-word parts of their records

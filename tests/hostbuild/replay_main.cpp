@@ -13,6 +13,7 @@
 //   7 sid new_len expect_status                                    stream_rewind
 //   8 flags n_items (sid n_new)* expect_status n_slots slot*       batch_build (+ one step, destroy)
 //   9 skip k                                                       after `skip` device calls, k fail
+//  11 n slot* max_launches                                        gather_kv
 //  10 nb ref* nfree free* ns (sid pid kind len nblk blk*)* np (pid len nblk sealed nstreams blk*)*
 #include "../../include/oxy.h"
 
@@ -21,6 +22,7 @@
 #include <vector>
 
 extern "C" void oxy_stub_fail_next(int skip, int k);
+extern "C" long oxy_stub_gathers();
 
 static FILE* g_in;
 static long g_line = 0;
@@ -201,6 +203,21 @@ int main(int argc, char** argv) {
           CHECK(oxy_prefix_blocks(pool, (int32_t)pid, buf.data(), (int32_t)nb) == OXY_OK, "prefix_blocks");
           for (long i = 0; i < nblk; ++i) CHECK(buf[i] == need(), "prefix %ld block %ld", pid, i);
         }
+        break;
+      }
+      case 11: {
+        const long n = need();
+        std::vector<int64_t> slots((size_t)n);
+        for (auto& s : slots) s = need();
+        std::vector<char> k((size_t)n * 512, (char)-1), v((size_t)n * 512, (char)-1);
+        const long before = oxy_stub_gathers();
+        CHECK(oxy_gather_kv(pool, 0, slots.data(), (int32_t)n, k.data(), v.data(), nullptr) == OXY_OK,
+              "gather_kv of %ld slots", n);
+        for (long i = 0; i < n; ++i)
+          CHECK(*(int32_t*)&k[(size_t)i * 512] == slots[i] && *(int32_t*)&v[(size_t)i * 512] == slots[i],
+                "gathered row %ld", i);
+        const long most = need(), launches = oxy_stub_gathers() - before;
+        CHECK(launches <= most, "gather_kv of %ld slots: %ld launches > %ld", n, launches, most);
         break;
       }
       default:

@@ -168,3 +168,23 @@ def test_device_failures_leave_the_pool_unchanged(replay_exe, tmp_path):
     script, n = _fuzz_script(3001, 900, inject=True)
     assert n > 25
     _run(replay_exe, tmp_path, script)
+
+
+def _slot_lists(rng, n_slots):
+    for n in (1, 15, 16, 17, 511, 512, 513, 1300, 3000):
+        yield list(range(3, 3 + n))                                        # one long run
+        yield rng.integers(0, n_slots, n).tolist()                          # single slots
+        yield [s for s in range(n_slots) if s % 3 != 1][:n]                 # runs of one and two
+        yield (list(range(n_slots - 1, -1, -1)) * 2)[:n]                    # backwards
+        yield np.repeat(rng.integers(0, n_slots, n), 2)[:n].tolist()        # repeated
+    yield list(range(n_slots)) * 3                                          # more rows than a launch takes
+
+
+def test_read_back_covers_every_row_once_in_few_launches(replay_exe, tmp_path):
+    """A slot list travels as runs inside blocks; no list of n slots takes more launches than one
+    for every 512 slots."""
+    nb = 300
+    script = [[0, nb, 2, 1, 256, 0]]
+    for slots in _slot_lists(np.random.default_rng(11), nb * 16):
+        script.append([11, len(slots)] + slots + [-(-len(slots) // 512)])
+    _run(replay_exe, tmp_path, script)
