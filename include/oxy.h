@@ -117,9 +117,8 @@ typedef struct {
   int32_t max_work_items;   /* attention work items per batch (0 -> 16384)                   */
   int32_t max_partials;     /* per-token split results per batch (0 -> 32*max_q_tokens)      */
   int32_t split_tokens;     /* KV tokens per work item wherever query tokens share KV pages: the
-                               prefix phase (tiles of 8 tokens on a prefix longer than 1024
-                               tokens; single decode items and token pairs, in large launches
-                               tiles, on a shorter one) and the own phase of
+                               prefix phase (single decode items and token pairs, in large
+                               launches tiles of 4 or 8 tokens) and the own phase of
                                action chunks and multi-token decode.  Multiple of 32, <= 1024.
                                0 -> chosen from the length of the KV source alone: about an
                                eighth of it, within [64, 256]; 32 for a chunk of at most 64

@@ -10,8 +10,9 @@
 // into fixed-size splits.  A work item is (query rows that share one KV source, one split of
 // that source); it yields an un-normalised partial (reference max m in the log2 domain, sum
 // l, accumulator acc[256]).  A second kernel merges a query's partials by the log-sum-exp
-// rule.  The split size is fixed per pool and the path that evaluates a query depends on
-// its item only, so the arithmetic of a query never depends on what else is in the batch.
+// rule.  How many queries share a work item depends on the whole batch; the splits depend on the
+// pool and the item only, and a query's arithmetic is the same in a work item of any width, so its
+// bits never depend on what else is in the batch.
 //
 // MFMA mapping (v_mfma_f32_16x16x32_bf16, lane = 16*g + n, keys taken 32 at a time = page A
 // and page B of the block table):

@@ -578,27 +578,22 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       const int32_t w[kHdr] = {tok_off, n_tok, tbl_off, b, e, q0, part, path};
       hdr.insert(hdr.end(), w, w + kHdr);
     };
-    // Which path evaluates a query depends on its item and its prefix only (kind, n_new, phase,
-    // prefix length), never on its batch mates, so an item's arithmetic is the same in every
-    // batch it can appear in:
-    //   prefix phase, prefix longer than kStreamPrefixMax -> all queries attached to the prefix
-    //                   share tiles of 8 tokens (64 MFMA rows), which fetch the prefix pages once
-    //                   for all of them;
-    //   prefix phase, shorter prefix -> streaming path: a decode item (<= 2 new tokens) on its
-    //                   own, the other queries (an action chunk) two tokens at a time; in a
-    //                   launch of many items all of a prefix's queries in tiles (see `width`).
-    //                   A query's arithmetic is the same in an item of any width;
+    // Where a query's keys are split depends on its item and its prefix only (kind, n_new, phase,
+    // lengths), and its arithmetic is the same in a work item of any width, so an item's bits are
+    // the same in every batch it can appear in.  How many queries share a work item:
+    //   prefix phase -> a decode item (<= 2 new tokens) on its own, the other queries (an action
+    //                   chunk) two tokens at a time; in a launch of many items all of a prefix's
+    //                   queries in tiles (see `width`);
     //   own phase    -> items with <= 2 new tokens (decode) stream their own pages; larger
     //                   items (action chunks, multi-token decode) use tiles: 8 tokens on a long
     //                   KV source, 4 on one of at most 1024 tokens, where few workgroups exist
     //                   anyway and a wavefront's time goes with the number of query rows.
     auto tile_tok_for = [](int32_t source_len) { return source_len <= 1024 ? 4 : 8; };
-    constexpr int32_t kStreamPrefixMax = 1024;
     struct Group {
       int32_t pid;
       const Prefix* px;
-      std::vector<int32_t> toks;
-      std::vector<std::pair<int32_t, int32_t>> solo;   // (first token, count) of streaming items
+      std::vector<std::pair<int32_t, int32_t>> items;  // (first token, count), in batch order
+      int32_t n_tok = 0, n_small = 0, small_tok = 0;   // tokens; items of <= 2 tokens and theirs
     };
     std::vector<Group> groups;   // in order of first appearance; a batch touches few prefixes
     groups.reserve(16);
@@ -634,24 +629,29 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       if (!g) {
         const Prefix& px = p->prefixes.at(pid);
         if (px.len == 0) continue;
-        groups.push_back({pid, &px, {}, {}});
+        groups.push_back({pid, &px, {}});
         g = &groups.back();
       }
       const int32_t n_new = pl.new_len - pl.old_len;
-      if (n_new <= 2 && g->px->len <= kStreamPrefixMax)
-        g->solo.push_back({pl.tok0, n_new});
-      else
-        for (int32_t t = 0; t < n_new; ++t) g->toks.push_back(pl.tok0 + t);
+      g->items.push_back({pl.tok0, n_new});
+      g->n_tok += n_new;
+      if (n_new <= 2) {
+        g->n_small++;
+        g->small_tok += n_new;
+      }
     }
-    // Width of the items on short prefixes: pairs and single decode items (shortest chains, one
-    // workgroup per CU) while the launch has a resident slot for every item (two workgroups on
-    // each of 256 CUs), else tiles of 4, else of 8 tokens with the decode items among them.  Eight
-    // 50-token chunks on 832 tokens, six layers: pairs (1512 items) 145.7 us, 4 tokens 134.6, 8
-    // tokens (504) 135.0; one chunk + one request, 18 layers (202 items of pairs): pairs 189.8 us,
-    // 4 tokens 203.5, 8 tokens 246.3.
-    int32_t width = 2;
+    // Width of the prefix items: pairs and single decode items (shortest chains, one workgroup per
+    // CU) while the launch has a resident slot for every item (two workgroups on each of 256 CUs),
+    // else tiles of 4, else of 8 tokens with the decode items among them.  us per layer (pairs / 4 /
+    // 8 tokens): 832-token prefixes, one chunk + one request 10.5 / 11.3 / 13.7, two chunks + eight
+    // requests 13.6 / 12.5 / 14.2, eight chunks 24.7 / 23.1 / 22.5, sixteen 42.9 / 37.4 / 32.9;
+    // 2048-token prefixes, 14 requests on one 10.9 / 12.5 / 15.6, 64 requests on eight 22.9 / 17.1 /
+    // 20.1, eight chunks 37.0 / 30.9 / 26.8.  (On a prefix longer than 1024 tokens the width was
+    // always 8: with splits of 160 or 192 tokens, five or six steps in two rounds, small launches
+    // took 15.2 us a layer where pairs take 10.9.)
+    int32_t width = 8;
     {
-      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0;
+      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0;
       for (const Plan& pl : plan) {
         const OwnCut o = own_cut(pl);
         for (int32_t t0 = 0; t0 < o.n_new; t0 += o.tile) {
@@ -663,30 +663,23 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       for (const Group& g : groups) {
         const int32_t split = tile_split_for(c, g.px->len);
         const int64_t ns = (g.px->len + split - 1) / split;
-        int64_t n_tok = (int64_t)g.toks.size();
-        if (g.px->len > kStreamPrefixMax) {
-          const int32_t tile = tile_tok_for(g.px->len);
-          other += ns * ((n_tok + tile - 1) / tile);
-          continue;
-        }
-        pairs += ns * ((n_tok + 1) / 2 + (int64_t)g.solo.size());
-        for (const auto& so : g.solo) n_tok += so.second;
-        by4 += ns * ((n_tok + 3) / 4);
-        by8 += ns * ((n_tok + 7) / 8);
+        const int64_t in_pairs = ns * ((g.n_tok - g.small_tok + 1) / 2 + g.n_small);
+        pairs += in_pairs;
+        by4 += ns * ((g.n_tok + 3) / 4);
+        by8 += ns * ((g.n_tok + 7) / 8);
+        limited += g.px->len <= 1024 ? in_pairs : ns * ((g.n_tok + 7) / 8);
       }
-      // the limit holds for the narrowest form, whatever width the launch ends up with
-      if (pairs + other > c.max_work_items)
+      // The limit holds for pairs on a prefix of at most 1024 tokens and for tiles of 8 on a longer
+      // one, whatever width the launch ends up with; a narrower form is taken only if it fits too.
+      if (limited + other > c.max_work_items)
         return fail(OXY_ERR_WORKSPACE, "batch_build: %lld work items > max_work_items %d",
-                    (long long)(pairs + other), c.max_work_items);
-      constexpr int64_t kResident = 512;
-      if (pairs + other > kResident) width = by4 + other > kResident && by8 < by4 ? 8 : 4;
+                    (long long)(limited + other), c.max_work_items);
+      const int64_t resident = std::min(512, c.max_work_items);
+      if (pairs + other <= resident)
+        width = 2;
+      else if (by4 + other <= resident || (by8 == by4 && by4 + other <= c.max_work_items))
+        width = 4;
     }
-    if (width > 2)
-      for (Group& g : groups) {
-        for (const auto& so : g.solo)
-          for (int32_t t = 0; t < so.second; ++t) g.toks.push_back(so.first + t);
-        g.solo.clear();
-      }
     for (const Group& g : groups) {
       const Prefix& px = *g.px;
       const int32_t tbl_off = tbl_words;
@@ -694,23 +687,25 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       tbl_words += blocks_for(px.len);
       const int32_t split = tile_split_for(c, px.len);
       const int32_t nsplit = (px.len + split - 1) / split;
-      const int32_t tile_tok = px.len <= kStreamPrefixMax ? width : tile_tok_for(px.len);
-      for (size_t t0 = 0; t0 < g.toks.size(); t0 += tile_tok) {
-        const int32_t n = (int32_t)std::min<size_t>(tile_tok, g.toks.size() - t0);
-        const int32_t tok_off = (int32_t)toks.size();
-        toks.insert(toks.end(), g.toks.begin() + t0, g.toks.begin() + t0 + n);
+      auto add_prefix_items = [&](int32_t tok_off, int32_t n) {
         for (int32_t s = 0; s < nsplit; ++s)
           add_work(tok_off, n, tbl_off, s * split, std::min(px.len, (s + 1) * split),
-                   oxy::kNoCausal, s, tile_tok == 2 ? oxy::PATH_STREAM : oxy::PATH_TILE);
-      }
-      for (int32_t t : g.toks) n_parts[t] = nsplit;
-      for (const auto& so : g.solo) {
-        const int32_t tok_off = (int32_t)toks.size();
-        for (int32_t t = 0; t < so.second; ++t) toks.push_back(so.first + t);
-        for (int32_t s = 0; s < nsplit; ++s)
-          add_work(tok_off, so.second, tbl_off, s * split, std::min(px.len, (s + 1) * split),
-                   oxy::kNoCausal, s, oxy::PATH_STREAM);
-        for (int32_t t = 0; t < so.second; ++t) n_parts[so.first + t] = nsplit;
+                   oxy::kNoCausal, s, width == 2 ? oxy::PATH_STREAM : oxy::PATH_TILE);
+      };
+      // the queries that share work items, then the decode items on their own
+      const int32_t tok0 = (int32_t)toks.size();
+      for (const auto& it : g.items)
+        if (width > 2 || it.second > 2)
+          for (int32_t t = 0; t < it.second; ++t) toks.push_back(it.first + t);
+      const int32_t tok1 = (int32_t)toks.size();
+      for (int32_t t = tok0; t < tok1; t += width) add_prefix_items(t, std::min(width, tok1 - t));
+      for (const auto& it : g.items) {
+        if (width == 2 && it.second <= 2) {
+          const int32_t tok_off = (int32_t)toks.size();
+          for (int32_t t = 0; t < it.second; ++t) toks.push_back(it.first + t);
+          add_prefix_items(tok_off, it.second);
+        }
+        for (int32_t t = 0; t < it.second; ++t) n_parts[it.first + t] = nsplit;
       }
     }
     for (const Plan& pl : plan) {

@@ -307,6 +307,37 @@ def test_the_work_item_limit_counts_work_items_and_not_padding(seed):
     _close(pool, batch)
 
 
+@pytest.mark.parametrize("prefix_len,split", [(832, 128), (1025, 160), (1100, 160), (2048, 256)])
+def test_width_of_prefix_items_follows_the_load(prefix_len, split):
+    """Requests on one prefix, long or short: an item each while the launch has room for that, tiles
+    of 4 and of 8 queries in larger launches, and on a long prefix also where the limit on work items
+    leaves no room for more."""
+    def widths(n_req, max_work_items=0):
+        pool = _host_pool(4096, n_layers=1, max_work_items=max_work_items, max_partials=1 << 16)
+        pid = B.oxy_prefix_create(pool)
+        B.oxy_prefix_append(pool, pid, 0, 0, 0, prefix_len, 0, 0)
+        batch = B.oxy_batch_build(
+            pool, [(B.oxy_stream_create(pool, pid, B.KIND_DECODE), 1) for _ in range(n_req)], 0, 0)
+        work = B.oxy_batch_work(batch)
+        prefix = work[(work[:, 7] != 2) & (work[:, 5] == 0x3fffffff)]
+        _close(pool, batch)
+        n_split = -(-prefix_len // split)
+        assert int((work[:, 7] != 2).sum()) == len(prefix) + n_req   # and one own item each
+        assert sorted(set(int(x) for x in prefix[:, 3])) == [split * i for i in range(n_split)]
+        return set(int(x) for x in prefix[:, 1]), len(prefix) // n_split
+
+    assert widths(14) == ({1}, 14)
+    assert widths(100) == ({4}, 25)
+    assert widths(304) == ({8}, 38)
+    if prefix_len > 1024:
+        n_split = -(-prefix_len // split)
+        assert widths(14, 2 * n_split + 14) == ({6, 8}, 2)
+        assert widths(16, 4 * n_split + 16) == ({4}, 4)
+        with pytest.raises(B.OxyError) as e:
+            widths(14, 2 * n_split + 13)
+        assert e.value.code == B.ERR_WORKSPACE
+
+
 def test_prefix_append_layers_indexes_like_per_layer_appends():
     pool = _host_pool(64, n_layers=3)
     model = PoolModel(64, 16, 3)
