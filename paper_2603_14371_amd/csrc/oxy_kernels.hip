@@ -395,6 +395,13 @@ __device__ __forceinline__ float softmax_weights(const f32x4 s0, const f32x4 s1,
   }
   return sum;
 }
+// A row's sum times the factor of a moved reference.  Rounded here, never contracted with the addition
+// that follows: otherwise `attend`, where the two lie in different branches, and `attend_fresh`, where
+// they do not, give different bits.
+__device__ __forceinline__ float rescaled(const float l, const float alpha) {
+#pragma clang fp contract(off)
+  return l * alpha;
+}
 // One wavefront's 64 dims of a group's split result.  A split result leaves as (m, l, four
 // exponents) and acc * 2^(14 - exponent) in fp16: half the bytes of fp32, with the exponent of the
 // largest value per row and 64 dims, so that the rounding does not depend on the magnitude of the
@@ -677,7 +684,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
       for (int r = 0; r < G; ++r) {
         const bool up = mx[r] > m[r] + kGrow;
         const float alpha = up ? fast_exp2(m[r] - mx[r]) : 1.f;   // m = -inf gives 0
-        l[r] *= alpha;
+        l[r] = rescaled(l[r], alpha);
         if (round > 0) {   // acc holds zeros before
 #pragma unroll
           for (int c = 0; c < 4; ++c) acc[r][c] *= alpha;
@@ -879,7 +886,7 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
     m_own = up ? mx : m_own;
     if constexpr (!kOneStep) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) l[s] *= alpha;
+      for (int s = 0; s < 4; ++s) l[s] = rescaled(l[s], alpha);
       if (g == 0) sm.mx[wv][n][0] = alpha;
     }
 #pragma unroll
