@@ -418,7 +418,9 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
   amax = row_max4(amax);
   // biased exponent of amax, kept where 2^(14 - exponent) is a normal number
   const int eb = max(24, min(253, (int)(__float_as_uint(amax) >> 23)));
-  const float up = __uint_as_float((uint32_t)(127 + 14 + 126 - eb) << 23);
+  // an infinite value leaves no exponent for the others: all 64 are NaN then, instead of zeros (looking
+  // for the largest finite one in a branch of its own cost 0.5 % of a launch of chunks)
+  const float up = __uint_as_float((uint32_t)(127 + 14 + 126 - eb) << 23) + (amax - amax);
   const int ex = eb - 126;
   u32x4 o[2];
 #pragma unroll
