@@ -405,7 +405,8 @@ __device__ __forceinline__ float rescaled(const float l, const float alpha) {
 // One wavefront's 64 dims of a group's split result.  A split result leaves as (m, l, four
 // exponents) and acc * 2^(14 - exponent) in fp16: half the bytes of fp32, with the exponent of the
 // largest value per row and 64 dims, so that the rounding does not depend on the magnitude of the
-// values.  acc[c][e] = dim 16g + 4e + c of the 64: a lane's sixteen values are consecutive.  slot: split result of this lane's token.
+// values.  acc[c][e] = dim 16g + 4e + c of the 64: a lane's sixteen values are consecutive.  slot:
+// split result of this lane's token.
 __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi, const int slot,
                                            const f32x4 (&acc)[4], const int group, const int wv,
                                            const int lane) {

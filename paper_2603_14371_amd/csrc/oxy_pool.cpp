@@ -758,10 +758,13 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const bool fresh = (r[oxy::W_PATH] & oxy::kPathFresh) != 0;
         const bool shares = fresh ? false : (tile || !(r[oxy::W_PATH] & oxy::kPathAppends));
         recs[i].idx = i;
-        // A fresh tile of one step (three barriers, eight tokens' stores) ends about when a 4-step
-        // streaming item does: dealt out behind those and in front of the 2-step ones it does not
-        // become somebody's second workgroup on a CU (8 requests + one chunk: 230 us a step with
-        // cost 2, 216 with 3, 228 with 5, 239 with 8).
+        // A fresh tile has three barriers and eight tokens' stores beside its steps.  One of a single
+        // step ends about when a 4-step streaming item does: dealt out behind those and in front of
+        // the 2-step ones it does not become somebody's second workgroup on a CU.  us per layer with
+        // cost s / 2s / 2s + 1 / 3s for s steps: 8 requests + one chunk of 50 11.1 / 11.3 / 10.9 /
+        // 11.3 (runs of one side 10.9 to 11.6), two chunks of 100 16.7 / 15.5 / 15.3 / 16.6, of 200
+        // 28.2 / 26.25 / 25.95 / 26.0, one of 600 56.5 / 47.3 / 48.1 / 48.9 (these within 0.2), two of
+        // 300 appended separately no difference.
         recs[i].cost = fresh ? 2 * steps + 1 : tile ? 2 * steps : steps;
         recs[i].tile = tile && !fresh;
         recs[i].key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
