@@ -147,7 +147,7 @@ bool resolve_config(const oxy_pool_config* in, oxy_pool_config* c) {
   if (c->max_append_tokens == 0) c->max_append_tokens = kPage * c->num_blocks;
   if (c->max_work_items == 0) c->max_work_items = 16384;
   if (c->max_partials == 0) c->max_partials = 32 * c->max_q_tokens;
-  // split_tokens == 0 stays 0: the tile path then sizes its splits from the length of the KV
+  // split_tokens == 0 stays 0: splits of shared sources are then sized from the length of the KV
   // source alone (see tile_split_for), which keeps an item's arithmetic independent of its batch
   // stream_split_tokens == 0 becomes split_tokens; both 0: by the item's length (stream_split_for)
   if (c->stream_split_tokens == 0) c->stream_split_tokens = c->split_tokens;
@@ -196,7 +196,7 @@ void maybe_drop_prefix(oxy_pool* p, int32_t pid) {
     p->prefixes.erase(it);
 }
 
-// Split size of the shared-tile path for a KV source of `len` tokens.  With a configured
+// Split size of a KV source of `len` tokens whose pages several queries read.  With a configured
 // split_tokens it is that; otherwise about an eighth of the source, between 64 and 256 tokens:
 // short sources (an 832-token prefix, a 50-token chunk) get short dependent chains per
 // workgroup, long ones (2048 tokens) keep the number of partials per query down.
