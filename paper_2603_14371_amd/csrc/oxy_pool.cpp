@@ -640,18 +640,19 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         g->small_tok += n_new;
       }
     }
-    // Width of the prefix items: pairs and single decode items (shortest chains, one workgroup per
-    // CU) while the launch has a resident slot for every item (two workgroups on each of 256 CUs),
-    // else tiles of 4, else of 8 tokens with the decode items among them.  us per layer (pairs / 4 /
-    // 8 tokens): 832-token prefixes, one chunk + one request 10.5 / 11.3 / 13.7, two chunks + eight
-    // requests 13.6 / 12.5 / 14.2, eight chunks 24.7 / 23.1 / 22.5, sixteen 42.9 / 37.4 / 32.9;
-    // 2048-token prefixes, 14 requests on one 10.9 / 12.5 / 15.6, 64 requests on eight 22.9 / 17.1 /
-    // 20.1, eight chunks 37.0 / 30.9 / 26.8.  (On a prefix longer than 1024 tokens the width was
-    // always 8: with splits of 160 or 192 tokens, five or six steps in two rounds, small launches
-    // took 15.2 us a layer where pairs take 10.9.)
+    // Width of the prefix items: pairs and single decode items (the shortest chains) while the launch
+    // has a resident slot for every item (two workgroups on each of 256 CUs), or a CU where a
+    // prefix is longer than 1024 tokens and its items take two rounds; else tiles of 4, else of 8
+    // tokens with the decode items among them.  us per layer (pairs / 4 / 8 tokens): 832-token
+    // prefixes, one chunk + one request 10.5 / 11.3 / 13.7, two chunks + eight requests 13.6 / 12.5 /
+    // 14.2, eight chunks 24.7 / 23.1 / 22.5, sixteen 42.9 / 37.4 / 32.9; 2048-token prefixes, 14
+    // requests on one 10.9 / 12.5 / 15.6, 32 requests on two (336 items of pairs) 16.4 / 12.6 / 16.8,
+    // 64 requests on eight 22.9 / 17.1 / 20.1, eight chunks 37.0 / 30.9 / 26.8.  (On a prefix longer
+    // than 1024 tokens the width was always 8: with splits of 160 or 192 tokens, five or six steps
+    // in two rounds, small launches took 15.2 us a layer where pairs take 10.9.)
     int32_t width = 8;
     {
-      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0;
+      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0, for_pairs = 512;
       for (const Plan& pl : plan) {
         const OwnCut o = own_cut(pl);
         for (int32_t t0 = 0; t0 < o.n_new; t0 += o.tile) {
@@ -668,14 +669,15 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         by4 += ns * ((g.n_tok + 3) / 4);
         by8 += ns * ((g.n_tok + 7) / 8);
         limited += g.px->len <= 1024 ? in_pairs : ns * ((g.n_tok + 7) / 8);
+        if (g.px->len > 1024) for_pairs = 256;
       }
       // The limit holds for pairs on a prefix of at most 1024 tokens and for tiles of 8 on a longer
       // one, whatever width the launch ends up with; a narrower form is taken only if it fits too.
       if (limited + other > c.max_work_items)
         return fail(OXY_ERR_WORKSPACE, "batch_build: %lld work items > max_work_items %d",
                     (long long)(limited + other), c.max_work_items);
-      const int64_t resident = std::min(512, c.max_work_items);
-      if (pairs + other <= resident)
+      const int64_t resident = std::min<int64_t>(512, c.max_work_items);
+      if (pairs + other <= std::min(for_pairs, resident))
         width = 2;
       else if (by4 + other <= resident || (by8 == by4 && by4 + other <= c.max_work_items))
         width = 4;

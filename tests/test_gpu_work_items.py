@@ -107,7 +107,7 @@ def test_items_in_a_launch_of_many_equal_items_alone(n_prefix, prefix_len, width
     assert np.array_equal(np.concatenate([l for _, l in alone]), r["LSE"][0])
 
 
-@pytest.mark.parametrize("n_prefix,prefix_len,width", [(2, 1100, 2), (3, 1100, 4), (9, 1300, 8)])
+@pytest.mark.parametrize("n_prefix,prefix_len,width", [(2, 1100, 4), (3, 2048, 4), (9, 1300, 8)])
 @pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
 def test_the_same_on_long_prefixes(n_prefix, prefix_len, width, fold):
     """The same rule on prefixes whose splits take two rounds of 128 keys, the second one partly."""

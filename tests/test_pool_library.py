@@ -327,6 +327,7 @@ def test_width_of_prefix_items_follows_the_load(prefix_len, split):
         return set(int(x) for x in prefix[:, 1]), len(prefix) // n_split
 
     assert widths(14) == ({1}, 14)
+    assert widths(35) == (({1}, 35) if prefix_len <= 1024 else ({3, 4}, 9))   # a slot each, not a CU
     assert widths(100) == ({4}, 25)
     assert widths(304) == ({8}, 38)
     if prefix_len > 1024:
