@@ -28,7 +28,8 @@ enum { PATH_STREAM = 0,  // <=2 query tokens (16 rows)
 // k_new / v_new, row = (word >> kPathRowShift) + own position.
 // kPathAppends marks a streaming work item on an item's own pages: its query tokens are the new
 // rows that a folded append has to write (a streaming item on prefix pages appends nothing).
-constexpr int kPathMask = 15, kPathFresh = 16, kPathAppends = 32, kPathRowShift = 8;
+// kPathOnce (with kPathAppends) asks for non-temporal page loads.
+constexpr int kPathMask = 15, kPathFresh = 16, kPathAppends = 32, kPathOnce = 64, kPathRowShift = 8;
 
 struct InlineIds {
   int32_t v[kMaxInlineBlocks];

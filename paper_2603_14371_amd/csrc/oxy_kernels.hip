@@ -470,11 +470,11 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
 // A row's arithmetic does not depend on G or on the other rows: a query may be evaluated alone or
 // beside any others and gives the same bits.
 //
-// kOwnPages: a decode item's own pages, read by this work item alone (non-temporal loads, so that
-// they do not push shared pages out of the L2), which also writes the item's new rows when the
-// append is folded in.  Otherwise the pages are a prefix's or a multi-token item's, and other work
-// items read them too.
-template <int G, bool kOwnPages>
+// kOwnPages: a decode item's own pages, read by this work item alone, which also writes the item's
+// new rows when the append is folded in.  Otherwise the pages are a prefix's or a multi-token item's,
+// and other work items read them too.  kOnce: non-temporal page loads, for own pages that will have
+// left the L2 by the next step and are not to push shared pages out.
+template <int G, bool kOwnPages, bool kOnce>
 __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
   int tid = threadIdx.x;
   // keeps what is computed from the thread id inside this instance: shared with the other
@@ -495,7 +495,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
   u32x4 kr[16];      // kr[2j+hf]: K operand (j, hf) of this wavefront's 32 keys
   u32x4 vr[4][4];    // vr[s][c]: V operand c of this wavefront's 64 dims, step s of the round
   auto page_load = [](const char* p) {
-    if constexpr (kOwnPages) return __builtin_nontemporal_load((const u32x4*)p);
+    if constexpr (kOnce) return __builtin_nontemporal_load((const u32x4*)p);
     return *(const u32x4*)p;
   };
   // A step past the split's end re-reads a page of the split; its logits are masked and its V
@@ -956,11 +956,11 @@ __device__ __forceinline__ void attend_fresh_any(const AttnArgs& a, const WorkIt
 
 __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
   if (wi.n_tok <= 2)
-    attend<1, false>(a, wi, sm);
+    attend<1, false, false>(a, wi, sm);
   else if (wi.n_tok <= 4)
-    attend<2, false>(a, wi, sm);
+    attend<2, false, false>(a, wi, sm);
   else
-    attend<4, false>(a, wi, sm);
+    attend<4, false, false>(a, wi, sm);
 }
 
 // `work` travels in front of the argument block because the first arguments are preloaded into
@@ -985,7 +985,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(const int32_t* work, const
   const int path_word = head[W_PATH];
   if ((path_word & kPathMask) == PATH_NOOP) return;   // padding record
   if (path_word & kPathAppends)                       // one or two tokens on their own pages
-    attend<1, true>(a, wi, sm);
+    path_word & kPathOnce ? attend<1, true, true>(a, wi, sm) : attend<1, true, false>(a, wi, sm);
   else if (a.k_new && (path_word & kPathFresh))
     attend_fresh_any(a, wi, sm, path_word >> kPathRowShift);
   else if ((path_word & kPathFresh) && wi.kv_end - wi.kv_begin <= 32)

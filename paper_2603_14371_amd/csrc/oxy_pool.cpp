@@ -206,6 +206,8 @@ int32_t tile_split_for(const oxy_pool_config& c, int32_t len) {
   return std::max(64, std::min(256, s));
 }
 
+constexpr int64_t kOnceBytes = 128 << 20;   // see kPathOnce in oxy_batch_build
+
 // Streaming path on an item's own history.  A history of at most 512 tokens is cut into
 // 128-token work items (one step per wavefront: steps that wait for memory one after the other
 // are what such a launch is made of), a longer one into 256-token work items (two steps per
@@ -710,6 +712,17 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         for (int32_t t = 0; t < it.second; ++t) n_parts[it.first + t] = nsplit;
       }
     }
+    // A decode loop reads the same pages in every step, so own pages are loaded past the caches
+    // (non-temporal, see kOnce in the kernels) only where the step's pages in all layers are more than
+    // half of the 256 MB that the Infinity Cache holds, the rest left to whatever else a program runs
+    // between two steps.  us a step of 18 layers, non-temporal / plain: 3 requests on one observation
+    // (26 MB) 161.5 / 148.6, 8 on four (116 MB) 170.4 / 158.4, 16 on one (155 MB) 207.3 / 185.3 and with
+    // a chunk 259.1 / 217.7; beyond the cache 16 on four (340 MB) 218.4 / 223.5, 32 on one (601 MB) 245.1
+    // / 271.9; two pools of 158 MB used in turn 189.3 / 197.1.
+    int64_t live_tok = 0;
+    for (const Group& g : groups) live_tok += g.px->len;
+    for (const Plan& pl : plan) live_tok += pl.new_len;
+    const bool once = live_tok * c.n_layers * (oxy::kBlockBytes / kPage) > kOnceBytes;
     for (const Plan& pl : plan) {
       const int32_t tbl_off = tbl_words;
       table_refs.push_back({tbl_off, &pl.s->blocks, blocks_for(pl.new_len)});
@@ -717,6 +730,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       const OwnCut cut = own_cut(pl);
       const int32_t n_new = cut.n_new, step_tok = cut.tile, split = cut.split;
       int32_t path = cut.streams ? (oxy::PATH_STREAM | oxy::kPathAppends) : oxy::PATH_TILE;
+      if (cut.streams && once) path |= oxy::kPathOnce;
       if (cut.fresh) {
         path |= oxy::kPathFresh | (pl.tok0 << oxy::kPathRowShift);
         for (int32_t t = 0; t < n_new; ++t) fresh_toks.push_back(pl.tok0 + t);

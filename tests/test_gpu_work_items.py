@@ -134,3 +134,18 @@ def test_gather_of_any_slot_list(pick):
     gk, gv = gw.gather(0, [slots[i] for i in order])
     gw.close()
     assert np.array_equal(gk, k[order]) and np.array_equal(gv, v[order])
+
+
+@pytest.mark.parametrize("hist,n_new", [(40, 1), (127, 2), (300, 1), (520, 2)])
+def test_own_pages_read_past_the_caches_give_the_same_bits(hist, n_new):
+    """The non-temporal loads are taken where the pages of all layers are more than 128 MB: the same
+    layer in a pool of one layer and in one of enough layers, written and read by the work items."""
+    outs = []
+    for n_layers in (1, 1 + (128 << 20) // ((300 + hist) << 10)):
+        w = _step(300, 9, hist, n_new, n_layers)
+        w["num_blocks"] = 64
+        gw, g, _, _ = run_both(w, layers=[0], poison=True, fold_append=True)
+        outs.append(g[-1])
+        gw.close()
+    assert np.array_equal(outs[0]["O"][0], outs[1]["O"][0])
+    assert np.array_equal(outs[0]["LSE"][0], outs[1]["LSE"][0])
