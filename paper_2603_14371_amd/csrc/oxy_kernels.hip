@@ -785,8 +785,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
 // append and a separate one give the same bits.  kOneStep: the split is one step, and everything
 // it needs is requested at once; otherwise a step's operands are requested when it is their turn.
 // kRows: the keys are rows of k_new / v_new (row0 + own position); otherwise (the append went
-// before, one step only) they are read from the pages.
-template <bool kOneStep, bool kRows>
+// before, one step only) they are read from the pages.  kG: groups of two tokens; every wavefront
+// scales and stores its 64 dims of all of them, one after the other, which is what a tile ends with.
+template <bool kOneStep, bool kRows, int kG>
 __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& wi, WorkLds& sm,
                                              const int row0) {
   static_assert(kOneStep || kRows, "several steps from pages go through attend");
@@ -797,7 +798,6 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
   const float ninf = -__builtin_inff();
   const float sl2 = log2_scale(a);
   const int nsteps = (wi.kv_end - wi.kv_begin + 31) >> 5, last = wi.kv_end - 1;
-  const int n_groups = (wi.n_tok + 1) >> 1;
   const uint16_t* kn = (const uint16_t*)a.k_new + (size_t)row0 * kDim + 64 * wv + 8 * g;
   const uint16_t* vn = (const uint16_t*)a.v_new + (size_t)row0 * kDim + 64 * wv + 4 * n;
   const int blk_a = wi.pages[0], blk_b = wi.pages[1];
@@ -849,9 +849,9 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
 #pragma unroll
   for (int j = 0; j < 8; ++j) qf[j] = query_sign(a, qf[j]);
   float m_own = ninf, l[4] = {0.f, 0.f, 0.f, 0.f};   // of this wavefront's row n
-  f32x4 acc[kMaxGroups][4];
+  f32x4 acc[kG][4];
 #pragma unroll
-  for (int r = 0; r < kMaxGroups; ++r)
+  for (int r = 0; r < kG; ++r)
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[r][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
   for (int first = 0; first < (kOneStep ? 1 : nsteps); first += 4) {
@@ -903,7 +903,7 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
     __syncthreads();
     if constexpr (!kOneStep) {
 #pragma unroll
-      for (int r = 0; r < kMaxGroups; ++r)
+      for (int r = 0; r < kG; ++r)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[r][c] *= sm.mx[r][n][0];
     }
@@ -927,14 +927,13 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
           v[c] &= mask;
         }
 #pragma unroll
-        for (int r = 0; r < kMaxGroups; ++r)
-          if (r < n_groups) {
-            const u32x4 hi = sm.p[s][r][0][lane], lo = sm.p[s][r][1][lane];
+        for (int r = 0; r < kG; ++r) {
+          const u32x4 hi = sm.p[s][r][0][lane], lo = sm.p[s][r][1][lane];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(v[c], hi, acc[r][c]);
+          for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(v[c], hi, acc[r][c]);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(v[c], lo, acc[r][c]);
-          }
+          for (int c = 0; c < 4; ++c) acc[r][c] = mfma16(v[c], lo, acc[r][c]);
+        }
       }
   }
   const float total = row_sum4((l[0] + l[1]) + (l[2] + l[3]));
@@ -943,15 +942,28 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
     *(f32x2*)(a.part_ml + ((size_t)own_slot * kHeads + h) * 4) = (f32x2){m_own, total};
   }
 #pragma unroll
-  for (int r = 0; r < kMaxGroups; ++r) store_part(a, wi, sm.slot[2 * r + sub], acc[r], r, wv, lane);
+  for (int r = 0; r < kG; ++r) store_part(a, wi, sm.slot[2 * r + sub], acc[r], r, wv, lane);
+}
+
+template <bool kRows>
+__device__ __forceinline__ void attend_fresh_width(const AttnArgs& a, const WorkItem& wi, WorkLds& sm,
+                                                   const int row0) {
+  if (wi.n_tok <= 2)
+    attend_fresh<true, kRows, 1>(a, wi, sm, row0);
+  else if (wi.n_tok <= 4)
+    attend_fresh<true, kRows, 2>(a, wi, sm, row0);
+  else
+    attend_fresh<true, kRows, 4>(a, wi, sm, row0);
 }
 
 __device__ __forceinline__ void attend_fresh_any(const AttnArgs& a, const WorkItem& wi, WorkLds& sm,
                                                  const int row0) {
   if (wi.kv_end - wi.kv_begin <= 32)
-    attend_fresh<true, true>(a, wi, sm, row0);
+    attend_fresh_width<true>(a, wi, sm, row0);
+  else if (wi.n_tok <= 4)
+    attend_fresh<false, true, 2>(a, wi, sm, row0);
   else
-    attend_fresh<false, true>(a, wi, sm, row0);
+    attend_fresh<false, true, 4>(a, wi, sm, row0);
 }
 
 __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
@@ -989,7 +1001,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(const int32_t* work, const
   else if (a.k_new && (path_word & kPathFresh))
     attend_fresh_any(a, wi, sm, path_word >> kPathRowShift);
   else if ((path_word & kPathFresh) && wi.kv_end - wi.kv_begin <= 32)
-    attend_fresh<true, false>(a, wi, sm, 0);
+    attend_fresh_width<false>(a, wi, sm, 0);
   else
     attend_shared(a, wi, sm);
 }

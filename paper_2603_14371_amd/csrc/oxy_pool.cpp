@@ -599,7 +599,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     };
     std::vector<Group> groups;   // in order of first appearance; a batch touches few prefixes
     groups.reserve(16);
-    // How an item's own phase is cut, from the item alone.
+    int32_t short_tile = 8;   // query tokens of a short chunk's own tiles, see below
+    // How an item's own phase is cut, from the item alone but for the width of a short chunk's tiles.
     struct OwnCut {
       bool causal, streams, fresh, short_chunk;
       int32_t n_new, tile, split;   // new tokens, query tokens per work item, keys per split
@@ -611,10 +612,10 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       o.streams = o.n_new <= 2;
       o.fresh = !o.streams && pl.old_len == 0;
       // A short chunk on an empty history (an action chunk, Sec. 3.2) is cut into single 32-key
-      // steps whose wavefronts share the rows out (8 tokens): its tiles start last (their keys are
-      // this step's new rows) and would otherwise be the workgroups the launch ends with.
+      // steps whose wavefronts share the rows out: its tiles start last (their keys are this
+      // step's new rows) and would otherwise be the workgroups the launch ends with.
       o.short_chunk = o.fresh && pl.new_len <= 64 && !c.split_tokens;
-      o.tile = o.streams ? 2 : o.short_chunk ? 8 : tile_tok_for(pl.new_len);
+      o.tile = o.streams ? 2 : o.short_chunk ? short_tile : tile_tok_for(pl.new_len);
       o.split = o.streams ? stream_split_for(c, pl.new_len)
                           : o.short_chunk ? 32 : tile_split_for(c, pl.new_len);
       return o;
@@ -654,7 +655,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     // in two rounds, small launches took 15.2 us a layer where pairs take 10.9.)
     int32_t width = 8;
     {
-      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0, for_pairs = 512;
+      int64_t other = 0, narrow = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0, for_pairs = 512;
       for (const Plan& pl : plan) {
         const OwnCut o = own_cut(pl);
         for (int32_t t0 = 0; t0 < o.n_new; t0 += o.tile) {
@@ -662,6 +663,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
           const int32_t hi = o.causal ? pl.old_len + t0 + n : pl.new_len;
           other += (hi + o.split - 1) / o.split;
         }
+        if (o.short_chunk)   // what tiles of 4 tokens add
+          narrow += ((o.n_new + 3) / 4 - (o.n_new + 7) / 8) * ((pl.new_len + o.split - 1) / o.split);
       }
       for (const Group& g : groups) {
         const int32_t split = tile_split_for(c, g.px->len);
@@ -683,6 +686,12 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         width = 2;
       else if (by4 + other <= resident || (by8 == by4 && by4 + other <= c.max_work_items))
         width = 4;
+      // A short chunk's own tiles are what a small launch ends with (8 tokens: last store 4.6 us after
+      // its start, prefix items 3.8): 4 tokens while every item has a CU.  us a step of 18 layers, 8 / 4
+      // tokens: 50 queries + one request (196 / 208 items) 177.2 / 166.4; with eight requests on eight
+      // observations (258 / 270) 189.6 / 213.0; 2 tokens as 4 in the first (165.9).
+      const int64_t prefix_items = width == 2 ? pairs : width == 4 ? by4 : by8;
+      if (prefix_items + other + narrow <= std::min(256, c.max_work_items)) short_tile = 4;
     }
     for (const Group& g : groups) {
       const Prefix& px = *g.px;

@@ -149,3 +149,23 @@ def test_own_pages_read_past_the_caches_give_the_same_bits(hist, n_new):
         gw.close()
     assert np.array_equal(outs[0]["O"][0], outs[1]["O"][0])
     assert np.array_equal(outs[0]["LSE"][0], outs[1]["LSE"][0])
+
+
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+@pytest.mark.parametrize("chunk", [3, 5, 8, 32, 33, 62, 64])
+def test_width_of_a_short_chunks_own_tiles(chunk, fold):
+    """Tiles of 4 tokens in a small launch, of 8 beside 40 requests (280 further items): the same bits,
+    and the oracle's values."""
+    outs = []
+    for n_dec in (1, 40):
+        b = _TraceBuilder()
+        pid = b.prefix(832)
+        act = b.stream(pid, ACTION)
+        dec = [b.stream(pid, DECODE) for _ in range(n_dec)]
+        b.step([(act, chunk)] + [(d, 1) for d in dec])
+        w = _workload("short_tiles", 5151, 1, 256, b.trace)
+        gw, g, _, _ = run_both(w, poison=True, fold_append=fold)
+        outs.append(g[-1])
+        gw.close()
+    assert np.array_equal(outs[0]["O"][0][:chunk], outs[1]["O"][0][:chunk])
+    assert np.array_equal(outs[0]["LSE"][0][:chunk], outs[1]["LSE"][0][:chunk])
