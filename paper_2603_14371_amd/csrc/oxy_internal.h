@@ -75,6 +75,7 @@ struct AttnArgs {
   int32_t n_work;
   int32_t n_q;
   float scale;
+  int32_t write_through;    // split results go to memory at once (not zero) or when the L2 is flushed
   // Append folded into the work items (all three null otherwise): this step's new rows
   // [n_q][256] bf16 and their slots.  A streaming work item first writes the new rows that lie
   // in its key range into the pool; a fresh tile reads its keys from the new rows themselves
@@ -83,6 +84,11 @@ struct AttnArgs {
   const void* v_new;
   const int32_t* d_slots;
 };
+// Launches with more split results than this write them through.  us per layer, flushed / written
+// through: 1.4 MB 13.2 / 13.0, 2.0 MB (50 queries + one request) 9.3 / 9.5, 2.2 MB 10.5 / 10.7, 2.9 MB
+// 13.7 / 13.3, 3.5 MB 13.6 / 13.5, 4.0 MB 12.6 / 11.9, 7.4 MB 15.3 / 13.2, 14.7 MB 21.5 / 18.1, 64 requests
+// and two chunks on 2048 tokens (7 MB) 25.5 / 24.7, 256 requests 83.1 / 79.5.
+constexpr int kWriteThroughParts = 640;   // 2.6 MB
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s);       // work items, then merge
 // Split-result buffers in static device memory of the current device (kStaticMaxPartials
 // entries, shared by every call on that device).  The first call on a device looks the address

@@ -402,6 +402,25 @@ __device__ __forceinline__ float rescaled(const float l, const float alpha) {
 #pragma clang fp contract(off)
   return l * alpha;
 }
+// Stores a at dst and b 64 bytes on.  A launch leaves its split results dirty in eight L2s, and the
+// merge launch starts only when they have been written back: 1.4 us after the last work item of a
+// launch with 9 split results, 5.8 us with 15 MB of them.  Written through (sc0 sc1) they reach
+// memory while other work items run.  A work item then ends with their acknowledgement, which costs
+// a small launch more than it gives, hence a flag (see kWriteThroughParts).  In inline assembly: no
+// builtin takes these bits with a 64-bit address.  The wait counts that the compiler places after it are
+// only ever stricter than needed, and the two wait states keep the data registers from being
+// written in the cycles in which a 128-bit store still reads them.
+__device__ __forceinline__ void store_piece_pair(const AttnArgs& args, u32x4* dst, const u32x4 a,
+                                                 const u32x4 b) {
+  if (args.write_through) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\t"
+                 "global_store_dwordx4 %0, %2, off offset:64 sc0 sc1\n\t"
+                 "s_nop 1" ::"v"(dst), "v"(a), "v"(b) : "memory");
+  } else {
+    dst[0] = a;
+    dst[4] = b;
+  }
+}
 // One wavefront's 64 dims of a group's split result.  A split result leaves as (m, l, four
 // exponents) and acc * 2^(14 - exponent) in fp16: half the bytes of fp32, with the exponent of the
 // largest value per row and 64 dims, so that the rounding does not depend on the magnitude of the
@@ -441,8 +460,7 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
   if (2 * group + (n >> 3) < wi.n_tok) {
     const size_t row = (size_t)slot * kHeads + (n & 7);
     u32x4* dst = (u32x4*)(a.part_acc + row * kDim + 64 * wv + 8 * g);
-    dst[0] = o[0];
-    dst[4] = o[1];
+    store_piece_pair(a, dst, o[0], o[1]);
     if (g == 0) ((int8_t*)(a.part_ml + row * 4 + 2))[wv] = (int8_t)ex;
   }
 }

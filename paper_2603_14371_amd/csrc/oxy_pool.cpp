@@ -67,14 +67,15 @@ struct StepKey {
   float scale = 0.f;
   int32_t layer_begin = 0, layer_end = 0, mode = 0;   // mode: 0 separate, 1 fused, 2 folded
   int32_t n_work = 0, n_tokens = 0, n_fresh = 0, off_work = 0, off_tables = 0, off_part_off = 0,
-          off_n_parts = 0;
+          off_n_parts = 0, write_through = 0;
   bool operator==(const StepKey& o) const {
     return d_base == o.d_base && k_new == o.k_new && v_new == o.v_new && q == o.q &&
            out == o.out && lse == o.lse && kv_stride == o.kv_stride && q_stride == o.q_stride &&
            lse_stride == o.lse_stride && scale == o.scale && layer_begin == o.layer_begin &&
            layer_end == o.layer_end && mode == o.mode && n_work == o.n_work &&
            n_tokens == o.n_tokens && n_fresh == o.n_fresh && off_work == o.off_work && off_tables == o.off_tables &&
-           off_part_off == o.off_part_off && off_n_parts == o.off_n_parts;
+           off_part_off == o.off_part_off && off_n_parts == o.off_n_parts &&
+           write_through == o.write_through;
   }
   // same number and kinds of launches in the same order: an instantiated graph can be updated
   // in place from a recording of the other
@@ -1032,6 +1033,8 @@ int32_t oxy_stream_append(oxy_pool* p, const oxy_batch* b, int32_t layer, const 
 }
 
 namespace {
+int32_t writes_through(const oxy_batch* b) { return b->n_partials > oxy::kWriteThroughParts; }
+
 oxy::AttnArgs attn_args(const oxy_pool* p, const oxy_batch* b, int32_t layer, const void* q, void* out,
                         float* lse, float scale) {
   const DescSlot& ds = p->slots[b->slot];
@@ -1050,6 +1053,7 @@ oxy::AttnArgs attn_args(const oxy_pool* p, const oxy_batch* b, int32_t layer, co
   a.n_work = b->n_launch;
   a.n_q = b->n_tokens;
   a.scale = scale;
+  a.write_through = writes_through(b);
   a.k_new = a.v_new = nullptr;
   a.d_slots = nullptr;
   return a;
@@ -1201,6 +1205,7 @@ int32_t replay_step(const StepCall& c, hipStream_t s) {
   key.off_tables = b->off_tables;
   key.off_part_off = b->off_part_off;
   key.off_n_parts = b->off_n_parts;
+  key.write_through = writes_through(b);
   const uint64_t now = ++p->graph_clock;
   StepGraph* hit = nullptr;
   for (StepGraph& g : p->graphs)
