@@ -1068,8 +1068,10 @@ __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_
   for (int p = kMergeAhead; p < np; ++p) big = fmaxf(big, ml[(size_t)p * kHeads * 4]);
   float total = 0.f;
   float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto add = [&](const f32x4& mls, const u32x4& v) {   // mls = (m, l, exponents of the 64-dim parts, -)
-    const float wgt = (mls[0] == ninf) ? 0.f : fast_exp2(mls[0] - big);
+  auto weight = [&](const f32x4& mls, const bool live) {   // mls = (m, l, exponents of the 64-dim parts, -)
+    return !live || mls[0] == ninf ? 0.f : fast_exp2(mls[0] - big);
+  };
+  auto add = [&](const float wgt, const f32x4& mls, const u32x4& v) {
     total = __builtin_fmaf(wgt, mls[1], total);
     const int ex = (int32_t)(__float_as_uint(mls[2]) << ex_shift) >> 24;   // signed byte d0 / 64
     const float ws = __builtin_amdgcn_ldexpf(wgt, ex - 14);
@@ -1081,11 +1083,22 @@ __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_
       o[2 * i + 1] = __builtin_fmaf(ws, hi, o[2 * i + 1]);
     }
   };
+  // Four at a time, under one condition: a wavefront has its SIMD to itself here, and one after the
+  // other every split result waited for its own exponential (nine took 0.6 us of a 1.9 us merge).
+  // Past the end the first one is added once more, with weight zero.
 #pragma unroll
-  for (int u = 0; u < kMergeAhead; ++u)
-    if (u < np) add(w[u], x[u]);
-  for (int p = kMergeAhead; p < np; ++p)
-    add(*(const f32x4*)(ml + (size_t)p * kHeads * 4), *(const u32x4*)(src + (size_t)p * stride));
+  for (int u0 = 0; u0 < kMergeAhead; u0 += 4)
+    if (u0 < np) {
+      float wgt[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) wgt[i] = weight(w[u0 + i], u0 + i < np);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) add(wgt[i], w[u0 + i], x[u0 + i]);
+    }
+  for (int p = kMergeAhead; p < np; ++p) {
+    const f32x4 mls = *(const f32x4*)(ml + (size_t)p * kHeads * 4);
+    add(weight(mls, true), mls, *(const u32x4*)(src + (size_t)p * stride));
+  }
   const float inv = 1.f / total;
   const u32x4 packed = {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv),
                         pack_bf16(o[4] * inv, o[5] * inv), pack_bf16(o[6] * inv, o[7] * inv)};
