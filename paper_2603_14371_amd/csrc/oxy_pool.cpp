@@ -120,7 +120,7 @@ struct oxy_batch {
   int32_t slot = -1;
   int32_t flags = 0;
   int32_t n_items = 0, n_tokens = 0, n_work = 0, n_partials = 0;
-  int32_t n_launch = 0;   // n_work rounded up to a multiple of 64 with padding records: the grid
+  int32_t n_launch = 0;   // records rounded up to a multiple of 64 with padding records: the grid
   int32_t n_fresh = 0;    // tokens of items whose own-phase tiles read k_new / v_new (folded append)
   int32_t off_fresh = 0;
   bool append_foldable = false;   // every item has <= 2 new tokens or an empty own history
@@ -128,6 +128,7 @@ struct oxy_batch {
   int32_t off_slots = 0, off_work = 0, off_toks = 0, off_tables = 0, off_part_off = 0,
           off_n_parts = 0;
   std::vector<int32_t> host;  // full descriptor image (kept for introspection)
+  std::vector<int32_t> listed;  // headers of the work list, where some items have two records
 };
 
 namespace {
@@ -570,6 +571,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   };
   std::vector<TableRef> table_refs;
   std::vector<int32_t> order;   // final order of the records; -1 = padding record
+  std::vector<int32_t> wide_tiles;   // items whose last tokens a record of their own takes
+  int32_t n_items_of_list = 0;       // items; records from here on are second halves
   int32_t tbl_words = 0;
   bool foldable = !append_only;
   if (!append_only) {
@@ -600,8 +603,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     };
     std::vector<Group> groups;   // in order of first appearance; a batch touches few prefixes
     groups.reserve(16);
-    int32_t short_tile = 8;   // query tokens of a short chunk's own tiles, see below
-    // How an item's own phase is cut, from the item alone but for the width of a short chunk's tiles.
+    // How an item's own phase is cut, from the item alone.
     struct OwnCut {
       bool causal, streams, fresh, short_chunk;
       int32_t n_new, tile, split;   // new tokens, query tokens per work item, keys per split
@@ -616,7 +618,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       // steps whose wavefronts share the rows out: its tiles start last (their keys are this
       // step's new rows) and would otherwise be the workgroups the launch ends with.
       o.short_chunk = o.fresh && pl.new_len <= 64 && !c.split_tokens;
-      o.tile = o.streams ? 2 : o.short_chunk ? short_tile : tile_tok_for(pl.new_len);
+      o.tile = o.streams ? 2 : o.short_chunk ? 8 : tile_tok_for(pl.new_len);
       o.split = o.streams ? stream_split_for(c, pl.new_len)
                           : o.short_chunk ? 32 : tile_split_for(c, pl.new_len);
       return o;
@@ -656,7 +658,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     // in two rounds, small launches took 15.2 us a layer where pairs take 10.9.)
     int32_t width = 8;
     {
-      int64_t other = 0, narrow = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0, for_pairs = 512;
+      int64_t other = 0, pairs = 0, by4 = 0, by8 = 0, limited = 0, for_pairs = 512;
       for (const Plan& pl : plan) {
         const OwnCut o = own_cut(pl);
         for (int32_t t0 = 0; t0 < o.n_new; t0 += o.tile) {
@@ -664,8 +666,6 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
           const int32_t hi = o.causal ? pl.old_len + t0 + n : pl.new_len;
           other += (hi + o.split - 1) / o.split;
         }
-        if (o.short_chunk)   // what tiles of 4 tokens add
-          narrow += ((o.n_new + 3) / 4 - (o.n_new + 7) / 8) * ((pl.new_len + o.split - 1) / o.split);
       }
       for (const Group& g : groups) {
         const int32_t split = tile_split_for(c, g.px->len);
@@ -687,12 +687,6 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         width = 2;
       else if (by4 + other <= resident || (by8 == by4 && by4 + other <= c.max_work_items))
         width = 4;
-      // A short chunk's own tiles are what a small launch ends with (8 tokens: last store 4.6 us after
-      // its start, prefix items 3.8): 4 tokens while every item has a CU.  us a step of 18 layers, 8 / 4
-      // tokens: 50 queries + one request (196 / 208 items) 177.2 / 166.4; with eight requests on eight
-      // observations (258 / 270) 189.6 / 213.0; 2 tokens as 4 in the first (165.9).
-      const int64_t prefix_items = width == 2 ? pairs : width == 4 ? by4 : by8;
-      if (prefix_items + other + narrow <= std::min(256, c.max_work_items)) short_tile = 4;
     }
     for (const Group& g : groups) {
       const Prefix& px = *g.px;
@@ -755,11 +749,32 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const int32_t kv_hi = cut.causal ? q0 + n : pl.new_len;
         const int32_t nsplit = (kv_hi + split - 1) / split;
         const int32_t base = n_parts[pl.tok0 + t0];
-        for (int32_t s = 0; s < nsplit; ++s)
+        for (int32_t s = 0; s < nsplit; ++s) {
+          if (cut.short_chunk && n > 4) wide_tiles.push_back((int32_t)(hdr.size() / kHdr));
           add_work(tok_off, n, tbl_off, s * split, std::min(kv_hi, (s + 1) * split),
                    cut.causal ? q0 : oxy::kNoCausal, base + s, path);
+        }
         for (int32_t t = 0; t < n; ++t) n_parts[pl.tok0 + t0 + t] += nsplit;
       }
+    }
+    // A short chunk's own tiles are what a small launch ends with (8 tokens: last store 4.6 us after
+    // its start, prefix items 3.8), so while every workgroup has a CU a tile is shared by two: the second
+    // half is a record behind the items, which the work list that callers see does not count.  us a step
+    // of 18 layers, without / with: 50 queries + one request (196 / 208 workgroups) 177.2 / 166.4, with
+    // eight requests on eight observations (258 / 270) 189.6 / 213.0; four shares as two in the first
+    // (165.9).
+    n_items_of_list = (int32_t)(hdr.size() / kHdr);
+    if (n_items_of_list + (int64_t)wide_tiles.size() <= std::min(256, c.max_work_items)) {
+      for (int32_t i : wide_tiles) {
+        int32_t w[kHdr];
+        std::copy(&hdr[(size_t)i * kHdr], &hdr[(size_t)i * kHdr] + kHdr, w);
+        w[oxy::W_TOK_OFF] += 4;
+        w[oxy::W_N_TOK] -= 4;
+        if (w[oxy::W_CAUSAL_Q0] != oxy::kNoCausal) w[oxy::W_CAUSAL_Q0] += 4;
+        hdr.insert(hdr.end(), w, w + kHdr);
+      }
+    } else {
+      wide_tiles.clear();
     }
     // Order of the work list.  Workgroup i runs on XCD i % 8 and every XCD has its own L2, so
     // tiles that read the same pages (same table, same split) are given indices of one residue
@@ -878,7 +893,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         order.erase(std::remove(order.begin(), order.end(), -1), order.end());
     }
   }
-  const int32_t n_work = (int32_t)order.size();
+  const int32_t n_work = (int32_t)order.size();   // records
   int64_t n_partials = 0;
   std::vector<int32_t> part_off(n_parts.size());
   for (size_t t = 0; t < n_parts.size(); ++t) {
@@ -914,7 +929,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   b->flags = flags;
   b->n_items = n_items;
   b->n_tokens = (int32_t)n_tokens;
-  b->n_work = n_work;
+  b->n_work = n_work - (int32_t)wide_tiles.size();
   b->n_partials = (int32_t)n_partials;
   b->append_foldable = foldable;
   // Sections in the order work | slots | part_off | n_parts | fresh tokens | token lists | tables: the block
@@ -961,6 +976,15 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   std::copy(fresh_toks.begin(), fresh_toks.end(), h.begin() + b->off_fresh);
   std::copy(part_off.begin(), part_off.end(), h.begin() + b->off_part_off);
   std::copy(n_parts.begin(), n_parts.end(), h.begin() + b->off_n_parts);
+  if (!wide_tiles.empty()) {   // the list that callers see, where it is not the records
+    const int32_t noop[kHdr] = {0, 0, 0, 0, 0, oxy::kNoCausal, 0, oxy::PATH_NOOP};
+    b->listed.reserve((size_t)b->n_work * kHdr);
+    for (int32_t i : order)
+      if (i < n_items_of_list) {
+        const int32_t* r = i < 0 ? noop : &hdr[(size_t)i * kHdr];
+        b->listed.insert(b->listed.end(), r, r + kHdr);
+      }
+  }
   // Work records, 128 bytes each: header, then inline copies of the tile's token ids and of the
   // block ids of the split's first pages, so a workgroup needs one load before its first pages.
   for (int32_t i = 0; i < b->n_launch; ++i) {
@@ -973,8 +997,9 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     }
     const int32_t* r = &hdr[(size_t)order[i] * kHdr];
     std::copy(r, r + kHdr, w);
+    if (std::find(wide_tiles.begin(), wide_tiles.end(), order[i]) != wide_tiles.end()) w[oxy::W_N_TOK] = 4;
     for (int32_t k = 0; k < oxy::kWorkInlineToks; ++k)
-      w[8 + k] = toks[r[oxy::W_TOK_OFF] + std::min(k, r[oxy::W_N_TOK] - 1)];
+      w[8 + k] = toks[w[oxy::W_TOK_OFF] + std::min(k, w[oxy::W_N_TOK] - 1)];
     const int32_t pg0 = r[oxy::W_KV_BEGIN] / kPage;
     const int32_t npg = blocks_for(r[oxy::W_KV_END]) - pg0;
     for (int32_t k = 0; k < oxy::kWorkInlinePages; ++k)
@@ -1450,8 +1475,9 @@ int32_t oxy_batch_slots(const oxy_batch* b, int64_t* out, int32_t cap) {
 int32_t oxy_batch_work(const oxy_batch* b, int32_t* out, int32_t cap_items) {
   if (!b || !out || cap_items < b->n_work) return fail(OXY_ERR_INVALID_ARG, "batch_work: cap");
   for (int32_t i = 0; i < b->n_work; ++i) {   // the eight header words of each record
-    std::copy(b->host.begin() + b->off_work + (size_t)i * oxy::kWorkWords,
-              b->host.begin() + b->off_work + (size_t)i * oxy::kWorkWords + 8, out + (size_t)i * 8);
+    const int32_t* r = b->listed.empty() ? &b->host[b->off_work + (size_t)i * oxy::kWorkWords]
+                                         : &b->listed[(size_t)i * 8];
+    std::copy(r, r + 8, out + (size_t)i * 8);
     out[(size_t)i * 8 + oxy::W_PATH] &= oxy::kPathMask;
   }
   return OXY_OK;

@@ -152,9 +152,9 @@ def test_own_pages_read_past_the_caches_give_the_same_bits(hist, n_new):
 
 
 @pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
-@pytest.mark.parametrize("chunk", [3, 5, 8, 32, 33, 62, 64])
+@pytest.mark.parametrize("chunk", [3, 5, 8, 12, 32, 33, 62, 64])
 def test_width_of_a_short_chunks_own_tiles(chunk, fold):
-    """Tiles of 4 tokens in a small launch, of 8 beside 40 requests (280 further items), where a long
+    """Tiles shared by two workgroups in a small launch, and whole beside 40 requests (280 further items), where a long
     chunk's split results are also written through: the same bits, and the oracle's values."""
     outs = []
     for n_dec in (1, 40):
