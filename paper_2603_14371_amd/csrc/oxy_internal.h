@@ -102,9 +102,11 @@ struct AppendArgs {
   const void* k_new;
   const void* v_new;
   const int32_t* d_slots;
-  int32_t n_tokens;
+  int32_t n_blocks;      // workgroups: tokens, or runs
   void* layer_base;
-  const int32_t* tok_list;   // null: tokens 0..n_tokens-1; else the n_tokens token ids to append
+  // null: tokens 0..n_blocks-1, a row each; else runs of up to 16 tokens in order that fill a block from
+  // its first slot on, (first token << 4) | (length - 1)
+  const int32_t* runs;
 };
 // merge of `a`, and in the same launch the append described by `next` (may be null)
 hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStream_t s,

@@ -121,7 +121,7 @@ struct oxy_batch {
   int32_t flags = 0;
   int32_t n_items = 0, n_tokens = 0, n_work = 0, n_partials = 0;
   int32_t n_launch = 0;   // records rounded up to a multiple of 64 with padding records: the grid
-  int32_t n_fresh = 0;    // tokens of items whose own-phase tiles read k_new / v_new (folded append)
+  int32_t n_fresh = 0;    // blocks of items whose own-phase tiles read k_new / v_new (folded append)
   int32_t off_fresh = 0;
   bool append_foldable = false;   // every item has <= 2 new tokens or an empty own history
   // word offsets inside the descriptor
@@ -563,7 +563,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   // kept as their eight header words until the order is known.
   constexpr int kHdr = 8;
   std::vector<int32_t> hdr, toks, n_parts(append_only ? 0 : n_tokens, 0);
-  std::vector<int32_t> fresh_toks;   // tokens whose rows the merge launch writes under a folded append
+  std::vector<int32_t> fresh_runs;   // rows that the merge launch writes under a folded append (AppendArgs)
   struct TableRef {
     int32_t off;
     const std::vector<int32_t>* src;
@@ -737,7 +737,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       if (cut.streams && once) path |= oxy::kPathOnce;
       if (cut.fresh) {
         path |= oxy::kPathFresh | (pl.tok0 << oxy::kPathRowShift);
-        for (int32_t t = 0; t < n_new; ++t) fresh_toks.push_back(pl.tok0 + t);
+        for (int32_t t = 0; t < n_new; t += kPage)   // own positions from 0: block by block
+          fresh_runs.push_back((pl.tok0 + t) << 4 | (std::min(kPage, n_new - t) - 1));
       } else if (!cut.streams) {
         foldable = false;   // old and new keys in one tile: only the separate append covers it
       }
@@ -932,7 +933,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   b->n_work = n_work - (int32_t)wide_tiles.size();
   b->n_partials = (int32_t)n_partials;
   b->append_foldable = foldable;
-  // Sections in the order work | slots | part_off | n_parts | fresh tokens | token lists | tables: the block
+  // Sections in the order work | slots | part_off | n_parts | fresh runs | token lists | tables: the block
   // tables, whose size changes whenever a stream takes a new block, come last, so that the
   // device addresses of all sections stay the same from step to step while the shape of the
   // batch (tokens, work items, tile token lists) does -- a recorded launch sequence
@@ -945,7 +946,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   b->off_slots = b->off_work + b->n_launch * oxy::kWorkWords;
   b->off_part_off = b->off_slots + (int32_t)n_tokens;
   b->off_n_parts = b->off_part_off + (int32_t)part_off.size();
-  b->n_fresh = (int32_t)fresh_toks.size();
+  b->n_fresh = (int32_t)fresh_runs.size();
   b->off_fresh = b->off_n_parts + (int32_t)n_parts.size();
   b->off_toks = b->off_fresh + b->n_fresh;
   b->off_tables = b->off_toks + (int32_t)toks.size();
@@ -973,7 +974,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   for (const TableRef& tr : table_refs)
     std::copy(tr.src->begin(), tr.src->begin() + tr.count, tables + tr.off);
   std::copy(toks.begin(), toks.end(), h.begin() + b->off_toks);
-  std::copy(fresh_toks.begin(), fresh_toks.end(), h.begin() + b->off_fresh);
+  std::copy(fresh_runs.begin(), fresh_runs.end(), h.begin() + b->off_fresh);
   std::copy(part_off.begin(), part_off.end(), h.begin() + b->off_part_off);
   std::copy(n_parts.begin(), n_parts.end(), h.begin() + b->off_n_parts);
   if (!wide_tiles.empty()) {   // the list that callers see, where it is not the records
@@ -1148,14 +1149,14 @@ int32_t issue_step(const StepCall& c, hipStream_t s) {
     ap.k_new = (const char*)c.k_new + (size_t)layer * c.kv_layer_stride;
     ap.v_new = (const char*)c.v_new + (size_t)layer * c.kv_layer_stride;
     ap.d_slots = d_desc + b->off_slots;
-    ap.n_tokens = b->n_tokens;
+    ap.n_blocks = b->n_tokens;
     ap.layer_base = layer_base(p, layer);
-    ap.tok_list = nullptr;
+    ap.runs = nullptr;
     return ap;
   };
   auto append_now = [&](int32_t layer) {
     oxy::AppendArgs ap = append_of(layer);
-    return oxy::launch_append(ap.k_new, ap.v_new, ap.d_slots, ap.n_tokens, ap.layer_base, s);
+    return oxy::launch_append(ap.k_new, ap.v_new, ap.d_slots, ap.n_blocks, ap.layer_base, s);
   };
   if (c.fuse) {
     hipError_t e = append_now(c.layer_begin);
@@ -1190,8 +1191,8 @@ int32_t issue_step(const StepCall& c, hipStream_t s) {
     } else if (c.fold && b->n_fresh > 0) {
       // items whose tiles took their keys from k_new / v_new: their rows go to the pool here
       oxy::AppendArgs fr = append_of(layer);
-      fr.n_tokens = b->n_fresh;
-      fr.tok_list = d_desc + b->off_fresh;
+      fr.n_blocks = b->n_fresh;
+      fr.runs = d_desc + b->off_fresh;
       e = oxy::launch_merge_append(a, &fr, s, ev[2], ev[3]);
     } else {
       e = oxy::launch_merge_append(a, nullptr, s, ev[2], ev[3]);

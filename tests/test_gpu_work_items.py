@@ -169,3 +169,23 @@ def test_width_of_a_short_chunks_own_tiles(chunk, fold):
         gw.close()
     assert np.array_equal(outs[0]["O"][0][:chunk], outs[1]["O"][0][:chunk])
     assert np.array_equal(outs[0]["LSE"][0][:chunk], outs[1]["LSE"][0][:chunk])
+
+
+@pytest.mark.parametrize("first,then", [(1, 3), (4, 4), (7, 2), (8, 8), (11, 5), (12, 20), (15, 1), (17, 14)])
+def test_parts_of_a_block_leave_its_other_rows(first, then):
+    """A block's rows written in two parts that meet inside a V chunk, at its end and at a block's end, then
+    a range across the seam written again; and chunks of the same lengths on an empty history,
+    whose rows the merge launch writes.  Pool contents bit for bit."""
+    from parity_util import assert_pool_contents_equal
+    b = _TraceBuilder()
+    pid = b.prefix(first)
+    b.trace.append({"op": "prefix_append", "pid": pid, "n": then, "pos0": first, "data": b.recipe(then)})
+    if first > 1:
+        b.trace.append({"op": "prefix_append", "pid": pid, "n": 2, "pos0": first - 1, "data": b.recipe(2)})
+    acts = [b.stream(pid, ACTION) for _ in range(2)]
+    b.step([(acts[0], first + then), (acts[1], first + 2)])
+    w = _workload("parts", 5154, 2, 64, b.trace)
+    gw, _, ow, _ = run_both(w, poison=True, fold_append=True)
+    n = assert_pool_contents_equal(gw, ow)
+    gw.close()
+    assert n == 2 * (2 * (first + then) + first + 2)
