@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -17,27 +18,33 @@ PROBE_SRC = os.path.join(HERE, "benchaid", "probe_kernels.hip")
 PROBE_LIB = os.path.join(HERE, "benchaid", "libprobe.so")
 
 
-def _hipcc(sources, target, verbose):
-    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    cmd = [hipcc, "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-result"]
-    cmd += DEVICE_FLAGS
-    cmd += list(sources) + ["-o", target]
+MARSHAL_SRC = os.path.join(CSRC, "oxy_python.cpp")
+MARSHAL_LIB = os.path.join(HERE, "libmarshal.so")
+
+
+def _compile(compiler, flags, sources, target, verbose):
+    cmd = [compiler, "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-result"]
+    cmd += list(flags) + list(sources) + ["-o", target]
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines()
                     if "packed-fp32-ops' is not a recognized feature" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError("%s failed:\n%s" % (compiler, out))
     if verbose and out.strip():
         print(out)
     return target
 
 
 def build_library(verbose=False):
-    """liboxy.so (the method) and benchaid/libprobe.so (the benchmark's measurement aids)."""
-    _hipcc([os.path.join(CSRC, s) for s in SOURCES], LIB, verbose)
-    _hipcc([PROBE_SRC], PROBE_LIB, verbose)
+    """liboxy.so (the method), libmarshal.so (list conversion of the Python binding) and
+    benchaid/libprobe.so (the benchmark's measurement aids)."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    _compile(hipcc, DEVICE_FLAGS, [os.path.join(CSRC, s) for s in SOURCES], LIB, verbose)
+    _compile(hipcc, DEVICE_FLAGS, [PROBE_SRC], PROBE_LIB, verbose)
+    _compile(os.environ.get("CXX", "g++"), ["-I" + sysconfig.get_paths()["include"]], [MARSHAL_SRC],
+             MARSHAL_LIB, verbose)   # no HIP in it
     return LIB
 
 

@@ -4,6 +4,9 @@ import ctypes
 import os
 import re
 
+import numpy as np
+import pytest
+
 from paper_2603_14371_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -49,3 +52,20 @@ def test_invalid_configs_are_rejected_without_a_device():
         assert e.code == binding.ERR_INVALID_ARG
     cfg = binding.make_config(18, 8192)
     assert binding.oxy_kv_bytes(cfg) == 18 * 8192 * 16384
+
+
+@pytest.mark.parametrize("values", [
+    [], [0], [5, -1, 2**63 - 1, -2**63], (7, 8), [True, 2], [np.int64(4), 5], [1.0, 2], np.arange(3),
+    np.arange(8, dtype=np.int32)[::3], [2**63], [1, None], ["1"],
+], ids=str)
+def test_integer_sequences_reach_the_library_as_numpy_converts_them(values):
+    """oxy_gather_kv takes any sequence of integers; a list of plain ints is converted natively."""
+    try:
+        want = np.ascontiguousarray(values, dtype=np.int64)
+    except (TypeError, ValueError, OverflowError) as e:
+        with pytest.raises(type(e)):
+            binding._i64(values)
+        return
+    arr, ptr, n = binding._i64(values)
+    assert n == len(want) and [int(x) for x in arr] == want.tolist()
+    assert [ctypes.c_int64.from_address(ptr + 8 * i).value for i in range(n)] == want.tolist()
