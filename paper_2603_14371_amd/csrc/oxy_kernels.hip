@@ -508,7 +508,13 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
 // new rows when the append is folded in.  Otherwise the pages are a prefix's or a multi-token item's,
 // and other work items read them too.  kOnce: non-temporal page loads, for own pages that will have
 // left the L2 by the next step and are not to push shared pages out.
-template <int G, bool kOwnPages, bool kOnce>
+//
+// kSteps: 32-key steps of a round that are loaded, 4, or 2 for a split of at most 64 keys (the last one of
+// an 832-token prefix, a short history's): wavefronts 2 and 3 load no K then, and all of them half of V.
+// (With every step loaded, the pages past the end once more, such an item took as long as one of 128
+// keys and kept the loads of its CU's other workgroup waiting: 18 layers of eight requests and a chunk
+// 185.3 us, now 182.1; others +-0.5 %.)
+template <int G, bool kOwnPages, bool kOnce, int kSteps>
 __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
   int tid = threadIdx.x;
   // keeps what is computed from the thread id inside this instance: shared with the other
@@ -527,7 +533,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
 
 
   u32x4 kr[16];      // kr[2j+hf]: K operand (j, hf) of this wavefront's 32 keys
-  u32x4 vr[4][4];    // vr[s][c]: V operand c of this wavefront's 64 dims, step s of the round
+  u32x4 vr[kSteps][4];    // vr[s][c]: V operand c of this wavefront's 64 dims, step s of the round
   auto page_load = [](const char* p) {
     if constexpr (kOnce) return __builtin_nontemporal_load((const u32x4*)p);
     return *(const u32x4*)p;
@@ -548,7 +554,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     int off = kPageBytes + v_chunk_offset(wv, 0, g & 1, n);
     asm volatile("" : "+v"(off));
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
+    for (int s = 0; s < kSteps; ++s) {
       const char* p = base + (size_t)((g >> 1) ? blks[2 * s + 1] : blks[2 * s]) * kBlockBytes + off;
 #pragma unroll
       for (int c = 0; c < 4; ++c) vr[s][c] = page_load(p + c * 512);
@@ -624,15 +630,24 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     }
     slot_req = request_slot<G>(a, wi, lane);
     __builtin_amdgcn_sched_barrier(0);
-    load_k_of(wi.rec[16 + 2 * wv], wi.rec[17 + 2 * wv]);
-    load_v_of(wi.pages);
-    __builtin_amdgcn_sched_barrier(0);
+    auto store_q = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int r = 0; r < G; ++r) {
-      const u32x4 z = {0, 0, 0, 0};
+      for (int r = 0; r < G; ++r) {
+        const u32x4 z = {0, 0, 0, 0};
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
-        sm.q[r][2 * wv + jj][lane] = 2 * r + sub < wi.n_tok ? query_sign(a, qtmp[r][jj]) : z;
+        for (int jj = 0; jj < 2; ++jj)
+          sm.q[r][2 * wv + jj][lane] = 2 * r + sub < wi.n_tok ? query_sign(a, qtmp[r][jj]) : z;
+      }
+    };
+    // on both sides by itself: behind the join the queries would be waited for as if no K were in flight
+    if (kSteps == 2 && wv >= 2) {
+      load_v_of(wi.pages);
+      store_q();
+    } else {
+      load_k_of(wi.rec[16 + 2 * wv], wi.rec[17 + 2 * wv]);
+      load_v_of(wi.pages);
+      store_q();
     }
   }
   if (tid < 2 * G) sm.slot[tid] = slot_req + wi.part_idx;
@@ -743,10 +758,10 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     __syncthreads();
     // With one group all P operands are requested at once, in front of the branches of a last
     // round; with more the products of one group hide the reads of the next.
-    u32x4 ph[4], pl[4];
+    u32x4 ph[kSteps], pl[kSteps];
     if constexpr (G == 1) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
+      for (int s = 0; s < kSteps; ++s) {
         ph[s] = sm.p[s][0][0][lane];
         pl[s] = sm.p[s][0][1][lane];
       }
@@ -761,7 +776,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     };
     if constexpr (!kLast) {
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
+      for (int s = 0; s < kSteps; ++s)
 #pragma unroll
         for (int r = 0; r < G; ++r) contract(s, r);
       __builtin_amdgcn_sched_barrier(0);   // likewise vr[]
@@ -770,7 +785,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     } else {
       const int nv = nsteps - 4 * round;   // 1..4 steps
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
+      for (int s = 0; s < kSteps; ++s) {
         const int left_s = wi.kv_end - (wi.kv_begin + 32 * (4 * round + s));
         if (s < nv && left_s < 32) {
           const u32x4 mask = value_mask(left_s, g);
@@ -785,7 +800,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
 #pragma unroll
         for (int r = 0; r < G; ++r) {
 #pragma unroll
-          for (int s = 0; s < 4; ++s)
+          for (int s = 0; s < kSteps; ++s)
             if (G > 1 && (decltype(full)::value || s < nv)) contract(s, r);
           const int slot = sm.slot[2 * r + sub];
           store_part(a, wi, slot, acc[r], r, wv, lane);
@@ -797,14 +812,15 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
           }
         }
       };
-      if (G > 1 && nv == 4)
+      if (G > 1 && nv == kSteps)
         finish(std::true_type());
       else
         finish(std::false_type());
     }
   };
-  for (int round = 0; round + 1 < rounds; ++round) round_body(round, std::false_type());
-  round_body(rounds - 1, std::true_type());
+  if constexpr (kSteps == 4)
+    for (int round = 0; round + 1 < rounds; ++round) round_body(round, std::false_type());
+  round_body(kSteps == 4 ? rounds - 1 : 0, std::true_type());
 }
 
 // Own phase of an item whose history was empty before the step (an action chunk): up to eight
@@ -1001,12 +1017,13 @@ __device__ __forceinline__ void attend_fresh_any(const AttnArgs& a, const WorkIt
 }
 
 __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
+  const bool few_keys = wi.kv_end - wi.kv_begin <= 64;
   if (wi.n_tok <= 2)
-    attend<1, false, false>(a, wi, sm);
+    few_keys ? attend<1, false, false, 2>(a, wi, sm) : attend<1, false, false, 4>(a, wi, sm);
   else if (wi.n_tok <= 4)
-    attend<2, false, false>(a, wi, sm);
+    few_keys ? attend<2, false, false, 2>(a, wi, sm) : attend<2, false, false, 4>(a, wi, sm);
   else
-    attend<4, false, false>(a, wi, sm);
+    attend<4, false, false, 4>(a, wi, sm);   // bound by its products and stores: no faster with half the loads
 }
 
 // `work` travels in front of the argument block because the first arguments are preloaded into
@@ -1031,7 +1048,7 @@ __global__ __launch_bounds__(256, 2) void attn_kernel(const int32_t* work, const
   const int path_word = head[W_PATH];
   if ((path_word & kPathMask) == PATH_NOOP) return;   // padding record
   if (path_word & kPathAppends)                       // one or two tokens on their own pages
-    path_word & kPathOnce ? attend<1, true, true>(a, wi, sm) : attend<1, true, false>(a, wi, sm);
+    path_word & kPathOnce ? attend<1, true, true, 4>(a, wi, sm) : attend<1, true, false, 4>(a, wi, sm);
   else if (a.k_new && (path_word & kPathFresh))
     attend_fresh_any(a, wi, sm, path_word >> kPathRowShift);
   else if ((path_word & kPathFresh) && wi.kv_end - wi.kv_begin <= 32)
