@@ -128,7 +128,9 @@ struct oxy_batch {
   int32_t off_slots = 0, off_work = 0, off_toks = 0, off_tables = 0, off_part_off = 0,
           off_n_parts = 0;
   std::vector<int32_t> host;  // full descriptor image (kept for introspection)
-  std::vector<int32_t> listed;  // headers of the work list, where some items have two records
+  // items that two records share: (first record, tokens of the item), and the second records
+  std::vector<std::pair<int32_t, int32_t>> shared_items;
+  std::vector<int32_t> second_records;
 };
 
 namespace {
@@ -977,15 +979,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   std::copy(fresh_runs.begin(), fresh_runs.end(), h.begin() + b->off_fresh);
   std::copy(part_off.begin(), part_off.end(), h.begin() + b->off_part_off);
   std::copy(n_parts.begin(), n_parts.end(), h.begin() + b->off_n_parts);
-  if (!wide_tiles.empty()) {   // the list that callers see, where it is not the records
-    const int32_t noop[kHdr] = {0, 0, 0, 0, 0, oxy::kNoCausal, 0, oxy::PATH_NOOP};
-    b->listed.reserve((size_t)b->n_work * kHdr);
-    for (int32_t i : order)
-      if (i < n_items_of_list) {
-        const int32_t* r = i < 0 ? noop : &hdr[(size_t)i * kHdr];
-        b->listed.insert(b->listed.end(), r, r + kHdr);
-      }
-  }
+  std::vector<char> is_wide(wide_tiles.empty() ? 0 : (size_t)n_items_of_list);
+  for (int32_t i : wide_tiles) is_wide[i] = 1;
   // Work records, 128 bytes each: header, then inline copies of the tile's token ids and of the
   // block ids of the split's first pages, so a workgroup needs one load before its first pages.
   for (int32_t i = 0; i < b->n_launch; ++i) {
@@ -998,7 +993,14 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     }
     const int32_t* r = &hdr[(size_t)order[i] * kHdr];
     std::copy(r, r + kHdr, w);
-    if (std::find(wide_tiles.begin(), wide_tiles.end(), order[i]) != wide_tiles.end()) w[oxy::W_N_TOK] = 4;
+    if (!is_wide.empty()) {
+      if (order[i] >= n_items_of_list) {
+        b->second_records.push_back(i);
+      } else if (is_wide[order[i]]) {
+        b->shared_items.push_back({i, r[oxy::W_N_TOK]});
+        w[oxy::W_N_TOK] = 4;
+      }
+    }
     for (int32_t k = 0; k < oxy::kWorkInlineToks; ++k)
       w[8 + k] = toks[w[oxy::W_TOK_OFF] + std::min(k, w[oxy::W_N_TOK] - 1)];
     const int32_t pg0 = r[oxy::W_KV_BEGIN] / kPage;
@@ -1475,11 +1477,18 @@ int32_t oxy_batch_slots(const oxy_batch* b, int64_t* out, int32_t cap) {
 
 int32_t oxy_batch_work(const oxy_batch* b, int32_t* out, int32_t cap_items) {
   if (!b || !out || cap_items < b->n_work) return fail(OXY_ERR_INVALID_ARG, "batch_work: cap");
-  for (int32_t i = 0; i < b->n_work; ++i) {   // the eight header words of each record
-    const int32_t* r = b->listed.empty() ? &b->host[b->off_work + (size_t)i * oxy::kWorkWords]
-                                         : &b->listed[(size_t)i * 8];
-    std::copy(r, r + 8, out + (size_t)i * 8);
-    out[(size_t)i * 8 + oxy::W_PATH] &= oxy::kPathMask;
+  size_t shared = 0, second = 0;
+  for (int32_t i = 0, rec = 0; i < b->n_work; ++rec) {   // the eight header words of each record
+    if (second < b->second_records.size() && b->second_records[second] == rec) {
+      ++second;
+      continue;
+    }
+    int32_t* o = out + (size_t)i++ * 8;
+    const int32_t* r = &b->host[b->off_work + (size_t)rec * oxy::kWorkWords];
+    std::copy(r, r + 8, o);
+    if (shared < b->shared_items.size() && b->shared_items[shared].first == rec)
+      o[oxy::W_N_TOK] = b->shared_items[shared++].second;
+    o[oxy::W_PATH] &= oxy::kPathMask;
   }
   return OXY_OK;
 }
