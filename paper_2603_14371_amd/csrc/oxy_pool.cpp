@@ -176,7 +176,7 @@ size_t table_words_of(const oxy_pool_config& c) { return 2 * (size_t)c.num_block
 size_t desc_words_of(const oxy_pool_config& c) {
   return (size_t)c.max_append_tokens + (size_t)oxy::kWorkWords * c.max_work_items +
          2 * (size_t)c.max_q_tokens /* token lists */ + table_words_of(c) /* tables */ +
-         3 * (size_t)c.max_q_tokens /* part_off, n_parts, fresh tokens */;
+         3 * (size_t)c.max_q_tokens /* part_off, n_parts, fresh runs */;
 }
 
 void layout_of(const oxy_pool_config& c, size_t* acc_off, size_t* ml_off, size_t* total) {
