@@ -681,37 +681,43 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     const bool need_mask = (kLast && left < 32) || pos + 31 > wi.q0;
     constexpr int kAhead = G == 4 ? 2 : 4;
     f32x4 s0[G], s1[G];
-#pragma unroll
-    for (int r = 0; r < G; ++r) {
-      s0[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      s1[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const u32x4 q = sm.q[r][j][lane];
-        s0[r] = mfma16(kr[2 * j], q, s0[r]);
-        s1[r] = mfma16(kr[2 * j + 1], q, s1[r]);
-      }
-    }
-    // a few query reads ahead of the products: more would cost registers that four groups do
-    // not leave, fewer make every pair of products wait a full LDS round trip
-    __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
-#pragma unroll
-    for (int i = 0; i < 8 * G - kAhead; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-    }
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * kAhead, 0);
-    if (need_mask) {   // wave-uniform: only the end of a split or the causal diagonal
-      const int k0 = pos + 16 * (g >> 1) + 4 * (g & 1);
+    // with two steps wavefronts 2 and 3 have no keys (and kr[] was never written): nothing is visible
+    if (kSteps == 4 || wv < 2) {
 #pragma unroll
       for (int r = 0; r < G; ++r) {
-        const int end = min(wi.kv_end, wi.q0 + 2 * r + sub + 1) - k0;
+        s0[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        s1[r] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          s0[r][e] = e < end ? s0[r][e] : ninf;
-          s1[r][e] = 8 + e < end ? s1[r][e] : ninf;
+        for (int j = 0; j < 8; ++j) {
+          const u32x4 q = sm.q[r][j][lane];
+          s0[r] = mfma16(kr[2 * j], q, s0[r]);
+          s1[r] = mfma16(kr[2 * j + 1], q, s1[r]);
         }
       }
+      // a few query reads ahead of the products: more would cost registers that four groups do
+      // not leave, fewer make every pair of products wait a full LDS round trip
+      __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+      for (int i = 0; i < 8 * G - kAhead; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * kAhead, 0);
+      if (need_mask) {   // wave-uniform: only the end of a split or the causal diagonal
+        const int k0 = pos + 16 * (g >> 1) + 4 * (g & 1);
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+          const int end = min(wi.kv_end, wi.q0 + 2 * r + sub + 1) - k0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            s0[r][e] = e < end ? s0[r][e] : ninf;
+            s1[r][e] = 8 + e < end ? s1[r][e] : ninf;
+          }
+        }
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < G; ++r) s0[r] = s1[r] = (f32x4){ninf, ninf, ninf, ninf};
     }
 #pragma unroll
     for (int r = 0; r < G; ++r) {

@@ -35,6 +35,15 @@ def test_edges_of_steps_rounds_and_tiles(prefix_len, chunk, hist, n_new, split, 
     gw.close()
 
 
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+@pytest.mark.parametrize("prefix_len", [34, 63, 64, 65, 191, 192])
+@pytest.mark.parametrize("chunk,hist,n_new", [(1, 60, 4), (4, 29, 3), (2, 70, 1)])
+def test_splits_of_at_most_64_keys(prefix_len, chunk, hist, n_new, fold):
+    """Two of the four wavefronts have no keys there: they load none and add nothing."""
+    gw, _, _, _ = run_both(_step(prefix_len, chunk, hist, n_new), poison=True, fold_append=fold)
+    gw.close()
+
+
 @pytest.mark.parametrize("scale", [-1.0 / 16, 0.0])
 def test_softmax_scale_may_be_negative_or_zero(scale):
     w = _step(150, 9, 140, 1)
