@@ -1022,14 +1022,20 @@ __device__ __forceinline__ void attend_fresh_any(const AttnArgs& a, const WorkIt
     attend_fresh<false, true, 4>(a, wi, sm, row0);
 }
 
+// The narrowest comes last, and with it the four-step instance that every decode step runs: the compiler
+// lays the instances out in the order of these tests, and the last one lies next to the kernel's common
+// exit.  With two-step instances between them a launch whose code has left the caches (other kernels and a
+// read of 512 MB in front of every launch) fetched one more line from memory at its end: one request on
+// 832 tokens 7.3-7.5 us, now 6.9-7.1, three 7.1-7.2 / 7.0, one with a chunk 7.6-7.8 / 7.3-7.5; larger launches and
+// launches that follow each other within 1 %.
 __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
   const bool few_keys = wi.kv_end - wi.kv_begin <= 64;
-  if (wi.n_tok <= 2)
-    few_keys ? attend<1, false, false, 2>(a, wi, sm) : attend<1, false, false, 4>(a, wi, sm);
-  else if (wi.n_tok <= 4)
+  if (wi.n_tok > 4)
+    attend<4, false, false, 4>(a, wi, sm);   // bound by its products and stores: no faster with half the loads
+  else if (wi.n_tok > 2)
     few_keys ? attend<2, false, false, 2>(a, wi, sm) : attend<2, false, false, 4>(a, wi, sm);
   else
-    attend<4, false, false, 4>(a, wi, sm);   // bound by its products and stores: no faster with half the loads
+    few_keys ? attend<1, false, false, 2>(a, wi, sm) : attend<1, false, false, 4>(a, wi, sm);
 }
 
 // `work` travels in front of the argument block because the first arguments are preloaded into
