@@ -147,10 +147,13 @@ __global__ __launch_bounds__(256) void append_kernel(const uint16_t* __restrict_
 
 // Rows of keys key0..key0+n-1 of one block, by one workgroup: all rows are read at once, K goes out as
 // 16-byte chunks and V, turned through LDS, as whole chunks where all eight keys of one are among them
-// and key by key elsewhere, so that nothing else in the page is touched.
+// and key by key elsewhere, so that nothing else in the page is touched.  kWhole: all sixteen rows, without
+// the other form's clamps and conditions (52 blocks of one layer 2.8 us, with them 3.1; 50 blocks in each of 18
+// layers 6.2 / 6.4, kernel trace).
 struct __align__(16) PageLds {
   uint16_t v[kPage][kDim + 8];   // +8: rows land in different banks
 };
+template <bool kWhole>
 __device__ __forceinline__ void append_page(const uint16_t* __restrict__ k_src,
                                             const uint16_t* __restrict__ v_src, const int key0,
                                             const int n, char* __restrict__ block, PageLds& sm,
@@ -160,14 +163,15 @@ __device__ __forceinline__ void append_page(const uint16_t* __restrict__ k_src,
   u32x4 k[2], v[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    const int idx = t + 256 * i, row = min(max((idx >> 5) - key0, 0), n - 1), cd = idx & 31;
+    const int idx = t + 256 * i, cd = idx & 31;
+    const int row = kWhole ? idx >> 5 : min(max((idx >> 5) - key0, 0), n - 1);
     k[i] = *(const u32x4*)(k_src + (size_t)row * kDim + cd * 8);
     v[i] = *(const u32x4*)(v_src + (size_t)row * kDim + cd * 8);
   }
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int idx = t + 256 * i, key = idx >> 5, cd = idx & 31;
-    if (key >= key0 && key < key0 + n)
+    if (kWhole || (key >= key0 && key < key0 + n))
       *(u32x4*)(kp + k_chunk_offset(cd >> 2, key >> 3, cd & 3, key & 7)) = k[i];
     *(u32x4*)(&sm.v[key][cd * 8]) = v[i];
   }
@@ -181,7 +185,7 @@ __device__ __forceinline__ void append_page(const uint16_t* __restrict__ k_src,
       const int k0 = (e < 2 ? 4 * gp : 8 + 4 * gp) + 2 * (e & 1);
       out[e] = (uint32_t)sm.v[k0][d] | ((uint32_t)sm.v[k0 + 1][d] << 16);
     }
-    if (key0 <= 4 * gp && key0 + n >= 12 + 4 * gp) {
+    if (kWhole || (key0 <= 4 * gp && key0 + n >= 12 + 4 * gp)) {
       *(u32x4*)(vp + ci * 16) = out;
     } else {
 #pragma unroll
@@ -192,6 +196,15 @@ __device__ __forceinline__ void append_page(const uint16_t* __restrict__ k_src,
       }
     }
   }
+}
+__device__ __forceinline__ void append_rows(const uint16_t* __restrict__ k_src,
+                                            const uint16_t* __restrict__ v_src, const int key0,
+                                            const int n, char* __restrict__ block, PageLds& sm,
+                                            const int t) {
+  if (n == kPage)
+    append_page<true>(k_src, v_src, 0, kPage, block, sm, t);
+  else
+    append_page<false>(k_src, v_src, key0, n, block, sm, t);
 }
 
 // Append of a run of consecutive positions of one table (a prefix): one workgroup per block.
@@ -210,7 +223,7 @@ __global__ __launch_bounds__(256) void append_blocks_kernel(const uint16_t* __re
   layer_base += blockIdx.y * pool_layer_stride;
   const int page = (pos0 >> 4) + blockIdx.x;
   const int lo = max(pos0, page * kPage), hi = min(pos0 + n_tokens, (page + 1) * kPage);
-  append_page(k_new + (size_t)(lo - pos0) * kDim, v_new + (size_t)(lo - pos0) * kDim, lo & 15, hi - lo,
+  append_rows(k_new + (size_t)(lo - pos0) * kDim, v_new + (size_t)(lo - pos0) * kDim, lo & 15, hi - lo,
               layer_base + (size_t)blocks.v[blockIdx.x] * kBlockBytes, sm, threadIdx.x);
 }
 
@@ -1177,7 +1190,7 @@ __global__ __launch_bounds__(256) void merge_append_kernel(const int32_t* n_part
   const uint16_t* k_row = (const uint16_t*)nx.k_new + (size_t)tok * kDim;
   const uint16_t* v_row = (const uint16_t*)nx.v_new + (size_t)tok * kDim;
   if (nx.runs)   // a row each: 18 layers of 50 queries + one request 167.2 us instead of 163.6
-    append_page(k_row, v_row, 0, (run & 15) + 1, (char*)nx.layer_base + (size_t)(slot >> 4) * kBlockBytes,
+    append_rows(k_row, v_row, 0, (run & 15) + 1, (char*)nx.layer_base + (size_t)(slot >> 4) * kBlockBytes,
                 sm, threadIdx.x);
   else
     append_row(k_row, v_row, slot, (char*)nx.layer_base, threadIdx.x);
