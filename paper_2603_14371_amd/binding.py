@@ -4,6 +4,7 @@ Device buffers are passed as integer addresses (torch tensors' data_ptr()); the 
 stream as torch.cuda.current_stream().cuda_stream.  Every function raises OxyError
 on a negative status.  There is no fallback: if the library is missing, loading fails.
 """
+import array
 import ctypes
 import os
 
@@ -152,11 +153,15 @@ _marshal_lib = None
 
 
 def _marshal():
+    """libmarshal.so, or False where it is not built (Python's headers are not everywhere)."""
     global _marshal_lib
     if _marshal_lib is None:
-        L = ctypes.PyDLL(MARSHAL_PATH)   # keeps the GIL
-        L.oxy_ints_of_list.argtypes = [ctypes.py_object, ctypes.c_void_p, ctypes.c_int64]
-        _marshal_lib = L
+        try:
+            L = ctypes.PyDLL(MARSHAL_PATH)   # keeps the GIL
+            L.oxy_ints_of_list.argtypes = [ctypes.py_object, ctypes.c_void_p, ctypes.c_int64]
+            _marshal_lib = L
+        except (OSError, AttributeError):
+            _marshal_lib = False
     return _marshal_lib
 
 
@@ -302,10 +307,17 @@ def _i64(values):
     # a list of Python ints, as oxy_batch_slots returns it, is converted natively: 1338 slots take
     # 5.6 us (array.array 22.2, struct.pack 10.2, numpy 35.8), and a read-back converts in every layer
     if type(values) is list:
-        n = len(values)
-        arr = (ctypes.c_int64 * n)()
-        if _marshal().oxy_ints_of_list(values, arr, n):
-            return arr, ctypes.addressof(arr), n
+        n, native = len(values), _marshal()
+        if native:
+            arr = (ctypes.c_int64 * n)()
+            if native.oxy_ints_of_list(values, arr, n):
+                return arr, ctypes.addressof(arr), n
+        else:
+            try:
+                arr = array.array("q", values)
+                return arr, arr.buffer_info()[0], n
+            except (TypeError, OverflowError):
+                pass    # other element types: numpy's conversion rules
     arr = np.ascontiguousarray(values, dtype=np.int64)
     return arr, arr.ctypes.data, len(arr)
 

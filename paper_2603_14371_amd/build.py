@@ -1,5 +1,6 @@
 """Builds liboxy.so (HIP kernels for gfx950 + host pool) in-tree with hipcc."""
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -38,13 +39,20 @@ def _compile(compiler, flags, sources, target, verbose):
 
 
 def build_library(verbose=False):
-    """liboxy.so (the method), libmarshal.so (list conversion of the Python binding) and
-    benchaid/libprobe.so (the benchmark's measurement aids)."""
+    """liboxy.so (the method), benchaid/libprobe.so (the benchmark's measurement aids) and, where
+    Python's headers and a host compiler are there, libmarshal.so (list conversion of the Python
+    binding, which converts by Python's own means without it)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     _compile(hipcc, DEVICE_FLAGS, [os.path.join(CSRC, s) for s in SOURCES], LIB, verbose)
     _compile(hipcc, DEVICE_FLAGS, [PROBE_SRC], PROBE_LIB, verbose)
-    _compile(os.environ.get("CXX", "g++"), ["-I" + sysconfig.get_paths()["include"]], [MARSHAL_SRC],
-             MARSHAL_LIB, verbose)   # no HIP in it
+    headers, cxx = sysconfig.get_paths()["include"], os.environ.get("CXX", "g++")
+    if os.path.exists(os.path.join(headers, "Python.h")) and shutil.which(cxx):
+        _compile(cxx, ["-I" + headers], [MARSHAL_SRC], MARSHAL_LIB, verbose)   # no HIP in it
+    else:
+        if os.path.exists(MARSHAL_LIB):
+            os.remove(MARSHAL_LIB)   # of an earlier build, maybe for another Python
+        if verbose:
+            print("libmarshal.so not built: no Python.h in %s or no %s" % (headers, cxx))
     return LIB
 
 

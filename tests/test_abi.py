@@ -58,8 +58,16 @@ def test_invalid_configs_are_rejected_without_a_device():
     [], [0], [5, -1, 2**63 - 1, -2**63], (7, 8), [True, 2], [np.int64(4), 5], [1.0, 2], np.arange(3),
     np.arange(8, dtype=np.int32)[::3], [2**63], [1, None], ["1"],
 ], ids=str)
-def test_integer_sequences_reach_the_library_as_numpy_converts_them(values):
-    """oxy_gather_kv takes any sequence of integers; a list of plain ints is converted natively."""
+@pytest.mark.parametrize("native", [True, False], ids=["libmarshal", "liboxy_alone"])
+def test_integer_sequences_reach_the_library_as_numpy_converts_them(values, native, monkeypatch):
+    """oxy_gather_kv takes any sequence of integers; a list of plain ints is converted natively where
+    libmarshal.so is there."""
+    monkeypatch.setattr(binding, "_marshal_lib", None)
+    if native and not os.path.exists(binding.MARSHAL_PATH):
+        pytest.skip("libmarshal.so is not built here")
+    if not native:
+        monkeypatch.setattr(binding, "MARSHAL_PATH", "/nowhere/libmarshal.so")
+    assert bool(binding._marshal()) == native
     try:
         want = np.ascontiguousarray(values, dtype=np.int64)
     except (TypeError, ValueError, OverflowError) as e:
@@ -69,3 +77,18 @@ def test_integer_sequences_reach_the_library_as_numpy_converts_them(values):
     arr, ptr, n = binding._i64(values)
     assert n == len(want) and [int(x) for x in arr] == want.tolist()
     assert [ctypes.c_int64.from_address(ptr + 8 * i).value for i in range(n)] == want.tolist()
+
+
+@pytest.mark.parametrize("missing", ["compiler", "headers"])
+def test_the_library_builds_without_python_headers_or_a_host_compiler(missing, monkeypatch, tmp_path):
+    from paper_2603_14371_amd import build
+    built = []
+    monkeypatch.setattr(build, "_compile", lambda compiler, flags, sources, target, verbose: built.append(target))
+    monkeypatch.setattr(build, "MARSHAL_LIB", str(tmp_path / "libmarshal.so"))
+    (tmp_path / "libmarshal.so").write_text("of an earlier build")
+    if missing == "compiler":
+        monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    else:
+        monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    assert build.build_library() == build.LIB
+    assert built == [build.LIB, build.PROBE_LIB] and not os.path.exists(build.MARSHAL_LIB)
