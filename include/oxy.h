@@ -279,9 +279,16 @@ int32_t oxy_pool_stats(oxy_pool *pool, int32_t *free_blocks, int32_t *live_prefi
 int32_t oxy_batch_info(const oxy_batch *batch, int32_t *n_items, int32_t *n_tokens,
                        int32_t *n_work, int32_t *n_partials);
 int32_t oxy_batch_slots(const oxy_batch *batch, int64_t *out, int32_t cap);
-/* Raw work list, 8 int32 per item: token-list offset, token count, block-table offset,
- * kv_begin, kv_end, causal base position (or 0x3fffffff), partial index, path. */
+/* Work items, 8 int32 each: token-list offset, token count, block-table offset, kv_begin,
+ * kv_end, causal base position (or 0x3fffffff), partial index, path (2 = padding).  An item whose
+ * tokens two records of the launch share is listed once, with all of them. */
 int32_t oxy_batch_work(const oxy_batch *batch, int32_t *out, int32_t cap_items);
+/* The records exactly as a launch reads them, one workgroup each, 32 int32: the eight words above
+ * (the path word with the flags of its upper bits), the query token ids (the last one repeated up
+ * to eight) and the block ids of the first 16 pages (likewise).  An item that two records share
+ * is two of them.  out HOST [cap_records] may be NULL with cap_records 0: only *n_records is set. */
+int32_t oxy_batch_records(const oxy_batch *batch, int32_t *out, int32_t cap_records,
+                          int32_t *n_records);
 
 /* --- frame scheduler: the per-frame execution flow (Alg. 1, App. A.3; Sec. 3.2) --------
  * Host logic only.  Per frame: the caller appends the prefill KV of each new observation to a

@@ -37,7 +37,7 @@ EXPORTS = [
     "oxy_gather_kv",
     "oxy_stream_info", "oxy_stream_blocks", "oxy_prefix_info", "oxy_prefix_blocks",
     "oxy_block_refcounts", "oxy_free_blocks", "oxy_pool_stats", "oxy_batch_info",
-    "oxy_batch_slots", "oxy_batch_work",
+    "oxy_batch_slots", "oxy_batch_work", "oxy_batch_records",
     "oxy_sched_create", "oxy_sched_destroy", "oxy_sched_admit", "oxy_sched_next_step",
     "oxy_sched_end_frame", "oxy_sched_info", "oxy_sched_request_info", "oxy_sched_calibrate",
 ]
@@ -130,6 +130,7 @@ def lib():
             "oxy_batch_info": [vp, pi32, pi32, pi32, pi32],
             "oxy_batch_slots": [vp, ctypes.POINTER(ctypes.c_int64), i32],
             "oxy_batch_work": [vp, pi32, i32],
+            "oxy_batch_records": [vp, pi32, i32, pi32],
             "oxy_sched_create": [vp, ctypes.POINTER(SchedConfig), ctypes.POINTER(vp)],
             "oxy_sched_destroy": [vp],
             "oxy_sched_admit": [vp, i32, i32, pi32],
@@ -405,6 +406,15 @@ def oxy_batch_work(batch):
     out = np.zeros((max(n, 1), 8), dtype=np.int32)
     _check(lib().oxy_batch_work(batch, _p32(out), n))
     return out[:n]
+
+
+def oxy_batch_records(batch):
+    """The launched records, padding included: [n, 32]."""
+    n = _i32()
+    _check(lib().oxy_batch_records(batch, None, 0, ctypes.byref(n)))
+    out = np.zeros((max(n.value, 1), 32), dtype=np.int32)
+    _check(lib().oxy_batch_records(batch, _p32(out), n.value, ctypes.byref(n)))
+    return out[:n.value]
 
 
 def oxy_sched_create(pool, k, denoise_steps, chunk, max_active=0, mode=SCHED_BATCHED):

@@ -1493,4 +1493,14 @@ int32_t oxy_batch_work(const oxy_batch* b, int32_t* out, int32_t cap_items) {
   return OXY_OK;
 }
 
+int32_t oxy_batch_records(const oxy_batch* b, int32_t* out, int32_t cap_records, int32_t* n_records) {
+  if (!b || !n_records) return fail(OXY_ERR_INVALID_ARG, "batch_records: null argument");
+  *n_records = b->n_launch;
+  if (!out && cap_records == 0) return OXY_OK;
+  if (!out || cap_records < b->n_launch) return fail(OXY_ERR_INVALID_ARG, "batch_records: cap");
+  const auto first = b->host.begin() + b->off_work;
+  std::copy(first, first + (size_t)b->n_launch * oxy::kWorkWords, out);
+  return OXY_OK;
+}
+
 }  // extern "C"

@@ -150,6 +150,11 @@ int main(int argc, char** argv) {
         std::vector<int32_t> work((size_t)n_work * 8 + 8);
         if (!(flags & OXY_BATCH_APPEND_ONLY))
           CHECK(oxy_batch_work(b, work.data(), n_work) == OXY_OK, "batch_work");
+        int32_t n_rec = -1;
+        CHECK(oxy_batch_records(b, nullptr, 0, &n_rec) == OXY_OK && n_rec >= n_work, "%d records", n_rec);
+        std::vector<int32_t> rec((size_t)n_rec * 32);
+        CHECK(oxy_batch_records(b, rec.data(), n_rec, &n_rec) == OXY_OK, "batch_records");
+        CHECK(n_rec == 0 || oxy_batch_records(b, rec.data(), n_rec - 1, &n_rec) != OXY_OK, "records past cap");
         if (device) {   // the launches are stand-ins; what runs is the host side of each call
           void* p = (void*)16;
           CHECK(oxy_stream_append(pool, b, 0, p, p, nullptr) == OXY_OK, "stream_append");
