@@ -145,39 +145,72 @@ def test_gather_of_any_slot_list(pick):
     assert np.array_equal(gk, k[order]) and np.array_equal(gv, v[order])
 
 
+def _launched(prefix_len, chunk, decoders, n_layers=1):
+    """Records (padding left out), work items and split results of a step of one chunk and
+    `decoders` = (own history, new tokens) each, all on one prefix; from a host-only pool."""
+    from paper_2603_14371_amd import binding as B
+    pool = B.oxy_pool_create(B.make_config(n_layers, 4096, flags=B.POOL_HOST_ONLY, max_q_tokens=512,
+                                           max_append_tokens=1 << 16, max_partials=8192))
+    pid = B.oxy_prefix_create(pool)
+    B.oxy_prefix_append(pool, pid, 0, 0, 0, prefix_len, 0, 0)
+    items = [(B.oxy_stream_create(pool, pid, B.KIND_ACTION), chunk)]
+    for hist, n_new in decoders:
+        items.append((B.oxy_stream_create(pool, pid, B.KIND_DECODE), n_new))
+        if hist:
+            B.oxy_batch_destroy(B.oxy_batch_build(pool, [(items[-1][0], hist)], B.BATCH_APPEND_ONLY, 0))
+    batch = B.oxy_batch_build(pool, items, 0, 0)
+    rec, work, n_partials = B.oxy_batch_records(batch), B.oxy_batch_work(batch), B.oxy_batch_info(batch)[3]
+    B.oxy_batch_destroy(batch)
+    B.oxy_pool_destroy(pool)
+    return rec[rec[:, 7] & 15 != 2], work[work[:, 7] != 2], n_partials
+
+
 @pytest.mark.parametrize("hist,n_new", [(40, 1), (127, 2), (300, 1), (520, 2)])
 def test_own_pages_read_past_the_caches_give_the_same_bits(hist, n_new):
     """The non-temporal loads are taken where the pages of all layers are more than 128 MB: the same
     layer in a pool of one layer and in one of enough layers, written and read by the work items."""
-    outs = []
+    outs, marked = [], []
     for n_layers in (1, 1 + (128 << 20) // ((300 + hist) << 10)):
         w = _step(300, 9, hist, n_new, n_layers)
         w["num_blocks"] = 64
+        rec, _, _ = _launched(300, 9, [(hist, n_new)], n_layers)
+        own = rec[rec[:, 7] & 32 != 0]             # a decode item's own pages; 64 = past the caches
+        marked.append(set((own[:, 7] & 64).tolist()))
         gw, g, _, _ = run_both(w, layers=[0], poison=True, fold_append=True)
         outs.append(g[-1])
         gw.close()
+    assert marked == [{0}, {64}]
     assert np.array_equal(outs[0]["O"][0], outs[1]["O"][0])
     assert np.array_equal(outs[0]["LSE"][0], outs[1]["LSE"][0])
 
 
 @pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
-@pytest.mark.parametrize("chunk", [3, 5, 8, 12, 32, 33, 62, 64])
-def test_width_of_a_short_chunks_own_tiles(chunk, fold):
-    """Tiles shared by two workgroups in a small launch, and whole beside 40 requests (280 further items), where a long
-    chunk's split results are also written through: the same bits, and the oracle's values."""
+@pytest.mark.parametrize("prefix_len,chunk", [(256, n) for n in (3, 5, 8, 12, 32, 33, 62, 64)] + [(832, 62), (832, 64)])
+def test_width_of_a_short_chunks_own_tiles(prefix_len, chunk, fold):
+    """A chunk's tiles shared by two workgroups in a small launch and whole in one of more than 256, and their
+    split results left in the caches and written through (more than 640 of them): the same bits, and the
+    oracle's values.  On 832 tokens a long chunk alone has whole tiles, beside 40 requests (whose
+    prefix items are wider) shared ones."""
+    if prefix_len == 256:   # (requests, tiles shared, written through)
+        batches = [(1, chunk > 4, False), (50 if chunk <= 33 else 24, False, False), (130, False, True)]
+    else:
+        batches = [(1, False, False), (40, True, True)]
     outs = []
-    for n_dec in (1, 40):
+    for n_dec, shared, through in batches:
+        rec, work, n_partials = _launched(prefix_len, chunk, [(0, 1)] * n_dec)
+        assert (len(rec) > len(work)) == shared and (n_partials > 640) == through
         b = _TraceBuilder()
-        pid = b.prefix(832)
+        pid = b.prefix(prefix_len)
         act = b.stream(pid, ACTION)
         dec = [b.stream(pid, DECODE) for _ in range(n_dec)]
         b.step([(act, chunk)] + [(d, 1) for d in dec])
         w = _workload("short_tiles", 5151, 1, 256, b.trace)
-        gw, g, _, _ = run_both(w, poison=True, fold_append=fold)
+        gw, g, _, _ = run_both(w, poison=True, fold_append=fold, max_q_tokens=512, max_append_tokens=512)
         outs.append(g[-1])
         gw.close()
-    assert np.array_equal(outs[0]["O"][0][:chunk], outs[1]["O"][0][:chunk])
-    assert np.array_equal(outs[0]["LSE"][0][:chunk], outs[1]["LSE"][0][:chunk])
+    for o in outs[1:]:
+        assert np.array_equal(outs[0]["O"][0][:chunk], o["O"][0][:chunk])
+        assert np.array_equal(outs[0]["LSE"][0][:chunk], o["LSE"][0][:chunk])
 
 
 @pytest.mark.parametrize("first,then", [(1, 3), (4, 4), (7, 2), (8, 8), (11, 5), (12, 20), (15, 1), (17, 14)])
