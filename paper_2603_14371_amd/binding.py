@@ -306,9 +306,11 @@ def oxy_batch_destroy(batch):
 def _i64(values):
     """(array, address, length) of a sequence of integers."""
     # a list of Python ints, as oxy_batch_slots returns it, is converted natively: 1338 slots take
-    # 5.6 us (array.array 22.2, struct.pack 10.2, numpy 35.8), and a read-back converts in every layer
+    # 5.8 us (array.array 24.0, struct.pack 10.2, numpy 35.8), and a read-back converts in every layer;
+    # a short one is not worth the call (8 slots 1.0 us, array.array 0.5; 64 slots 1.2 / 1.4)
     if type(values) is list:
-        n, native = len(values), _marshal()
+        n = len(values)
+        native = _marshal() if n >= 48 else False
         if native:
             arr = (ctypes.c_int64 * n)()
             if native.oxy_ints_of_list(values, arr, n):

@@ -58,16 +58,26 @@ def test_invalid_configs_are_rejected_without_a_device():
     [], [0], [5, -1, 2**63 - 1, -2**63], (7, 8), [True, 2], [np.int64(4), 5], [1.0, 2], np.arange(3),
     np.arange(8, dtype=np.int32)[::3], [2**63], [1, None], ["1"],
 ], ids=str)
+@pytest.mark.parametrize("times", [1, 20, 48])
 @pytest.mark.parametrize("native", [True, False], ids=["libmarshal", "liboxy_alone"])
-def test_integer_sequences_reach_the_library_as_numpy_converts_them(values, native, monkeypatch):
-    """oxy_gather_kv takes any sequence of integers; a list of plain ints is converted natively where
-    libmarshal.so is there."""
+def test_integer_sequences_reach_the_library_as_numpy_converts_them(values, native, times, monkeypatch):
+    """oxy_gather_kv takes any sequence of integers; a long list of plain ints is converted natively
+    where libmarshal.so is there."""
+    values = np.tile(values, times) if isinstance(values, np.ndarray) else values * times
     monkeypatch.setattr(binding, "_marshal_lib", None)
     if native and not os.path.exists(binding.MARSHAL_PATH):
         pytest.skip("libmarshal.so is not built here")
     if not native:
         monkeypatch.setattr(binding, "MARSHAL_PATH", "/nowhere/libmarshal.so")
     assert bool(binding._marshal()) == native
+    calls = []
+    if native:
+        class Counting:
+            def oxy_ints_of_list(self, *args):
+                calls.append(args)
+                return lib.oxy_ints_of_list(*args)
+        lib = binding._marshal()
+        monkeypatch.setattr(binding, "_marshal_lib", Counting())
     try:
         want = np.ascontiguousarray(values, dtype=np.int64)
     except (TypeError, ValueError, OverflowError) as e:
@@ -75,6 +85,7 @@ def test_integer_sequences_reach_the_library_as_numpy_converts_them(values, nati
             binding._i64(values)
         return
     arr, ptr, n = binding._i64(values)
+    assert len(calls) == (native and type(values) is list and n >= 48)
     assert n == len(want) and [int(x) for x in arr] == want.tolist()
     assert [ctypes.c_int64.from_address(ptr + 8 * i).value for i in range(n)] == want.tolist()
 
