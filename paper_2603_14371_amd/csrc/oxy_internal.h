@@ -84,11 +84,20 @@ struct AttnArgs {
   const void* v_new;
   const int32_t* d_slots;
 };
-// Launches with more split results than this write them through.  us per layer, flushed / written
-// through: 1.4 MB 13.2 / 13.0, 2.0 MB (50 queries + one request) 9.3 / 9.5, 2.2 MB 10.5 / 10.7, 2.9 MB
-// 13.7 / 13.3, 3.5 MB 13.6 / 13.5, 4.0 MB 12.6 / 11.9, 7.4 MB 15.3 / 13.2, 14.7 MB 21.5 / 18.1, 64 requests
-// and two chunks on 2048 tokens (7 MB) 25.5 / 24.7, 256 requests 83.1 / 79.5.
-constexpr int kWriteThroughParts = 640;   // 2.6 MB
+// Launches with more split results than kWriteThroughParts write them through, those with decode items
+// (whose work items are short and end a launch, acknowledgement included) and two workgroups on some CU
+// only beyond kWriteThroughMixed.  us per layer, flushed / written through, as steps that follow each other and
+// (in brackets) with a read of 512 MB between them:
+//   no decode items: 800 results 9.7 / 9.2 (10.4 / 9.9), 819 12.95 / 12.3 (13.9 / 14.5), 900 11.3 / 11.0 (12.0 / 11.9),
+//     1050 10.4 / 9.7 (11.1 / 10.4), 1350 12.6 / 12.0 (13.6 / 13.3), 2000 18.3 / 16.6 (20.4 / 19.3), eight chunks on 832
+//     tokens 20.8 / 17.8 (22.2 / 19.5), on 2048 24.9 / 24.1 (26.5 / 26.4);
+//   decode items, at most 256 workgroups: 714 12.4 / 12.0 (13.4 / 13.2), 1039 13.2 / 12.5 (14.4 / 13.8);
+//   decode items, more workgroups: 707 11.4 / 11.9 (12.4 / 12.9), 774 12.2 / 12.5 (12.2 / 12.7), 876 12.3 / 12.7 (13.1 / 13.4),
+//     970 11.2 / 10.9 (12.4 / 12.7), 1071 10.3 / 9.8 (11.1 / 11.9), 1073 11.5 / 11.6 (12.6 / 13.4), 1172 14.3 / 15.4 (15.1 / 15.8);
+//     1377 12.4 / 11.8 (13.6 / 13.7), 1608 13.8 / 12.8 (14.8 / 14.5), 64 requests and two chunks on 2048 tokens (1791)
+//     24.4 / 23.6 (24.3 / 23.7).
+constexpr int kWriteThroughParts = 640;    // 2.6 MB
+constexpr int kWriteThroughMixed = 1280;   // 5.3 MB
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s);       // work items, then merge
 // Split-result buffers in static device memory of the current device (kStaticMaxPartials
 // entries, shared by every call on that device).  The first call on a device looks the address

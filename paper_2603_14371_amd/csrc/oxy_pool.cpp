@@ -123,6 +123,7 @@ struct oxy_batch {
   int32_t n_launch = 0;   // records rounded up to a multiple of 64 with padding records: the grid
   int32_t n_fresh = 0;    // blocks of items whose own-phase tiles read k_new / v_new (folded append)
   int32_t off_fresh = 0;
+  bool decodes = false;           // some item has <= 2 new tokens
   bool append_foldable = false;   // every item has <= 2 new tokens or an empty own history
   // word offsets inside the descriptor
   int32_t off_slots = 0, off_work = 0, off_toks = 0, off_tables = 0, off_part_off = 0,
@@ -576,7 +577,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   std::vector<int32_t> wide_tiles;   // items whose last tokens a record of their own takes
   int32_t n_items_of_list = 0;       // items; records from here on are second halves
   int32_t tbl_words = 0;
-  bool foldable = !append_only;
+  bool foldable = !append_only, decodes = false;
   if (!append_only) {
     hdr.reserve(1024 * kHdr);
     toks.reserve(2 * n_tokens);
@@ -736,6 +737,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       const OwnCut cut = own_cut(pl);
       const int32_t n_new = cut.n_new, step_tok = cut.tile, split = cut.split;
       int32_t path = cut.streams ? (oxy::PATH_STREAM | oxy::kPathAppends) : oxy::PATH_TILE;
+      decodes |= cut.streams;
       if (cut.streams && once) path |= oxy::kPathOnce;
       if (cut.fresh) {
         path |= oxy::kPathFresh | (pl.tok0 << oxy::kPathRowShift);
@@ -934,6 +936,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
   b->n_tokens = (int32_t)n_tokens;
   b->n_work = n_work - (int32_t)wide_tiles.size();
   b->n_partials = (int32_t)n_partials;
+  b->decodes = decodes;
   b->append_foldable = foldable;
   // Sections in the order work | slots | part_off | n_parts | fresh runs | token lists | tables: the block
   // tables, whose size changes whenever a stream takes a new block, come last, so that the
@@ -1061,7 +1064,10 @@ int32_t oxy_stream_append(oxy_pool* p, const oxy_batch* b, int32_t layer, const 
 }
 
 namespace {
-int32_t writes_through(const oxy_batch* b) { return b->n_partials > oxy::kWriteThroughParts; }
+int32_t writes_through(const oxy_batch* b) {
+  const bool mixed = b->decodes && b->n_launch > 256;
+  return b->n_partials > (mixed ? oxy::kWriteThroughMixed : oxy::kWriteThroughParts);
+}
 
 oxy::AttnArgs attn_args(const oxy_pool* p, const oxy_batch* b, int32_t layer, const void* q, void* out,
                         float* lse, float scale) {

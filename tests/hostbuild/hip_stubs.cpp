@@ -16,6 +16,8 @@ extern "C" void oxy_stub_fail_next(int skip, int k) { g_fail_skip = skip, g_fail
 extern "C" long oxy_stub_calls() { return g_calls; }
 static long g_gathers = 0;
 extern "C" long oxy_stub_gathers() { return g_gathers; }
+static long g_write_through = -1;   // of the last attention launch
+extern "C" long oxy_stub_write_through() { return g_write_through; }
 
 static hipError_t outcome() {
   ++g_calls;
@@ -133,6 +135,7 @@ hipError_t launch_gather_inline(const void*, const GatherRuns& runs, int32_t n_r
 }
 // the work items load whole eight-word parts of their records
 static hipError_t attention_outcome(const AttnArgs& a) {
+  g_write_through = a.write_through;
   return (uintptr_t)a.work % (4 * kWorkWords) ? hipErrorInvalidValue : outcome();
 }
 hipError_t launch_attention(const AttnArgs& a, hipStream_t) { return attention_outcome(a); }

@@ -14,6 +14,7 @@
 //   8 flags n_items (sid n_new)* expect_status n_slots slot*       batch_build (+ one step, destroy)
 //   9 skip k                                                       after `skip` device calls, k fail
 //  11 n slot* max_launches                                        gather_kv
+//  12 expect_write_through                                       of the last attention launch
 //  10 nb ref* nfree free* ns (sid pid kind len nblk blk*)* np (pid len nblk sealed nstreams blk*)*
 #include "../../include/oxy.h"
 
@@ -23,6 +24,7 @@
 
 extern "C" void oxy_stub_fail_next(int skip, int k);
 extern "C" long oxy_stub_gathers();
+extern "C" long oxy_stub_write_through();
 
 static FILE* g_in;
 static long g_line = 0;
@@ -223,6 +225,11 @@ int main(int argc, char** argv) {
                 "gathered row %ld", i);
         const long most = need(), launches = oxy_stub_gathers() - before;
         CHECK(launches <= most, "gather_kv of %ld slots: %ld launches > %ld", n, launches, most);
+        break;
+      }
+      case 12: {
+        const long exp = need();
+        CHECK(oxy_stub_write_through() == exp, "write_through %ld != %ld", oxy_stub_write_through(), exp);
         break;
       }
       default:

@@ -188,3 +188,29 @@ def test_read_back_covers_every_row_once_in_few_launches(replay_exe, tmp_path):
     for slots in _slot_lists(np.random.default_rng(11), nb * 16):
         script.append([11, len(slots)] + slots + [-(-len(slots) // 512)])
     _run(replay_exe, tmp_path, script)
+
+
+@pytest.mark.parametrize("prefix_len,chunks,requests,through", [
+    (832, 1, 0, 0), (832, 2, 0, 1),                          # 450 and 900 split results, no decode items
+    (832, 1, 20, 0), (832, 1, 30, 0), (832, 2, 8, 0),         # 610, 690, 964; more than 256 workgroups
+    (2048, 1, 15, 0), (2048, 1, 20, 1), (2048, 2, 4, 1),      # 635, 680 and 1036; fewer
+    (832, 3, 0, 1), (832, 2, 47, 0), (832, 2, 48, 1),         # 1350; 1276 and 1284, decode items among them
+])
+def test_which_launches_write_their_split_results_through(replay_exe, tmp_path, prefix_len, chunks, requests,
+                                                          through):
+    nb = 512
+    model = PoolModel(nb, 16, 2, list(range(nb)))
+    script = [[0, nb, 2, 1, 512, 0], [1, model.prefix_create()]]
+    for layer in range(2):
+        model.prefix_append(0, layer, prefix_len, 0)
+        script.append([2, 0, layer, prefix_len, 0, 0])
+    items = []
+    for kind, n_new, count in ((0, 50, chunks), (1, 1, requests)):
+        for _ in range(count):
+            sid = model.stream_create(0, kind)
+            script.append([5, 0, kind, 0, sid])
+            items.append((sid, n_new))
+    slots = model.batch_build(items)
+    script.append([8, 0, len(items)] + [x for it in items for x in it] + [0, len(slots)] + slots)
+    script.append([12, through])
+    _run(replay_exe, tmp_path, script)
