@@ -520,13 +520,14 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
 // kOwnPages: a decode item's own pages, read by this work item alone, which also writes the item's
 // new rows when the append is folded in.  Otherwise the pages are a prefix's or a multi-token item's,
 // and other work items read them too.  kOnce: non-temporal page loads, for own pages that will have
-// left the L2 by the next step and are not to push shared pages out.
+// left the Infinity Cache by the next step and are not to push others out (see kOnceBytes).
 //
-// kSteps: 32-key steps of a round that are loaded, 4, or 2 for a split of at most 64 keys (the last one of
-// an 832-token prefix, a short history's): wavefronts 2 and 3 load no K then, and all of them half of V.
-// (With every step loaded, the pages past the end once more, such an item took as long as one of 128
-// keys and kept the loads of its CU's other workgroup waiting: 18 layers of eight requests and a chunk
-// 185.3 us, now 182.1; others +-0.5 %.)
+// kSteps: 32-key steps of a round that are loaded, 4, or 2 for a split of at most 64 keys of a prefix or of a
+// multi-token item (the last one of an 832-token prefix, a short observation's): wavefronts 2 and 3 load no
+// K then, and all of them half of V.  A decode item's own pages always take 4.  (With every step loaded, the
+// pages past the end once more, such an item took as long as one of 128 keys and kept the loads of its
+// CU's other workgroup waiting: work-item launch of eight requests and a chunk 7.3 us, now 7.0, of six
+// requests with 13 new tokens 10.2 / 9.6; others +-0.5 %.)
 template <int G, bool kOwnPages, bool kOnce, int kSteps>
 __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
   int tid = threadIdx.x;

@@ -721,11 +721,14 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     }
     // A decode loop reads the same pages in every step, so own pages are loaded past the caches
     // (non-temporal, see kOnce in the kernels) only where the step's pages in all layers are more than
-    // half of the 256 MB that the Infinity Cache holds, the rest left to whatever else a program runs
-    // between two steps.  us a step of 18 layers, non-temporal / plain: 3 requests on one observation
-    // (26 MB) 161.5 / 148.6, 8 on four (116 MB) 170.4 / 158.4, 16 on one (155 MB) 207.3 / 185.3 and with
-    // a chunk 259.1 / 217.7; beyond the cache 16 on four (340 MB) 218.4 / 223.5, 32 on one (601 MB) 245.1
-    // / 271.9; two pools of 158 MB used in turn 189.3 / 197.1.
+    // half of the 256 MB that the Infinity Cache holds.  us per layer, non-temporal / plain, as steps that
+    // follow each other and (in brackets) with 512 MB of other memory read between them, as a model's
+    // weights are: one request 7.4 / 7.0 (7.8 / 7.8), 3 on one observation (43 MB) 8.5 / 7.6 (8.7 / 8.6), 12 (70 MB)
+    // 8.2 / 7.4 (8.4 / 8.2), 4 with 1000 tokens (90 MB) 10.7 / 9.2 (10.9 / 10.75), 8 on two (104 MB) 8.8 / 7.9 (9.05 /
+    // 8.95); above the limit 16 on one (148 MB) 10.8 / 9.6 (11.0 / 10.9), 40 and a chunk (320 MB) 12.5 / 12.9 (12.45 /
+    // 12.9), and 32 on one (601 MB) 245 / 272 a step of 18 layers.  Where 512 MB are read before every single
+    // launch plain loads lose up to 0.55 us of such a launch below the limit too (17 MB 6.8 / 6.7, 43 MB 6.7 /
+    // 6.9, 70 MB 6.4 / 6.8, 90 MB 8.8 / 9.4).
     int64_t live_tok = 0;
     for (const Group& g : groups) live_tok += g.px->len;
     for (const Plan& pl : plan) live_tok += pl.new_len;
