@@ -86,7 +86,8 @@ struct AttnArgs {
 };
 // Launches with more split results than kWriteThroughParts write them through, those with decode items
 // (whose work items are short and end a launch, acknowledgement included) and two workgroups on some CU
-// only beyond kWriteThroughMixed.  us per layer, flushed / written through, as steps that follow each other and
+// only beyond kWriteThroughMixed.  (What gains is that items still run when the first results leave; the rule
+// goes by counts and does not look at how long they do.)  us per layer, flushed / written through, as steps that follow each other and
 // (in brackets) with a read of 512 MB between them:
 //   no decode items: 800 results 9.7 / 9.2 (10.4 / 9.9), 819 12.95 / 12.3 (13.9 / 14.5), 900 11.3 / 11.0 (12.0 / 11.9),
 //     1050 10.4 / 9.7 (11.1 / 10.4), 1350 12.6 / 12.0 (13.6 / 13.3), 2000 18.3 / 16.6 (20.4 / 19.3), eight chunks on 832
