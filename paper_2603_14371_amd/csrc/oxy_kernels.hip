@@ -33,6 +33,7 @@
 
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 namespace oxy {
 
@@ -87,6 +88,20 @@ __device__ __forceinline__ float row_sum4(float x) {
   const uint32_t v = __float_as_uint(y);
   const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
   return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// x of the lane N places on in the row of 16 lanes
+template <int N>
+__device__ __forceinline__ float dpp_row_ror(const float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + N, 0xf, 0xf, false));
+}
+// f(0), f(1), .. f(N - 1) with the index as a constant
+template <int N, class F, int... I>
+__device__ __forceinline__ void static_for_each(const F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(const F& f) {
+  static_for_each<N>(f, std::make_integer_sequence<int, N>());
 }
 // ------------------------------------------------------------------------------------------
 // page layout (see oxy.h)
@@ -1087,86 +1102,116 @@ __global__ __attribute__((aligned(4096))) __launch_bounds__(256, 2) void attn_ke
 }
 
 // ------------------------------------------------------------------------------------------
-// merge of a query token's partials (log-sum-exp rule).  One workgroup per token; a thread owns
-// eight consecutive output dims of one head and has every load of the first sixteen partials in
-// flight at once.
+// merge of a query token's partials (log-sum-exp rule).  One wavefront per token and head, which has
+// every load of the first sixteen partials in flight at once.
 // (A merge fused into attn_kernel by "last arriver merges" was built twice and measured: with
 // device-scope fences every workgroup pays a whole-L2 write-back + invalidate (165 us per
 // launch); with scoped write-through stores and no fences it is correct and fence-free, but the
 // tile workgroups finish last and then merge their eight tokens serially (53 us).  Hence its own
 // kernel.)
 // ------------------------------------------------------------------------------------------
-constexpr int kMergeAhead = 16;   // partials whose loads are all issued before anything is used
+constexpr int kMergeAhead = 16;       // partials whose loads are all issued before anything is used
+constexpr int kMergeBlocks = 2;       // workgroups of a token, four heads each
+constexpr int kRowBcast0 = 0x150;     // DPP: all lanes of each 16 get the value of lane 0 (+ u: lane u)
 
-// One workgroup per token; thread t owns head t/32 and eight consecutive output dims.  n_parts and
-// part_off are preloaded arguments (see attn_kernel).
+// largest value / sum of a row of 16 lanes, in all of them
+__device__ __forceinline__ float lanes16_max(float x) {
+  x = fmaxf(x, dpp_row_ror<8>(x));
+  x = fmaxf(x, dpp_row_ror<4>(x));
+  x = fmaxf(x, dpp_row_ror<2>(x));
+  return fmaxf(x, dpp_row_ror<1>(x));
+}
+__device__ __forceinline__ float lanes16_sum(float x) {
+  x += dpp_row_ror<8>(x);
+  x += dpp_row_ror<4>(x);
+  x += dpp_row_ror<2>(x);
+  return x + dpp_row_ror<1>(x);
+}
+
+// Bound by the round trip of its loads, by their bytes where tokens are many (400 tokens of 9 split results:
+// 14.7 MB).  Lane 16q + i owns dims 64q + 4i..+3 of the output, and, for the weights, split result i of every
+// sixteen in the 64 dims q, whose exponent it applies: sixteen weights take one exponential per wavefront, and a
+// weight reaches its 16 lanes by a DPP broadcast.  (With a workgroup per token, eight dims per thread and every
+// weight computed by every thread, the sums of nine split results alone took 0.7 us of a wavefront.  Layer of
+// a decode step 6.80 -> 6.36 us, of 50 queries + one request 8.37 -> 7.88, of three requests 7.37 -> 6.77, of 78 queries
+// with up to 15 split results 12.8 -> 11.9, of 64 requests and two chunks on 2048 tokens 23.6 -> 23.1.)
+// kAhead: split results whose loads are issued before anything is used, np rounded up to a multiple of four
+// or the most: an instance for each, so that the first wait is for (m, l) only (loads under conditions are
+// all waited for where the conditions meet; three requests 6.96 us a layer, now 6.77).
+template <int kAhead>
+__device__ __forceinline__ void merge_head(const AttnArgs& a, const size_t base, const int np, const int tok,
+                                           const int h, const int lane) {
+  const int i = lane & 15, q = lane >> 4;
+  // wave-uniform; a lane adds 32 bits to them
+  const char* ml = (const char*)(a.part_ml + (base * kHeads + h) * 4);
+  const char* acc = (const char*)(a.part_acc + (base * kHeads + h) * kDim);
+  constexpr uint32_t kMlStride = kHeads * 4 * sizeof(float), kAccStride = kHeads * kDim * sizeof(uint16_t);
+  const float ninf = -__builtin_inff();
+  u32x2 x[kAhead];
+  // (m, l, exponents of the 64-dim parts, -) of this lane's split result; past the end the last one's
+  auto load_ml = [&](const int p0) {
+    return *(const f32x4*)(ml + (uint32_t)min(p0 + i, np - 1) * kMlStride);
+  };
+  auto load_x = [&](const int p0) {
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      x[u] = *(const u32x2*)(acc + (size_t)min(p0 + u, np - 1) * kAccStride + (uint32_t)lane * 8u);
+  };
+  f32x4 w = load_ml(0);
+  load_x(0);
+  float big = w[0];
+  if constexpr (kAhead == kMergeAhead)
+    for (int p0 = kAhead; p0 < np; p0 += kAhead)
+      big = fmaxf(big, load_ml(p0)[0]);
+  big = lanes16_max(big);
+  float total = 0.f, o[4] = {0.f, 0.f, 0.f, 0.f};
+  auto add = [&](const int p0) {
+    const bool live = p0 + i < np && w[0] != ninf;
+    const float wgt = live ? fast_exp2(w[0] - big) : 0.f;
+    total += wgt * (live ? w[1] : 0.f);
+    const int ex = (int32_t)(__float_as_uint(w[2]) << (24 - 8 * q)) >> 24;   // signed byte q
+    const float ws = __builtin_amdgcn_ldexpf(wgt, ex - 14);
+    static_for<kAhead>([&](auto u) {
+      const float wu = __uint_as_float(
+          __builtin_amdgcn_update_dpp(0, __float_as_uint(ws), kRowBcast0 + u.value, 0xf, 0xf, false));
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        float lo, hi;
+        unpack_f16(x[u.value][k], lo, hi);
+        o[2 * k] = __builtin_fmaf(wu, lo, o[2 * k]);
+        o[2 * k + 1] = __builtin_fmaf(wu, hi, o[2 * k + 1]);
+      }
+    });
+  };
+  add(0);
+  if constexpr (kAhead == kMergeAhead)
+    for (int p0 = kAhead; p0 < np; p0 += kAhead) {
+      w = load_ml(p0);
+      load_x(p0);
+      add(p0);
+    }
+  total = lanes16_sum(total);
+  const float inv = 1.f / total;
+  const u32x2 packed = {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv)};
+  *(u32x2*)((uint16_t*)a.out + ((size_t)tok * kHeads + h) * kDim + 4 * lane) = packed;
+  if (a.lse && lane == 0)
+    a.lse[(size_t)tok * kHeads + h] = (big + __builtin_amdgcn_logf(total)) * 0.6931471805599453f;
+}
+// n_parts and part_off are preloaded arguments (see attn_kernel).
 __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_t* part_off,
-                                            const AttnArgs& a, const int tok) {
-  const int t = threadIdx.x;
-  const int h = t >> 5, d0 = (t & 31) * 8;
-  const int ex_shift = 24 - 8 * (d0 >> 6);
+                                            const AttnArgs& a, const int block) {
+  const int tok = block / kMergeBlocks, lane = threadIdx.x & 63;
+  const int h = 4 * (block % kMergeBlocks) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int np = ((DescPtr)n_parts)[tok];
   const size_t base = (size_t)((DescPtr)part_off)[tok];
-  const float* ml = a.part_ml + (base * kHeads + h) * 4;
-  const uint16_t* src = a.part_acc + (base * kHeads + h) * kDim + d0;
-  const size_t stride = (size_t)kHeads * kDim;
-  const float ninf = -__builtin_inff();
-  // one round trip for the common case: every load of the first 16 partials is in flight at once
-  u32x4 x[kMergeAhead];
-  f32x4 w[kMergeAhead];
-#pragma unroll
-  for (int u0 = 0; u0 < kMergeAhead; u0 += 4)
-    if (u0 < np) {   // wave-uniform; everything in flight is waited for below in any case
-#pragma unroll
-      for (int u = u0; u < u0 + 4; ++u) {
-        const int p = u < np ? u : 0;
-        x[u] = *(const u32x4*)(src + (size_t)p * stride);
-        w[u] = *(const f32x4*)(ml + (size_t)p * kHeads * 4);
-      }
-    }
-  float big = ninf;
-#pragma unroll
-  for (int u = 0; u < kMergeAhead; ++u) big = fmaxf(big, u < np ? w[u][0] : ninf);
-  for (int p = kMergeAhead; p < np; ++p) big = fmaxf(big, ml[(size_t)p * kHeads * 4]);
-  float total = 0.f;
-  float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  auto weight = [&](const f32x4& mls, const bool live) {   // mls = (m, l, exponents of the 64-dim parts, -)
-    return !live || mls[0] == ninf ? 0.f : fast_exp2(mls[0] - big);
-  };
-  auto add = [&](const float wgt, const f32x4& mls, const u32x4& v) {
-    total = __builtin_fmaf(wgt, mls[1], total);
-    const int ex = (int32_t)(__float_as_uint(mls[2]) << ex_shift) >> 24;   // signed byte d0 / 64
-    const float ws = __builtin_amdgcn_ldexpf(wgt, ex - 14);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float lo, hi;
-      unpack_f16(v[i], lo, hi);
-      o[2 * i] = __builtin_fmaf(ws, lo, o[2 * i]);
-      o[2 * i + 1] = __builtin_fmaf(ws, hi, o[2 * i + 1]);
-    }
-  };
-  // Four at a time, under one condition: a wavefront has its SIMD to itself here, and one after the
-  // other every split result waited for its own exponential (nine took 0.6 us of a 1.9 us merge).
-  // Past the end the first one is added once more, with weight zero.
-#pragma unroll
-  for (int u0 = 0; u0 < kMergeAhead; u0 += 4)
-    if (u0 < np) {
-      float wgt[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) wgt[i] = weight(w[u0 + i], u0 + i < np);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) add(wgt[i], w[u0 + i], x[u0 + i]);
-    }
-  for (int p = kMergeAhead; p < np; ++p) {
-    const f32x4 mls = *(const f32x4*)(ml + (size_t)p * kHeads * 4);
-    add(weight(mls, true), mls, *(const u32x4*)(src + (size_t)p * stride));
-  }
-  const float inv = 1.f / total;
-  const u32x4 packed = {pack_bf16(o[0] * inv, o[1] * inv), pack_bf16(o[2] * inv, o[3] * inv),
-                        pack_bf16(o[4] * inv, o[5] * inv), pack_bf16(o[6] * inv, o[7] * inv)};
-  *(u32x4*)((uint16_t*)a.out + ((size_t)tok * kHeads + h) * kDim + d0) = packed;
-  if (a.lse && (t & 31) == 0)
-    a.lse[(size_t)tok * kHeads + h] = (big + __builtin_amdgcn_logf(total)) * 0.6931471805599453f;
+  if (np <= 4)
+    merge_head<4>(a, base, np, tok, h, lane);
+  else if (np <= 8)
+    merge_head<8>(a, base, np, tok, h, lane);
+  else if (np <= 12)
+    merge_head<12>(a, base, np, tok, h, lane);
+  else
+    merge_head<kMergeAhead>(a, base, np, tok, h, lane);
 }
 
 __global__ __launch_bounds__(256) void merge_kernel(const int32_t* n_parts, const int32_t* part_off,
@@ -1181,7 +1226,7 @@ __global__ __launch_bounds__(256) void merge_append_kernel(const int32_t* n_part
                                                            const int32_t* part_off, const AttnArgs a,
                                                            const AppendArgs nx) {
   __shared__ PageLds sm;
-  const int n_merge = a.n_q, i = (int)blockIdx.x - n_merge;
+  const int n_merge = kMergeBlocks * a.n_q, i = (int)blockIdx.x - n_merge;
   if (i < 0) {
     merge_block(n_parts, part_off, a, blockIdx.x);
     return;
@@ -1212,7 +1257,7 @@ hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStr
   if (a.n_q <= 0) return hipErrorInvalidValue;
   const bool timed = start || stop;
   if (next && next->n_blocks > 0) {
-    const dim3 grid(a.n_q + next->n_blocks);
+    const dim3 grid(kMergeBlocks * a.n_q + next->n_blocks);
     if (timed)
       hipExtLaunchKernelGGL(merge_append_kernel, grid, dim3(256), 0, s, start, stop, 0, a.n_parts,
                             a.part_off, a, *next);
@@ -1220,10 +1265,10 @@ hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStr
       merge_append_kernel<<<grid, 256, 0, s>>>(a.n_parts, a.part_off, a, *next);
   } else {
     if (timed)
-      hipExtLaunchKernelGGL(merge_kernel, dim3(a.n_q), dim3(256), 0, s, start, stop, 0, a.n_parts,
+      hipExtLaunchKernelGGL(merge_kernel, dim3(kMergeBlocks * a.n_q), dim3(256), 0, s, start, stop, 0, a.n_parts,
                             a.part_off, a);
     else
-      merge_kernel<<<a.n_q, 256, 0, s>>>(a.n_parts, a.part_off, a);
+      merge_kernel<<<kMergeBlocks * a.n_q, 256, 0, s>>>(a.n_parts, a.part_off, a);
   }
   return hipGetLastError();
 }
