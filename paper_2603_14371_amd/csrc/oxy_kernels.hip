@@ -1111,7 +1111,10 @@ __global__ __attribute__((aligned(4096))) __launch_bounds__(256, 2) void attn_ke
 // kernel.)
 // ------------------------------------------------------------------------------------------
 constexpr int kMergeAhead = 16;       // partials whose loads are all issued before anything is used
-constexpr int kMergeBlocks = 2;       // workgroups of a token, four heads each
+// Heads, and wavefronts, of a merge workgroup: 4, or all 8 where a launch has more tokens than the GPU has CUs.
+// us per layer, 4 / 8: one request 6.70 / 6.83, 50 queries + one request 8.12 / 8.34, 78 queries 13.1 / 13.45, 164 22.8 /
+// 22.7, 356 72.7 / 72.7, 400 17.8 / 17.3.
+constexpr int kMergeManyTokens = 256;
 constexpr int kRowBcast0 = 0x150;     // DPP: all lanes of each 16 get the value of lane 0 (+ u: lane u)
 
 // largest value / sum of a row of 16 lanes, in all of them
@@ -1135,6 +1138,8 @@ __device__ __forceinline__ float lanes16_sum(float x) {
 // weight computed by every thread, the sums of nine split results alone took 0.7 us of a wavefront.  Layer of
 // a decode step 6.80 -> 6.36 us, of 50 queries + one request 8.37 -> 7.88, of three requests 7.37 -> 6.77, of 78 queries
 // with up to 15 split results 12.8 -> 11.9, of 64 requests and two chunks on 2048 tokens 23.6 -> 23.1.)
+// They are read here and never again, hence the non-temporal hint (50 queries + one request 8.22 -> 8.12 us,
+// 64 requests and two chunks 23.2 -> 22.8; on (m, l) too: 2 % slower).
 // kAhead: split results whose loads are issued before anything is used, np rounded up to a multiple of four
 // or the most: an instance for each, so that the first wait is for (m, l) only (loads under conditions are
 // all waited for where the conditions meet; three requests 6.96 us a layer, now 6.77).
@@ -1155,7 +1160,7 @@ __device__ __forceinline__ void merge_head(const AttnArgs& a, const size_t base,
   auto load_x = [&](const int p0) {
 #pragma unroll
     for (int u = 0; u < kAhead; ++u)
-      x[u] = *(const u32x2*)(acc + (size_t)min(p0 + u, np - 1) * kAccStride + (uint32_t)lane * 8u);
+      x[u] = __builtin_nontemporal_load((const u32x2*)(acc + (size_t)min(p0 + u, np - 1) * kAccStride + (uint32_t)lane * 8u));
   };
   f32x4 w = load_ml(0);
   load_x(0);
@@ -1198,10 +1203,12 @@ __device__ __forceinline__ void merge_head(const AttnArgs& a, const size_t base,
     a.lse[(size_t)tok * kHeads + h] = (big + __builtin_amdgcn_logf(total)) * 0.6931471805599453f;
 }
 // n_parts and part_off are preloaded arguments (see attn_kernel).
+template <int kBlockHeads>
 __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_t* part_off,
                                             const AttnArgs& a, const int block) {
-  const int tok = block / kMergeBlocks, lane = threadIdx.x & 63;
-  const int h = 4 * (block % kMergeBlocks) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kBlocks = kHeads / kBlockHeads;
+  const int tok = block / kBlocks, lane = threadIdx.x & 63;
+  const int h = kBlockHeads * (block % kBlocks) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int np = ((DescPtr)n_parts)[tok];
   const size_t base = (size_t)((DescPtr)part_off)[tok];
   if (np <= 4)
@@ -1214,23 +1221,28 @@ __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_
     merge_head<kMergeAhead>(a, base, np, tok, h, lane);
 }
 
-__global__ __launch_bounds__(256) void merge_kernel(const int32_t* n_parts, const int32_t* part_off,
-                                                    const AttnArgs a) {
-  merge_block(n_parts, part_off, a, blockIdx.x);
+template <int kBlockHeads>
+__global__ __launch_bounds__(64 * kBlockHeads) void merge_kernel(const int32_t* n_parts,
+                                                                 const int32_t* part_off,
+                                                                 const AttnArgs a) {
+  merge_block<kBlockHeads>(n_parts, part_off, a, blockIdx.x);
 }
 
 // merge of one layer and, in the same launch, an append that touches other memory than the
 // merge: the next layer's new rows (cross-layer fusion), or this layer's rows of the items whose
-// tiles read their keys from k_new / v_new (nx.runs names them, a block of a table each)
-__global__ __launch_bounds__(256) void merge_append_kernel(const int32_t* n_parts,
-                                                           const int32_t* part_off, const AttnArgs a,
-                                                           const AppendArgs nx) {
+// tiles read their keys from k_new / v_new (nx.runs names them, a block of a table each).  256 threads append.
+template <int kBlockHeads>
+__global__ __launch_bounds__(64 * kBlockHeads) void merge_append_kernel(const int32_t* n_parts,
+                                                                        const int32_t* part_off,
+                                                                        const AttnArgs a,
+                                                                        const AppendArgs nx) {
   __shared__ PageLds sm;
-  const int n_merge = kMergeBlocks * a.n_q, i = (int)blockIdx.x - n_merge;
+  const int n_merge = kHeads / kBlockHeads * a.n_q, i = (int)blockIdx.x - n_merge;
   if (i < 0) {
-    merge_block(n_parts, part_off, a, blockIdx.x);
+    merge_block<kBlockHeads>(n_parts, part_off, a, blockIdx.x);
     return;
   }
+  if (threadIdx.x >= 256) return;
   const int run = nx.runs ? nx.runs[i] : i << 4;
   const int tok = run >> 4, slot = nx.d_slots[tok];
   const uint16_t* k_row = (const uint16_t*)nx.k_new + (size_t)tok * kDim;
@@ -1252,24 +1264,31 @@ hipError_t launch_attention_work(const AttnArgs& a, hipStream_t s, hipEvent_t st
   return hipGetLastError();
 }
 
+namespace {
+template <int kBlockHeads>
+void launch_merge(const AttnArgs& a, const AppendArgs* next, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  const bool timed = start || stop, appends = next && next->n_blocks > 0;
+  const dim3 grid(kHeads / kBlockHeads * a.n_q + (appends ? next->n_blocks : 0)), block(64 * kBlockHeads);
+  if (appends && timed)
+    hipExtLaunchKernelGGL(merge_append_kernel<kBlockHeads>, grid, block, 0, s, start, stop, 0, a.n_parts,
+                          a.part_off, a, *next);
+  else if (appends)
+    merge_append_kernel<kBlockHeads><<<grid, block, 0, s>>>(a.n_parts, a.part_off, a, *next);
+  else if (timed)
+    hipExtLaunchKernelGGL(merge_kernel<kBlockHeads>, grid, block, 0, s, start, stop, 0, a.n_parts,
+                          a.part_off, a);
+  else
+    merge_kernel<kBlockHeads><<<grid, block, 0, s>>>(a.n_parts, a.part_off, a);
+}
+}  // namespace
+
 hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStream_t s,
                                hipEvent_t start, hipEvent_t stop) {
   if (a.n_q <= 0) return hipErrorInvalidValue;
-  const bool timed = start || stop;
-  if (next && next->n_blocks > 0) {
-    const dim3 grid(kMergeBlocks * a.n_q + next->n_blocks);
-    if (timed)
-      hipExtLaunchKernelGGL(merge_append_kernel, grid, dim3(256), 0, s, start, stop, 0, a.n_parts,
-                            a.part_off, a, *next);
-    else
-      merge_append_kernel<<<grid, 256, 0, s>>>(a.n_parts, a.part_off, a, *next);
-  } else {
-    if (timed)
-      hipExtLaunchKernelGGL(merge_kernel, dim3(kMergeBlocks * a.n_q), dim3(256), 0, s, start, stop, 0, a.n_parts,
-                            a.part_off, a);
-    else
-      merge_kernel<<<kMergeBlocks * a.n_q, 256, 0, s>>>(a.n_parts, a.part_off, a);
-  }
+  if (a.n_q > kMergeManyTokens)
+    launch_merge<kHeads>(a, next, s, start, stop);
+  else
+    launch_merge<kHeads / 2>(a, next, s, start, stop);
   return hipGetLastError();
 }
 
