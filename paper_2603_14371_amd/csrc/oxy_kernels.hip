@@ -465,11 +465,35 @@ __device__ __forceinline__ void store_piece_pair(const AttnArgs& args, u32x4* ds
     dst[4] = b;
   }
 }
+// Eight rows' 128 bytes each at (split result, offset), for both tokens of a group: see store_part.  Buffer
+// stores take the cache bits of the written-through form as an argument.
+__device__ __forceinline__ void store_lines(const AttnArgs& args, const int offset, const int slot_a,
+                                            const u32x4 a, const bool live_a, const int slot_b,
+                                            const u32x4 b, const bool live_b) {
+  constexpr int kPartBytes = kHeads * kDim * (int)sizeof(uint16_t), kFlags = 0x00027000;
+  constexpr int kThrough = 1 | 16;   // sc0, sc1
+  // a token that is not there has a buffer of no bytes: its rows are dropped
+  const auto part_a = __builtin_amdgcn_make_buffer_rsrc((char*)args.part_acc + (size_t)slot_a * kPartBytes, 0,
+                                                        live_a ? kPartBytes : 0, kFlags);
+  const auto part_b = __builtin_amdgcn_make_buffer_rsrc((char*)args.part_acc + (size_t)slot_b * kPartBytes, 0,
+                                                        live_b ? kPartBytes : 0, kFlags);
+  if (args.write_through) {
+    __builtin_amdgcn_raw_buffer_store_b128(a, part_a, offset, 0, kThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(b, part_b, offset, 0, kThrough);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b128(a, part_a, offset, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b128(b, part_b, offset, 0, 0);
+  }
+}
+constexpr int kRowRor8 = 0x128;   // DPP: lane n of each 16 gets lane n^8's value
 // One wavefront's 64 dims of a group's split result.  A split result leaves as (m, l, four
 // exponents) and acc * 2^(14 - exponent) in fp16: half the bytes of fp32, with the exponent of the
 // largest value per row and 64 dims, so that the rounding does not depend on the magnitude of the
-// values.  acc[c][e] = dim 16g + 4e + c of the 64: a lane's sixteen values are consecutive.  slot:
+// values.  kLines: whole lines, for items of eight tokens, whose launches write the most (us per layer, pieces /
+// lines: eight chunks on 2048 tokens 24.4 / 23.6, six on 1500 22.1 / 21.6, four and 32 requests on 1024 17.9 / 17.1,
+// eight on 832 17.36 / 17.32; narrower items are up to 1 % slower with it).  acc[c][e] = dim 16g + 4e + c of the 64: a lane's sixteen values are consecutive.  slot:
 // split result of this lane's token.
+template <bool kLines>
 __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi, const int slot,
                                            const f32x4 (&acc)[4], const int group, const int wv,
                                            const int lane) {
@@ -491,6 +515,23 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
   for (int e = 0; e < 4; ++e) {
     o[e >> 1][2 * (e & 1)] = pack_f16(acc[0][e] * up, acc[1][e] * up);
     o[e >> 1][2 * (e & 1) + 1] = pack_f16(acc[2][e] * up, acc[3][e] * up);
+  }
+  if constexpr (kLines) {
+    // Lane g of row n holds 16-byte pieces 2g and 2g+1 of the row's eight.  Rows n and n^8 (the group's two
+    // tokens) trade one each, so that a store takes whole lines: eight lanes the 128 bytes of one row, a
+    // token's eight rows at once.
+    u32x4 first = o[0], second = o[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      first[i] = __builtin_amdgcn_update_dpp(o[0][i], o[1][i], kRowRor8, 0xf, 0xc, false);
+      second[i] = __builtin_amdgcn_update_dpp(o[1][i], o[0][i], kRowRor8, 0xf, 0x3, false);
+    }
+    const int offset = (n & 7) * (kDim * 2) + 128 * wv + 32 * g + 16 * (n >> 3);
+    store_lines(a, offset, __builtin_amdgcn_readlane(slot, 0), first, 2 * group < wi.n_tok,
+                __builtin_amdgcn_readlane(slot, 8), second, 2 * group + 1 < wi.n_tok);
+    if (g == 0 && 2 * group + (n >> 3) < wi.n_tok)
+      ((int8_t*)(a.part_ml + ((size_t)slot * kHeads + (n & 7)) * 4 + 2))[wv] = (int8_t)ex;
+    return;
   }
   // Lane g of a row holds 16-byte pieces 2g and 2g+1 of the row's eight: exchanged so that the
   // four lanes of a row store pieces 0..3 together and then 4..7, 64 contiguous bytes each time.
@@ -838,7 +879,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
           for (int s = 0; s < kSteps; ++s)
             if (G > 1 && (decltype(full)::value || s < nv)) contract(s, r);
           const int slot = sm.slot[2 * r + sub];
-          store_part(a, wi, slot, acc[r], r, wv, lane);
+          store_part<(G >= 4)>(a, wi, slot, acc[r], r, wv, lane);
           if (wv == r) {   // wave-uniform: the sums of the groups are shared out
             const f32x4 lw = *(const f32x4*)sm.ls[r][lane];
             const float total = row_sum4((lw[0] + lw[1]) + (lw[2] + lw[3]));
@@ -1027,7 +1068,7 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
     *(f32x2*)(a.part_ml + ((size_t)own_slot * kHeads + h) * 4) = (f32x2){m_own, total};
   }
 #pragma unroll
-  for (int r = 0; r < kG; ++r) store_part(a, wi, sm.slot[2 * r + sub], acc[r], r, wv, lane);
+  for (int r = 0; r < kG; ++r) store_part<(kG >= 4)>(a, wi, sm.slot[2 * r + sub], acc[r], r, wv, lane);
 }
 
 template <bool kRows>
