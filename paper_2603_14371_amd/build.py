@@ -9,10 +9,10 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liboxy.so")
 SOURCES = ["oxy_kernels.hip", "oxy_pool.cpp", "oxy_sched.cpp"]
-# packed fp32 VALU forms are switched off for device code on purpose; the first two arguments of a
-# kernel are preloaded into scalar registers (the descriptor's address, a launch's first load)
+# packed fp32 VALU forms are switched off for device code on purpose; the first eight arguments of a
+# kernel (at most 14 words, none from a struct on) are preloaded into scalar registers
 DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-                "-mllvm", "-amdgpu-kernarg-preload-count=2"]
+                "-mllvm", "-amdgpu-kernarg-preload-count=8"]
 
 
 PROBE_SRC = os.path.join(HERE, "benchaid", "probe_kernels.hip")

@@ -1156,6 +1156,13 @@ constexpr int kMergeAhead = 16;       // partials whose loads are all issued bef
 // us per layer, 4 / 8: one request 6.70 / 6.83, 50 queries + one request 8.12 / 8.34, 78 queries 13.1 / 13.45, 164 22.8 /
 // 22.7, 356 72.7 / 72.7, 400 17.8 / 17.3.
 constexpr int kMergeManyTokens = 256;
+struct MergeArgs {
+  const uint16_t* part_acc;
+  const float* part_ml;
+  void* out;
+  float* lse;
+  const int32_t *n_parts, *part_off;
+};
 constexpr int kRowBcast0 = 0x150;     // DPP: all lanes of each 16 get the value of lane 0 (+ u: lane u)
 
 // largest value / sum of a row of 16 lanes, in all of them
@@ -1185,7 +1192,7 @@ __device__ __forceinline__ float lanes16_sum(float x) {
 // or the most: an instance for each, so that the first wait is for (m, l) only (loads under conditions are
 // all waited for where the conditions meet; three requests 6.96 us a layer, now 6.77).
 template <int kAhead>
-__device__ __forceinline__ void merge_head(const AttnArgs& a, const size_t base, const int np, const int tok,
+__device__ __forceinline__ void merge_head(const MergeArgs& a, const size_t base, const int np, const int tok,
                                            const int h, const int lane) {
   const int i = lane & 15, q = lane >> 4;
   // wave-uniform; a lane adds 32 bits to them
@@ -1243,15 +1250,13 @@ __device__ __forceinline__ void merge_head(const AttnArgs& a, const size_t base,
   if (a.lse && lane == 0)
     a.lse[(size_t)tok * kHeads + h] = (big + __builtin_amdgcn_logf(total)) * 0.6931471805599453f;
 }
-// n_parts and part_off are preloaded arguments (see attn_kernel).
 template <int kBlockHeads>
-__device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_t* part_off,
-                                            const AttnArgs& a, const int block) {
+__device__ __forceinline__ void merge_block(const MergeArgs& a, const int block) {
   constexpr int kBlocks = kHeads / kBlockHeads;
   const int tok = block / kBlocks, lane = threadIdx.x & 63;
   const int h = kBlockHeads * (block % kBlocks) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int np = ((DescPtr)n_parts)[tok];
-  const size_t base = (size_t)((DescPtr)part_off)[tok];
+  const int np = ((DescPtr)a.n_parts)[tok];
+  const size_t base = (size_t)((DescPtr)a.part_off)[tok];
   if (np <= 4)
     merge_head<4>(a, base, np, tok, h, lane);
   else if (np <= 8)
@@ -1262,25 +1267,28 @@ __device__ __forceinline__ void merge_block(const int32_t* n_parts, const int32_
     merge_head<kMergeAhead>(a, base, np, tok, h, lane);
 }
 
+// Everything a merge workgroup needs comes preloaded in scalar registers (13 of the 14 there are; see build.py):
+// the argument segment is memory that every workgroup of a launch would read at once, in front of its first load.
+// us per layer with the segment / preloaded: 50 queries + one request 8.02 / 7.81, eight requests and a chunk 8.92 /
+// 8.76, three requests 6.80 / 6.65, eight chunks on 832 tokens 16.82 / 16.61, 64 requests and two chunks 22.66 / 22.40, one
+// request (two workgroups) 6.33 / 6.36, eight chunks on 2048 22.44 / 22.49.
+#define OXY_MERGE_PARAMS                                                                              \
+  const uint16_t *part_acc, const float *part_ml, void *out, float *lse, const int32_t *n_parts, \
+      const int32_t *part_off, const int32_t n_q
 template <int kBlockHeads>
-__global__ __launch_bounds__(64 * kBlockHeads) void merge_kernel(const int32_t* n_parts,
-                                                                 const int32_t* part_off,
-                                                                 const AttnArgs a) {
-  merge_block<kBlockHeads>(n_parts, part_off, a, blockIdx.x);
+__global__ __launch_bounds__(64 * kBlockHeads) void merge_kernel(OXY_MERGE_PARAMS) {
+  merge_block<kBlockHeads>({part_acc, part_ml, out, lse, n_parts, part_off}, blockIdx.x);
 }
 
 // merge of one layer and, in the same launch, an append that touches other memory than the
 // merge: the next layer's new rows (cross-layer fusion), or this layer's rows of the items whose
 // tiles read their keys from k_new / v_new (nx.runs names them, a block of a table each).  256 threads append.
 template <int kBlockHeads>
-__global__ __launch_bounds__(64 * kBlockHeads) void merge_append_kernel(const int32_t* n_parts,
-                                                                        const int32_t* part_off,
-                                                                        const AttnArgs a,
-                                                                        const AppendArgs nx) {
+__global__ __launch_bounds__(64 * kBlockHeads) void merge_append_kernel(OXY_MERGE_PARAMS, const AppendArgs nx) {
   __shared__ PageLds sm;
-  const int n_merge = kHeads / kBlockHeads * a.n_q, i = (int)blockIdx.x - n_merge;
+  const int n_merge = kHeads / kBlockHeads * n_q, i = (int)blockIdx.x - n_merge;
   if (i < 0) {
-    merge_block<kBlockHeads>(n_parts, part_off, a, blockIdx.x);
+    merge_block<kBlockHeads>({part_acc, part_ml, out, lse, n_parts, part_off}, blockIdx.x);
     return;
   }
   if (threadIdx.x >= 256) return;
@@ -1310,16 +1318,18 @@ template <int kBlockHeads>
 void launch_merge(const AttnArgs& a, const AppendArgs* next, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const bool timed = start || stop, appends = next && next->n_blocks > 0;
   const dim3 grid(kHeads / kBlockHeads * a.n_q + (appends ? next->n_blocks : 0)), block(64 * kBlockHeads);
-  if (appends && timed)
-    hipExtLaunchKernelGGL(merge_append_kernel<kBlockHeads>, grid, block, 0, s, start, stop, 0, a.n_parts,
-                          a.part_off, a, *next);
-  else if (appends)
-    merge_append_kernel<kBlockHeads><<<grid, block, 0, s>>>(a.n_parts, a.part_off, a, *next);
-  else if (timed)
-    hipExtLaunchKernelGGL(merge_kernel<kBlockHeads>, grid, block, 0, s, start, stop, 0, a.n_parts,
-                          a.part_off, a);
+  const auto launch = [&](auto kernel, auto... more) {
+    if (timed)
+      hipExtLaunchKernelGGL(kernel, grid, block, 0, s, start, stop, 0, a.part_acc, a.part_ml, a.out, a.lse,
+                            a.n_parts, a.part_off, a.n_q, more...);
+    else
+      kernel<<<grid, block, 0, s>>>(a.part_acc, a.part_ml, a.out, a.lse, a.n_parts, a.part_off,
+                                    a.n_q, more...);
+  };
+  if (appends)
+    launch(merge_append_kernel<kBlockHeads>, *next);
   else
-    merge_kernel<kBlockHeads><<<grid, block, 0, s>>>(a.n_parts, a.part_off, a);
+    launch(merge_kernel<kBlockHeads>);
 }
 }  // namespace
 
