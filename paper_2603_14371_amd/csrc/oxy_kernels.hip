@@ -371,10 +371,27 @@ typedef const __attribute__((address_space(4))) i32x8* DescPtr8;
 // split's first 16 pages (the last one repeated).  All but the last eight words are requested
 // at once at the start of the kernel.
 struct WorkItem {
-  DescPtr rec, tbl;
+  DescPtr rec;
   i32x8 toks, pages;
-  int n_tok, kv_begin, kv_end, q0, part_idx;
+  int n_tok, tbl_off, kv_begin, kv_end, q0, part_idx;
 };
+// What a work item needs only after its first loads, read from the argument segment there.
+struct LateArgs {
+  uint16_t* part_acc;
+  float* part_ml;
+  const int32_t* tables;
+  int32_t write_through;
+};
+constexpr int kLateOffset = 7 * 8;   // behind the preloaded arguments
+__device__ __forceinline__ void take_late(AttnArgs& a) {
+  auto seg = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(seg));   // here, and not at the start of the kernel
+  const auto* late = (const __attribute__((address_space(4))) LateArgs*)(seg + kLateOffset);
+  a.part_acc = late->part_acc;
+  a.part_ml = late->part_ml;
+  a.tables = late->tables;
+  a.write_through = late->write_through;
+}
 // query token of this lane's row in group r
 __device__ __forceinline__ int token_of(const WorkItem& wi, const int r, const int second) {
   return second ? wi.toks[2 * r + 1] : wi.toks[2 * r];
@@ -585,7 +602,8 @@ __device__ __forceinline__ void store_part(const AttnArgs& a, const WorkItem& wi
 // CU's other workgroup waiting: work-item launch of eight requests and a chunk 7.3 us, now 7.0, of six
 // requests with 13 new tokens 10.2 / 9.6; others +-0.5 %.)
 template <int G, bool kOwnPages, bool kOnce, int kSteps>
-__device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
+__device__ __forceinline__ void attend(const AttnArgs& early_args, const WorkItem& wi, WorkLds& sm) {
+  AttnArgs a = early_args;
   int tid = threadIdx.x;
   // keeps what is computed from the thread id inside this instance: shared with the other
   // instances of the kernel it would have to live across all of them, which costs G = 4 spills
@@ -635,7 +653,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
       const DescPtr id = wi.rec + 16 + 8 * round + 2 * wv;
       load_k_of(id[0], id[1]);
     } else {
-      const DescPtr ids = wi.tbl + (wi.kv_begin >> 4);
+      const DescPtr ids = (DescPtr)a.tables + wi.tbl_off + (wi.kv_begin >> 4);
       const int pi = 8 * round + 2 * wv;
       load_k_of(ids[min(pi, npg - 1)], ids[min(pi + 1, npg - 1)]);
     }
@@ -644,7 +662,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     if (round < 2) {
       load_v_of(*(DescPtr8)(wi.rec + 16 + 8 * round));
     } else {
-      const DescPtr ids = wi.tbl + (wi.kv_begin >> 4);
+      const DescPtr ids = (DescPtr)a.tables + wi.tbl_off + (wi.kv_begin >> 4);
       i32x8 blks;
 #pragma unroll
       for (int i = 0; i < 8; ++i) blks[i] = ids[min(8 * round + i, npg - 1)];
@@ -702,6 +720,7 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
     __builtin_amdgcn_sched_barrier(0);
     auto store_q = [&]() {
       __builtin_amdgcn_sched_barrier(0);
+      take_late(a);
 #pragma unroll
       for (int r = 0; r < G; ++r) {
         const u32x4 z = {0, 0, 0, 0};
@@ -914,8 +933,9 @@ __device__ __forceinline__ void attend(const AttnArgs& a, const WorkItem& wi, Wo
 // before, one step only) they are read from the pages.  kG: groups of two tokens; every wavefront
 // scales and stores its 64 dims of all of them, one after the other, which is what a tile ends with.
 template <bool kOneStep, bool kRows, int kG>
-__device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& wi, WorkLds& sm,
+__device__ __forceinline__ void attend_fresh(const AttnArgs& early_args, const WorkItem& wi, WorkLds& sm,
                                              const int row0) {
+  AttnArgs a = early_args;
   static_assert(kOneStep || kRows, "several steps from pages go through attend");
   constexpr int kSteps = kOneStep ? 1 : 4;
   const int lane = threadIdx.x & 63;
@@ -972,6 +992,7 @@ __device__ __forceinline__ void attend_fresh(const AttnArgs& a, const WorkItem& 
   const int slot_req = request_slot<kMaxGroups>(a, wi, lane);
   if constexpr (kOneStep) load_v(0);
   __builtin_amdgcn_sched_barrier(0);
+  take_late(a);
 #pragma unroll
   for (int j = 0; j < 8; ++j) qf[j] = query_sign(a, qf[j]);
   float m_own = ninf, l[4] = {0.f, 0.f, 0.f, 0.f};   // of this wavefront's row n
@@ -1108,24 +1129,35 @@ __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem&
     few_keys ? attend<1, false, false, 2>(a, wi, sm) : attend<1, false, false, 4>(a, wi, sm);
 }
 
-// `work` travels in front of the argument block because the first arguments are preloaded into
-// scalar registers (see build.py): the record's address then waits for no load.
+// What the first loads need is preloaded into scalar registers (all 14 words there are; see build.py).  The rest is
+// read from the argument segment once those loads are on their way (take_late): every workgroup of a launch
+// reads that segment at the same time, and in front of the first loads it cost, us per layer, 50 queries + one
+// request 7.81 / 7.58, a chunk on 100 tokens 7.31 / 7.04, three requests 6.70 / 6.57, four chunks on 832 tokens 11.39 /
+// 11.22, one request 6.31 / 6.26, 64 requests and two chunks 22.29 / 22.18, 256 requests 71.6 / 71.8.
 // On a page of its own start: 768 bytes further on, because a kernel in front had grown, the same code took
 // 7.4-7.6 us instead of 7.0-7.2 in a cold launch of one request, and 19.8-20.1 instead of 19.3-19.5 in
 // repeated ones of 64 requests and two chunks.  Multiples of 8, 16 and 32 KiB are no better.
-__global__ __attribute__((aligned(4096))) __launch_bounds__(256, 2) void attn_kernel(const int32_t* work, const AttnArgs a) {
+__global__ __attribute__((aligned(4096))) __launch_bounds__(256, 2) void attn_kernel(
+    const int32_t* work, const void* q, const void* layer_base, const void* k_new, const void* v_new,
+    const int32_t* d_slots, const int32_t part_off, const float scale, const LateArgs) {
   __shared__ WorkLds sm;
+  AttnArgs a;
+  a.q = q;
+  a.layer_base = layer_base;
+  a.part_off = work + part_off;
+  a.scale = scale;
+  a.k_new = k_new;
+  a.v_new = v_new;
+  a.d_slots = d_slots;
   WorkItem wi;
   wi.rec = (DescPtr)work + (size_t)blockIdx.x * kWorkWords;
   const i32x8 head = ((DescPtr8)wi.rec)[0];
   wi.toks = ((DescPtr8)wi.rec)[1];
   wi.pages = ((DescPtr8)wi.rec)[2];
   // wanted here, in one go, and not one after the other where they are used first
-  asm volatile("" ::"s"(head), "s"(wi.toks), "s"(wi.pages), "s"(a.q), "s"(a.layer_base), "s"(a.tables),
-               "s"(a.part_off), "s"(a.part_acc), "s"(a.part_ml), "s"(a.k_new), "s"(a.v_new),
-               "s"(a.scale));
+  asm volatile("" ::"s"(head), "s"(wi.toks), "s"(wi.pages));
   wi.n_tok = head[W_N_TOK];
-  wi.tbl = (DescPtr)a.tables + head[W_TBL_OFF];
+  wi.tbl_off = head[W_TBL_OFF];
   wi.kv_begin = head[W_KV_BEGIN];
   wi.kv_end = head[W_KV_END];
   wi.q0 = head[W_CAUSAL_Q0];
@@ -1306,10 +1338,14 @@ __global__ __launch_bounds__(64 * kBlockHeads) void merge_append_kernel(OXY_MERG
 hipError_t launch_attention_work(const AttnArgs& a, hipStream_t s, hipEvent_t start,
                                  hipEvent_t stop) {
   if (a.n_work <= 0 || a.n_q <= 0) return hipErrorInvalidValue;
+  const LateArgs late = {a.part_acc, a.part_ml, a.tables, a.write_through};
+  const int32_t part_off = (int32_t)(a.part_off - a.work);   // of one descriptor
   if (start || stop)
-    hipExtLaunchKernelGGL(attn_kernel, dim3(a.n_work), dim3(256), 0, s, start, stop, 0, a.work, a);
+    hipExtLaunchKernelGGL(attn_kernel, dim3(a.n_work), dim3(256), 0, s, start, stop, 0, a.work, a.q, a.layer_base,
+                          a.k_new, a.v_new, a.d_slots, part_off, a.scale, late);
   else
-    attn_kernel<<<a.n_work, 256, 0, s>>>(a.work, a);
+    attn_kernel<<<a.n_work, 256, 0, s>>>(a.work, a.q, a.layer_base, a.k_new, a.v_new, a.d_slots, part_off, a.scale,
+                                         late);
   return hipGetLastError();
 }
 
