@@ -796,10 +796,28 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         int32_t idx, cost;
         bool tile;
       };
+      // What an item takes on a CU of its own, in half microseconds, from timelines of launches (start and end of
+      // every workgroup with its CU): 8 tokens x 64 or 128 keys 8.0-8.1 us, x 192 12.3; 4 x 128 5.4, x 256 9.3; a
+      // pair x 128 4.2, x 192 6.5; own pages of a request, read from HBM, 256 keys 9.6, up to 128 4.0-4.4; a
+      // fresh tile 4.4-5.  Two on one CU take as long as the longer one if the other has half its cost, 8 + 8
+      // tokens 11.2, 8 tokens + own 256 11.9, two own 256 15.  (With a cost of twice the steps for every tile and of
+      // the steps for everything else, 2-token tiles stood among the 8-token ones and own pages below them.  us per
+      // layer, that / this: two chunks and 40 requests on 832 tokens 16.7 / 12.1, six chunks and 48 on 700 19.1 / 16.3, five
+      // chunks on 1500 19.3 / 16.6, on 832 14.4 / 12.8, eight on 300 14.8 / 13.0, one of 300 queries 22.6 / 21.3, a chunk
+      // and 16 requests 9.93 / 9.34, two and 8 10.4 / 9.6, a chunk and 8 on eight observations 8.59 / 8.42, six
+      // requests with 13 new tokens 11.58 / 11.16, 64 requests and two chunks 22.2 / 22.1, eight chunks on 832 16.6 / 16.7.)
+      // A fresh tile is dealt out before the pairs, not to become somebody's second workgroup.  (Behind them where a
+      // third one comes to a CU: eight chunks on 500 tokens 16.85 / 16.6, six chunks and 48 requests 16.35 / 16.9.)
+      auto alone_cost = [](const int32_t* r) {
+        const int32_t n = r[oxy::W_N_TOK], steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
+        const int32_t more = (steps + 3) / 4 - 1;   // rounds behind the first
+        if (r[oxy::W_PATH] & oxy::kPathFresh) return 5 + 3 * steps + (n > 4 ? 2 : 0);
+        if (r[oxy::W_PATH] & oxy::kPathAppends) return 8 + 8 * more + steps / 2;
+        return n > 4 ? 14 + 8 * more + steps / 2 : n > 2 ? 9 + 8 * more + steps / 2 : 6 + 4 * more + steps / 2;
+      };
       std::vector<Rec> recs(nw);
       for (int32_t i = 0; i < nw; ++i) {
         const int32_t* r = &hdr[(size_t)i * kHdr];
-        const int32_t steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
         const bool tile = (r[oxy::W_PATH] & oxy::kPathMask) == oxy::PATH_TILE;
         // work items that read pages others read too: tiles (not those that take their keys from
         // the step's new rows: they read no pages, and dealt out as one group they would sit two
@@ -807,14 +825,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const bool fresh = (r[oxy::W_PATH] & oxy::kPathFresh) != 0;
         const bool shares = fresh ? false : (tile || !(r[oxy::W_PATH] & oxy::kPathAppends));
         recs[i].idx = i;
-        // A fresh tile has three barriers and eight tokens' stores beside its steps.  One of a single
-        // step ends about when a 4-step streaming item does: dealt out behind those and in front of
-        // the 2-step ones it does not become somebody's second workgroup on a CU.  us per layer with
-        // cost s / 2s / 2s + 1 / 3s for s steps: 8 requests + one chunk of 50 11.1 / 11.3 / 10.9 /
-        // 11.3 (runs of one side 10.9 to 11.6), two chunks of 100 16.7 / 15.5 / 15.3 / 16.6, of 200
-        // 28.2 / 26.25 / 25.95 / 26.0, one of 600 56.5 / 47.3 / 48.1 / 48.9 (these within 0.2), two of
-        // 300 appended separately no difference.
-        recs[i].cost = fresh ? 2 * steps + 1 : tile ? 2 * steps : steps;
+        recs[i].cost = alone_cost(r);
         recs[i].tile = tile && !fresh;
         recs[i].key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
                              : -(int64_t)i - 1;
@@ -849,16 +860,13 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       int64_t qcost[kXcd] = {0};
       for (int x = 0; x < kXcd; ++x) queue[x].reserve(nw / kXcd + 16);
       for (const Grp& g : grps) {
-        // least loaded XCD among those that still have a resident slot for every record of the
-        // group (two workgroups on each of 32 CUs); any XCD if none has
+        // least loaded XCD among those that still have a CU for every record of the group, else a
+        // resident slot (two workgroups on each of 32 CUs), else any
         int best = -1;
-        for (int x = 0; x < kXcd; ++x)
-          if (queue[x].size() + g.count <= (size_t)2 * kCuPerXcd && (best < 0 || qcost[x] < qcost[best]))
-            best = x;
-        if (best < 0) {
-          best = 0;
-          for (int x = 1; x < kXcd; ++x)
-            if (qcost[x] < qcost[best]) best = x;
+        for (size_t room : {(size_t)kCuPerXcd, (size_t)2 * kCuPerXcd, SIZE_MAX}) {
+          for (int x = 0; x < kXcd; ++x)
+            if (queue[x].size() + g.count <= room && (best < 0 || qcost[x] < qcost[best])) best = x;
+          if (best >= 0) break;
         }
         queue[best].insert(queue[best].end(), recs.begin() + g.first,
                            recs.begin() + g.first + g.count);
