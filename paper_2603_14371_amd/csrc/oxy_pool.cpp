@@ -772,15 +772,16 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     // eight requests on eight observations (258 / 270) 189.6 / 213.0; four shares as two in the first
     // (165.9).
     n_items_of_list = (int32_t)(hdr.size() / kHdr);
+    auto add_second_half = [&](int32_t i) {   // tokens 4.. of item i, whose own record keeps the first four
+      int32_t w[kHdr];
+      std::copy(&hdr[(size_t)i * kHdr], &hdr[(size_t)i * kHdr] + kHdr, w);
+      w[oxy::W_TOK_OFF] += 4;
+      w[oxy::W_N_TOK] -= 4;
+      if (w[oxy::W_CAUSAL_Q0] != oxy::kNoCausal) w[oxy::W_CAUSAL_Q0] += 4;
+      hdr.insert(hdr.end(), w, w + kHdr);
+    };
     if (n_items_of_list + (int64_t)wide_tiles.size() <= std::min(256, c.max_work_items)) {
-      for (int32_t i : wide_tiles) {
-        int32_t w[kHdr];
-        std::copy(&hdr[(size_t)i * kHdr], &hdr[(size_t)i * kHdr] + kHdr, w);
-        w[oxy::W_TOK_OFF] += 4;
-        w[oxy::W_N_TOK] -= 4;
-        if (w[oxy::W_CAUSAL_Q0] != oxy::kNoCausal) w[oxy::W_CAUSAL_Q0] += 4;
-        hdr.insert(hdr.end(), w, w + kHdr);
-      }
+      for (int32_t i : wide_tiles) add_second_half(i);
     } else {
       wide_tiles.clear();
     }
@@ -794,7 +795,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       struct Rec {
         int64_t key;     // readers of shared pages: (table, split begin); others: unique
         int32_t idx, cost;
-        bool tile;
+        bool tile, wide;   // reads pages that others may read too; of more than four tokens
       };
       // What an item takes on a CU of its own, in half microseconds, from timelines of launches (start and end of
       // every workgroup with its CU): 8 tokens x 64 or 128 keys 8.0-8.1 us, x 192 12.3; 4 x 128 5.4, x 256 9.3; a
@@ -827,6 +828,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         recs[i].idx = i;
         recs[i].cost = alone_cost(r);
         recs[i].tile = tile && !fresh;
+        recs[i].wide = recs[i].tile && r[oxy::W_N_TOK] > 4;
         recs[i].key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
                              : -(int64_t)i - 1;
       }
@@ -871,6 +873,27 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         queue[best].insert(queue[best].end(), recs.begin() + g.first,
                            recs.begin() + g.first + g.count);
         qcost[best] += g.cost;
+      }
+      // Chunks alone: an XCD's items of more than four tokens beyond one for each of its CUs would be what the launch
+      // ends with, two on a CU, so two records of four tokens share each of them if all have a slot.  us per layer,
+      // without / with: six chunks on 1500 tokens 20.2 / 17.5, on 2048 20.8 / 18.2, on 832 14.9 / 13.6, seven 16.0 / 14.1; beyond
+      // 64 records of an XCD it loses (eight on 1000 17.4 / 18.1).
+      for (int x = 0; x < kXcd && !decodes; ++x) {
+        std::vector<Rec>& q = queue[x];
+        const size_t n_wide = std::count_if(q.begin(), q.end(), [](const Rec& e) { return e.wide; });
+        size_t beyond = n_wide > kCuPerXcd ? n_wide - kCuPerXcd : 0;
+        if (q.size() + beyond > (size_t)2 * kCuPerXcd || hdr.size() / kHdr + beyond > (size_t)c.max_work_items) continue;
+        for (size_t i = q.size(); beyond > 0 && i-- > 0;) {
+          if (!q[i].wide) continue;
+          Rec second = q[i];
+          second.idx = (int32_t)(hdr.size() / kHdr);
+          add_second_half(q[i].idx);
+          wide_tiles.push_back(q[i].idx);
+          second.wide = q[i].wide = false;
+          second.cost = q[i].cost = alone_cost(&hdr[(size_t)second.idx * kHdr]);
+          q.push_back(second);
+          --beyond;
+        }
       }
       size_t longest = 0;
       for (int x = 0; x < kXcd; ++x) {

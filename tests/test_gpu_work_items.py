@@ -75,6 +75,25 @@ def test_magnitude_of_the_values_does_not_enter_the_rounding(power):
     assert np.array_equal(outs[0][nonzero] + power * 128, outs[1][nonzero])
 
 
+@pytest.mark.parametrize("n,prefix_len,chunk", [(7, 832, 50), (6, 1500, 47)])
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+def test_items_of_chunks_that_two_records_share_equal_the_chunk_alone(n, prefix_len, chunk, fold):
+    from paper_2603_14371_amd.harness import GpuWorld
+    b = _TraceBuilder()
+    acts = [b.stream(b.prefix(prefix_len), ACTION) for _ in range(n)]
+    w = _workload("shared_items", 5153, 1, 1024, b.trace)
+    gw = GpuWorld(w, synth.DataSource(w["seed"]), max_q_tokens=512, max_append_tokens=512, max_partials=16384,
+                  fold_append=fold, poison=True)
+    gw.run(w["trace"])
+    data = {"tag": 901, "tok0": 0, "n_total": n * chunk}
+    alone = [gw.step({"op": "step", "items": [(a, chunk)], "data": dict(data, tok0=i * chunk)})
+             for i, a in enumerate(acts)]
+    whole = gw.step({"op": "step", "items": [(a, chunk) for a in acts], "data": data})
+    gw.close()
+    for key in ("O", "LSE"):
+        assert np.array_equal(whole[key][0], np.concatenate([r[key][0] for r in alone]))
+
+
 @pytest.mark.parametrize("n_prefix,prefix_len,width", [(3, 832, 4), (9, 832, 8), (9, 190, 4)])
 @pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
 def test_items_in_a_launch_of_many_equal_items_alone(n_prefix, prefix_len, width, fold):

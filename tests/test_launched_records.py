@@ -131,6 +131,33 @@ def test_items_are_shared_up_to_256_workgroups_and_within_the_limit():
     assert seen == {True, False}
 
 
+@pytest.mark.parametrize("n,prefix_len,chunk,shares", [
+    (6, 1500, 50, True), (7, 832, 50, True), (6, 2048, 50, True), (7, 832, 47, True), (5, 832, 50, False),
+    (8, 832, 50, False), (8, 1000, 50, False), (1, 832, 400, False)])
+def test_chunks_alone_share_items_beyond_one_for_each_cu(n, prefix_len, chunk, shares):
+    """Items of more than four tokens on prefix pages, more than 256 of them and slots left: some are two
+    records of at most four, while all such have a slot; beside a request none is."""
+    def launch(request=False):
+        p = _Pool()
+        pids = [p.prefix(prefix_len) for _ in range(n)]
+        items = [(p.stream(pid, B.KIND_ACTION), chunk) for pid in pids]
+        items += [(p.stream(pids[0], B.KIND_DECODE, 5), 1)] if request else []
+        out = p.build(items)
+        p.close()
+        return out[0], out[1]
+    rec, work = launch()
+    assert (len(rec) > len(work)) == shares
+    if shares:
+        assert len(rec) <= 512
+        where = lambda r, d=0: (r[0] - d, *r[[2, 3, 4, 6]])   # noqa: E731
+        first, listed = {where(r): r[1] for r in rec}, {where(r) for r in work}
+        second = [r for r in rec if where(r) not in listed]
+        assert len(second) == len(rec) - len(work)
+        assert all(1 <= r[1] <= 4 and first[where(r, 4)] == 4 for r in second)
+        mixed, listed = launch(request=True)
+        assert len(mixed) == len(listed)
+
+
 @pytest.mark.parametrize("seed", range(30))
 def test_every_pair_of_query_and_key_in_one_record(seed):
     rng = np.random.default_rng(8000 + seed)
