@@ -794,7 +794,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       constexpr int kXcd = 8, kCuPerXcd = 32;
       struct Rec {
         int64_t key;     // readers of shared pages: (table, split begin); others: unique
-        int32_t idx, cost;
+        int32_t idx, cost, load;   // cost: what shares a CU; load: which XCD
         bool tile, wide;   // reads pages that others may read too; of more than four tokens
       };
       // What an item takes on a CU of its own, in half microseconds, from timelines of launches (start and end of
@@ -805,8 +805,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       // the steps for everything else, 2-token tiles stood among the 8-token ones and own pages below them.  us per
       // layer, that / this: two chunks and 40 requests on 832 tokens 16.7 / 12.1, six chunks and 48 on 700 19.1 / 16.3, five
       // chunks on 1500 19.3 / 16.6, on 832 14.4 / 12.8, eight on 300 14.8 / 13.0, one of 300 queries 22.6 / 21.3, a chunk
-      // and 16 requests 9.93 / 9.34, two and 8 10.4 / 9.6, a chunk and 8 on eight observations 8.59 / 8.42, six
-      // requests with 13 new tokens 11.58 / 11.16, 64 requests and two chunks 22.2 / 22.1, eight chunks on 832 16.6 / 16.7.)
+      // and 16 requests 9.93 / 9.34, two and 8 10.4 / 9.6, six requests with 13 new tokens 11.58 / 11.16, 64 requests and
+      // two chunks 22.2 / 22.1, eight chunks on 832 16.6 / 16.7.)
       // A fresh tile is dealt out before the pairs, not to become somebody's second workgroup.  (Behind them where a
       // third one comes to a CU: eight chunks on 500 tokens 16.85 / 16.6, six chunks and 48 requests 16.35 / 16.9.)
       auto alone_cost = [](const int32_t* r) {
@@ -827,6 +827,15 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const bool shares = fresh ? false : (tile || !(r[oxy::W_PATH] & oxy::kPathAppends));
         recs[i].idx = i;
         recs[i].cost = alone_cost(r);
+        // XCDs are balanced by steps, twice for several tokens, except where the time does not go with the keys
+        // (fresh tiles, tiles of more than four tokens): an XCD whose items read few keys gets the records that
+        // no CU is left for, and pairs them there.  us a step, by the cost / so, pages not in the caches: a chunk and
+        // eight requests on eight observations 187 / 162, two chunks and eight 195.8 / 194.4; a chunk and 16 requests,
+        // six requests with 13 new tokens +-0.7 %.
+        const int32_t steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
+        recs[i].load = fresh || (tile && r[oxy::W_N_TOK] > 4) ? recs[i].cost / 2
+                       : tile && r[oxy::W_N_TOK] > 2          ? 2 * steps
+                                                              : steps;
         recs[i].tile = tile && !fresh;
         recs[i].wide = recs[i].tile && r[oxy::W_N_TOK] > 4;
         recs[i].key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
@@ -843,14 +852,14 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       for (int32_t i = 0; i < nw;) {
         int32_t j = i;
         int64_t cst = 0;
-        while (j < nw && recs[j].key == recs[i].key) cst += recs[j++].cost;
+        while (j < nw && recs[j].key == recs[i].key) cst += recs[j++].load;
         // A tile that is the only reader of its pages fetches all of them from HBM itself (a
         // tile that shares its split finds most of them on their way into the L2 already) and
         // is the slowest kind of work item per step: it counts half as much again, which makes
         // the pairing below give it the smallest partner on its CU, or none.
         if (j - i == 1 && recs[i].tile) {
           recs[i].cost = recs[i].cost * 3 / 2;
-          cst = recs[i].cost;
+          cst = recs[i].load * 3 / 2;
         }
         grps.push_back({i, j - i, cst});
         i = j;
@@ -862,10 +871,10 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       int64_t qcost[kXcd] = {0};
       for (int x = 0; x < kXcd; ++x) queue[x].reserve(nw / kXcd + 16);
       for (const Grp& g : grps) {
-        // least loaded XCD among those that still have a CU for every record of the group, else a
-        // resident slot (two workgroups on each of 32 CUs), else any
+        // least loaded XCD among those that still have a resident slot for every record of the
+        // group (two workgroups on each of 32 CUs); any XCD if none has
         int best = -1;
-        for (size_t room : {(size_t)kCuPerXcd, (size_t)2 * kCuPerXcd, SIZE_MAX}) {
+        for (size_t room : {(size_t)2 * kCuPerXcd, SIZE_MAX}) {
           for (int x = 0; x < kXcd; ++x)
             if (queue[x].size() + g.count <= room && (best < 0 || qcost[x] < qcost[best])) best = x;
           if (best >= 0) break;
