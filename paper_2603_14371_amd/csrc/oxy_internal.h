@@ -118,6 +118,11 @@ struct AppendArgs {
   // its first slot on, (first token << 4) | (length - 1)
   const int32_t* runs;
 };
+// Heads, and wavefronts, of a merge workgroup: 4, or all 8 where a launch has more tokens than the GPU has CUs.
+// us per layer, 4 / 8: one request 6.70 / 6.83, 50 queries + one request 8.12 / 8.34, 78 queries 13.1 / 13.45, 164 22.8 /
+// 22.7, 356 72.7 / 72.7, 400 17.8 / 17.3.  Each is a kernel of its own: a recording of one is none of the other.
+constexpr int kMergeManyTokens = 256;
+constexpr int merge_heads(int32_t n_q) { return n_q > kMergeManyTokens ? kHeads : kHeads / 2; }
 // merge of `a`, and in the same launch the append described by `next` (may be null)
 hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStream_t s,
                                hipEvent_t start = nullptr, hipEvent_t stop = nullptr);

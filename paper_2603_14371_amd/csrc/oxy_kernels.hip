@@ -1207,10 +1207,6 @@ __global__ __attribute__((aligned(4096))) __launch_bounds__(256, 2) void attn_ke
 // kernel.)
 // ------------------------------------------------------------------------------------------
 constexpr int kMergeAhead = 16;       // partials whose loads are all issued before anything is used
-// Heads, and wavefronts, of a merge workgroup: 4, or all 8 where a launch has more tokens than the GPU has CUs.
-// us per layer, 4 / 8: one request 6.70 / 6.83, 50 queries + one request 8.12 / 8.34, 78 queries 13.1 / 13.45, 164 22.8 /
-// 22.7, 356 72.7 / 72.7, 400 17.8 / 17.3.
-constexpr int kMergeManyTokens = 256;
 struct MergeArgs {
   const uint16_t* part_acc;
   const float* part_ml;
@@ -1395,7 +1391,7 @@ void launch_merge(const AttnArgs& a, const AppendArgs* next, hipStream_t s, hipE
 hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStream_t s,
                                hipEvent_t start, hipEvent_t stop) {
   if (a.n_q <= 0) return hipErrorInvalidValue;
-  if (a.n_q > kMergeManyTokens)
+  if (merge_heads(a.n_q) == kHeads)
     launch_merge<kHeads>(a, next, s, start, stop);
   else
     launch_merge<kHeads / 2>(a, next, s, start, stop);

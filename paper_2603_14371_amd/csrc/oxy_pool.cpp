@@ -77,11 +77,11 @@ struct StepKey {
            off_part_off == o.off_part_off && off_n_parts == o.off_n_parts &&
            write_through == o.write_through;
   }
-  // same number and kinds of launches in the same order: an instantiated graph can be updated
+  // same number and kernels of launches in the same order: an instantiated graph can be updated
   // in place from a recording of the other
   bool same_topology(const StepKey& o) const {
     return layer_end - layer_begin == o.layer_end - o.layer_begin && mode == o.mode &&
-           (n_tokens > 0) == (o.n_tokens > 0) && (n_fresh > 0) == (o.n_fresh > 0);
+           oxy::merge_heads(n_tokens) == oxy::merge_heads(o.n_tokens) && (n_fresh > 0) == (o.n_fresh > 0);
   }
 };
 struct StepGraph {

@@ -8,6 +8,7 @@
 
 #include <cstdlib>
 #include <cstring>
+#include <string>
 
 static int g_fail_next = 0, g_fail_skip = 0;
 static long g_calls = 0;
@@ -55,7 +56,13 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 // recorded launch sequences: a stream, a graph and an instantiated graph are small heap objects,
-// so that the sanitizer sees every leak, double free and use after free of the host logic
+// so that the sanitizer sees every leak, double free and use after free of the host logic.  A graph
+// is the kernels that were launched while it was recorded; an instantiated one takes an update
+// from a graph of the same kernels only, and any other attempt is counted.
+static std::string g_launched;
+static long g_misfits = 0, g_updates = 0;
+long oxy_stub_misfits() { return g_misfits; }
+long oxy_stub_updates() { return g_updates; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   *s = (hipStream_t)malloc(8);
@@ -65,27 +72,35 @@ hipError_t hipStreamDestroy(hipStream_t s) {
   free((void*)s);
   return hipSuccess;
 }
-hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return outcome(); }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) {
+  g_launched.clear();
+  return outcome();
+}
 hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) {
-  *g = (hipGraph_t)malloc(8);
+  *g = (hipGraph_t) new std::string(g_launched);
   return hipSuccess;
 }
 hipError_t hipGraphDestroy(hipGraph_t g) {
-  free((void*)g);
+  delete (std::string*)g;
   return hipSuccess;
 }
-hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+hipError_t hipGraphInstantiate(hipGraphExec_t* x, hipGraph_t g, hipGraphNode_t*, char*, size_t) {
   hipError_t e = outcome();
-  if (e == hipSuccess) *x = (hipGraphExec_t)malloc(8);
+  if (e == hipSuccess) *x = (hipGraphExec_t) new std::string(*(std::string*)g);
   return e;
 }
 hipError_t hipGraphExecDestroy(hipGraphExec_t x) {
-  free((void*)x);
+  delete (std::string*)x;
   return hipSuccess;
 }
-hipError_t hipGraphExecUpdate(hipGraphExec_t x, hipGraph_t, hipGraphNode_t*,
+hipError_t hipGraphExecUpdate(hipGraphExec_t x, hipGraph_t g, hipGraphNode_t*,
                               hipGraphExecUpdateResult* res) {
-  *(volatile char*)x;   // must still be alive
+  ++g_updates;
+  if (*(std::string*)x != *(std::string*)g) {
+    ++g_misfits;
+    *res = hipGraphExecUpdateErrorFunctionChanged;
+    return hipErrorGraphExecUpdateFailure;
+  }
   hipError_t e = outcome();
   *res = e == hipSuccess ? hipGraphExecUpdateSuccess : hipGraphExecUpdateError;
   return e;
@@ -110,6 +125,7 @@ hipError_t launch_upload(const int32_t* pinned, int32_t* device, int32_t n_words
   return e;
 }
 hipError_t launch_append(const void*, const void*, const int32_t*, int32_t, void*, hipStream_t) {
+  g_launched += "append ";
   return outcome();
 }
 hipError_t launch_append_inline(const void*, const void*, const InlineIds&, int32_t, int32_t, void*,
@@ -136,6 +152,7 @@ hipError_t launch_gather_inline(const void*, const GatherRuns& runs, int32_t n_r
 // the work items load whole eight-word parts of their records
 static hipError_t attention_outcome(const AttnArgs& a) {
   g_write_through = a.write_through;
+  g_launched += "work ";
   return (uintptr_t)a.work % (4 * kWorkWords) ? hipErrorInvalidValue : outcome();
 }
 hipError_t launch_attention(const AttnArgs& a, hipStream_t) { return attention_outcome(a); }
@@ -148,8 +165,9 @@ hipError_t static_scratch(uint16_t** part_acc, float** part_ml) {
 hipError_t launch_attention_work(const AttnArgs& a, hipStream_t, hipEvent_t, hipEvent_t) {
   return attention_outcome(a);
 }
-hipError_t launch_merge_append(const AttnArgs&, const AppendArgs*, hipStream_t, hipEvent_t,
+hipError_t launch_merge_append(const AttnArgs& a, const AppendArgs* next, hipStream_t, hipEvent_t,
                                hipEvent_t) {
+  g_launched += (next && next->n_blocks > 0 ? "merge_append/" : "merge/") + std::to_string(merge_heads(a.n_q)) + " ";
   return outcome();
 }
 }  // namespace oxy

@@ -15,6 +15,7 @@
 //   9 skip k                                                       after `skip` device calls, k fail
 //  11 n slot* max_launches                                        gather_kv
 //  12 expect_write_through                                       of the last attention launch
+//  13 min_updates                                                of recordings so far, none of other kernels
 //  10 nb ref* nfree free* ns (sid pid kind len nblk blk*)* np (pid len nblk sealed nstreams blk*)*
 #include "../../include/oxy.h"
 
@@ -25,6 +26,8 @@
 extern "C" void oxy_stub_fail_next(int skip, int k);
 extern "C" long oxy_stub_gathers();
 extern "C" long oxy_stub_write_through();
+extern "C" long oxy_stub_updates();
+extern "C" long oxy_stub_misfits();
 
 static FILE* g_in;
 static long g_line = 0;
@@ -230,6 +233,13 @@ int main(int argc, char** argv) {
       case 12: {
         const long exp = need();
         CHECK(oxy_stub_write_through() == exp, "write_through %ld != %ld", oxy_stub_write_through(), exp);
+        break;
+      }
+      case 13: {
+        const long least = need();
+        CHECK(oxy_stub_updates() >= least, "%ld updates < %ld", oxy_stub_updates(), least);
+        CHECK(oxy_stub_misfits() == 0, "%ld of %ld updates from a recording of other kernels", oxy_stub_misfits(),
+              oxy_stub_updates());
         break;
       }
       default:

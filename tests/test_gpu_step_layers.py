@@ -162,3 +162,51 @@ def test_recordings_beyond_the_cache_are_updated_in_place():
         B.oxy_batch_destroy(batch)
     finally:
         gw.close()
+
+
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+def test_recordings_of_both_merge_forms_beyond_the_cache(fold):
+    """Steps of 250 and of 300 query tokens, whose merges are two kernels, in turn: six forms of each against
+    a cache of eight recordings.  Every replay, with the program's own eager work in between, gives the
+    unrecorded bits."""
+    import torch
+    from paper_2603_14371_amd import binding as B
+    from paper_2603_14371_amd.harness import GpuWorld, bits_of, to_device_bf16
+    b = synth._TraceBuilder()
+    pid = b.prefix(100)
+    counts = (250, 300)
+    sids = [b.stream(pid, synth.ACTION) for _ in counts]
+    w = synth._workload("both_merge_forms", 5171, 2, 256, b.trace)
+    data = synth.DataSource(1620)
+    gw = GpuWorld(w, data, max_q_tokens=512, max_append_tokens=512, max_partials=16384)
+    try:
+        gw.run(w["trace"])
+        stream, L = torch.cuda.current_stream(gw.device).cuda_stream, gw.n_layers
+        base = B.STEP_FOLD_APPEND if fold else 0
+        forms = []
+        for sid, n in zip(sids, counts):
+            k, v, q = (torch.stack([to_device_bf16(data({"tag": 910 + n, "tok0": 0, "n_total": n}, l, what, n), gw.device)
+                                    for l in range(L)]) for what in "kvq")
+            forms.append((B.oxy_batch_build(gw.pool, [(sid, n)], 0, stream), k, v, q,
+                          [torch.zeros_like(q) for _ in range(6)]))
+
+        def run(form, o, flags):
+            batch, k, v, q, _ = form
+            o.zero_()
+            B.oxy_step_layers(gw.pool, batch, 0, L, k.data_ptr(), v.data_ptr(), k.stride(0) * 2, q.data_ptr(),
+                              o.data_ptr(), q.stride(0) * 2, 0, 0, gw.scale, flags, None, stream)
+            torch.cuda.synchronize()
+            return bits_of(o)
+
+        refs = [run(f, torch.zeros_like(f[3]), base) for f in forms]
+        assert all(np.any(r != 0) for r in refs)
+        for rnd in range(3):
+            for i in range(6):
+                for f, ref in zip(forms, refs):
+                    assert np.array_equal(run(f, f[4][i], base | B.STEP_GRAPH), ref), "round %d form %d" % (rnd, i)
+        inst, upd, rep = B.oxy_step_graph_stats(gw.pool)
+        assert inst == 8 and upd == 36 - 8 and rep == 36, (inst, upd, rep)
+        for f in forms:
+            B.oxy_batch_destroy(f[0])
+    finally:
+        gw.close()

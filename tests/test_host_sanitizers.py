@@ -214,3 +214,25 @@ def test_which_launches_write_their_split_results_through(replay_exe, tmp_path, 
     script.append([8, 0, len(items)] + [x for it in items for x in it] + [0, len(slots)] + slots)
     script.append([12, through])
     _run(replay_exe, tmp_path, script)
+
+
+@pytest.mark.parametrize("n_layers", [1, 3])
+def test_recordings_are_updated_from_recordings_of_the_same_kernels(replay_exe, tmp_path, n_layers):
+    """The merge is another kernel above 256 query tokens.  Steps on both sides of that in turn, more of
+    them than recordings are kept: each takes the place of one whose launches are the same."""
+    nb = 512
+    model = PoolModel(nb, 16, n_layers, list(range(nb)))
+    script = [[0, nb, n_layers, 1, 512, 0], [1, model.prefix_create()]]
+    for layer in range(n_layers):
+        model.prefix_append(0, layer, 100, 0)
+        script.append([2, 0, layer, 100, 0, 0])
+    sids = []
+    for kind in (0, 1):
+        sids.append(model.stream_create(0, kind))
+        script.append([5, 0, kind, 0, sids[-1]])
+    for n in (255, 257, 256, 300, 64, 258, 250, 400, 3, 255, 258):
+        for items in ([(sids[0], n)], [(sids[0], n - 1), (sids[1], 1)]):
+            slots = model.batch_build(items)
+            script.append([8, 0, len(items)] + [x for it in items for x in it] + [0, len(slots)] + slots)
+    script.append([13, 20])
+    _run(replay_exe, tmp_path, script)
