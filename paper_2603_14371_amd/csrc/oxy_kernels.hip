@@ -32,6 +32,7 @@
 #include <hip/hip_ext.h>
 
 #include <mutex>
+#include <tuple>
 #include <type_traits>
 #include <utility>
 
@@ -401,7 +402,7 @@ struct LateArgs {
   const int32_t* tables;
   int32_t write_through;
 };
-constexpr int kLateOffset = 7 * 8;   // behind the preloaded arguments
+constexpr int kLateOffset = 7 * 8;   // behind the preloaded arguments (held against attn_kernel's own list below it)
 __device__ __forceinline__ void take_late(AttnArgs& a) {
   auto seg = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(seg));   // here, and not at the start of the kernel
@@ -1196,6 +1197,22 @@ __global__ __attribute__((aligned(4096))) __launch_bounds__(256, 2) void attn_ke
   else
     attend_shared(a, wi, sm);
 }
+// Where the argument segment holds a kernel's last argument: each lies at the next multiple of its alignment.
+template <class Kernel>
+struct Params;
+template <class... P>
+struct Params<void (*)(P...)> {
+  using Last = std::tuple_element_t<sizeof...(P) - 1, std::tuple<P...>>;
+  static constexpr size_t offset_of_last() {
+    constexpr size_t n = sizeof...(P), size[n] = {sizeof(P)...}, align[n] = {alignof(P)...};
+    size_t at = 0;
+    for (size_t i = 0; i + 1 < n; ++i) at = (at + align[i] - 1) / align[i] * align[i] + size[i];
+    return (at + align[n - 1] - 1) / align[n - 1] * align[n - 1];
+  }
+};
+using AttnParams = Params<decltype(&attn_kernel)>;
+static_assert(std::is_same_v<AttnParams::Last, LateArgs> && AttnParams::offset_of_last() == kLateOffset,
+              "take_late reads attn_kernel's last argument at kLateOffset");
 
 // ------------------------------------------------------------------------------------------
 // merge of a query token's partials (log-sum-exp rule).  One wavefront per token and head, which has

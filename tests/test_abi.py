@@ -3,6 +3,7 @@ no compute calls."""
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -103,3 +104,27 @@ def test_the_library_builds_without_python_headers_or_a_host_compiler(missing, m
         monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
     assert build.build_library() == build.LIB
     assert built == [build.LIB, build.PROBE_LIB] and not os.path.exists(build.MARSHAL_LIB)
+
+
+LIST = "const int32_t part_off, const float scale, const LateArgs)"
+
+
+@pytest.mark.parametrize("params,builds", [
+    (LIST, True),
+    (LIST.replace("int32_t", "int64_t"), False),                       # the last argument lies 8 bytes further on
+    (LIST.replace("const float scale, const LateArgs", "const LateArgs, const float scale"), False),
+], ids=["as_it_is", "wider", "reordered"])
+def test_last_argument_of_the_work_items_is_where_it_is_read(tmp_path, params, builds):
+    """Work items read their last argument at an offset of their own: another parameter list does not build."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    if not os.path.exists(hipcc):
+        pytest.skip("no hipcc")
+    csrc = os.path.join(ROOT, "paper_2603_14371_amd", "csrc")
+    text = open(os.path.join(csrc, "oxy_kernels.hip")).read()
+    assert text.count(LIST) == 1
+    src = tmp_path / "kernels.hip"
+    src.write_text(text.replace(LIST, params))
+    res = subprocess.run([hipcc, "-fsyntax-only", "--cuda-device-only", "-std=c++17", "--offload-arch=gfx950",
+                          "-I" + csrc, str(src)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert (res.returncode == 0) == builds, res.stdout[-2000:]
+    assert ("take_late reads" in res.stdout) == (not builds), res.stdout[-2000:]
