@@ -809,14 +809,16 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       // two chunks 22.2 / 22.1, eight chunks on 832 16.6 / 16.7.)
       // A fresh tile is dealt out before the pairs, not to become somebody's second workgroup.  (Behind them where a
       // third one comes to a CU: eight chunks on 500 tokens 16.85 / 16.6, six chunks and 48 requests 16.35 / 16.9.)
-      auto alone_cost = [](const int32_t* r) {
-        const int32_t n = r[oxy::W_N_TOK], steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
+      // n: tokens that the record is launched with, which are four where it shares its item.
+      auto alone_cost = [](const int32_t* r, const int32_t n) {
+        const int32_t steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
         const int32_t more = (steps + 3) / 4 - 1;   // rounds behind the first
         if (r[oxy::W_PATH] & oxy::kPathFresh) return 5 + 3 * steps + (n > 4 ? 2 : 0);
         if (r[oxy::W_PATH] & oxy::kPathAppends) return 8 + 8 * more + steps / 2;
         return n > 4 ? 14 + 8 * more + steps / 2 : n > 2 ? 9 + 8 * more + steps / 2 : 6 + 4 * more + steps / 2;
       };
       std::vector<Rec> recs(nw);
+      size_t shared = 0;   // of wide_tiles, which ascends
       for (int32_t i = 0; i < nw; ++i) {
         const int32_t* r = &hdr[(size_t)i * kHdr];
         const bool tile = (r[oxy::W_PATH] & oxy::kPathMask) == oxy::PATH_TILE;
@@ -826,7 +828,12 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const bool fresh = (r[oxy::W_PATH] & oxy::kPathFresh) != 0;
         const bool shares = fresh ? false : (tile || !(r[oxy::W_PATH] & oxy::kPathAppends));
         recs[i].idx = i;
-        recs[i].cost = alone_cost(r);
+        int32_t n_tok = r[oxy::W_N_TOK];
+        if (shared < wide_tiles.size() && wide_tiles[shared] == i) {
+          n_tok = 4;
+          ++shared;
+        }
+        recs[i].cost = alone_cost(r, n_tok);
         // XCDs are balanced by steps, twice for several tokens, except where the time does not go with the keys
         // (fresh tiles, tiles of more than four tokens): an XCD whose items read few keys gets the records that
         // no CU is left for, and pairs them there.  us a step, by the cost / so, pages not in the caches: a chunk and
@@ -899,7 +906,10 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
           add_second_half(q[i].idx);
           wide_tiles.push_back(q[i].idx);
           second.wide = q[i].wide = false;
-          second.cost = q[i].cost = alone_cost(&hdr[(size_t)second.idx * kHdr]);
+          // two records read the item's pages now, so neither is a sole reader
+          const int32_t* r = &hdr[(size_t)second.idx * kHdr];
+          q[i].cost = alone_cost(r, 4);
+          second.cost = alone_cost(r, r[oxy::W_N_TOK]);
           q.push_back(second);
           --beyond;
         }

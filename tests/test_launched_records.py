@@ -34,6 +34,7 @@ class _Pool:
         batch = B.oxy_batch_build(self.h, items, 0, 0)
         rec, work, info = B.oxy_batch_records(batch), B.oxy_batch_work(batch), B.oxy_batch_info(batch)
         B.oxy_batch_destroy(batch)
+        self.launched = rec
         rec, work = rec[rec[:, 7] & PATH_MASK != 2], work[work[:, 7] != 2]
         self._check(items, rec, info)
         return rec, work, info
@@ -156,6 +157,41 @@ def test_chunks_alone_share_items_beyond_one_for_each_cu(n, prefix_len, chunk, s
         assert all(1 <= r[1] <= 4 and first[where(r, 4)] == 4 for r in second)
         mixed, listed = launch(request=True)
         assert len(mixed) == len(listed)
+
+
+def _by_size(records):
+    """The records of every XCD in the order of their size: of more than 32, the largest of the first 32 is
+    dealt out with the smallest of the next 32."""
+    for x in range(8):
+        q = [r for r in records[x::8] if r[7] & PATH_MASK != 2]
+        if len(q) > 32:
+            top = min(len(q), 64)
+            m, r = top - 32, [None] * top
+            for j in range(m):
+                r[32 - m + j], r[top - 1 - j] = q[j], q[32 + j]
+            for j in range(m, 32):
+                r[j - m] = q[j]
+            q[:top] = r
+        yield q
+
+
+@pytest.mark.parametrize("n,prefix_len,chunk", [
+    (7, 832, 45), (7, 832, 46), (7, 832, 47), (7, 832, 53), (6, 1500, 45), (6, 1500, 50), (6, 2048, 53)])
+def test_halved_items_are_ordered_by_the_tokens_each_record_has(n, prefix_len, chunk):
+    """An XCD's records of three and four tokens on a whole split of a prefix stand together in the order of
+    size, behind those of more tokens: also the ones whose item has one or two tokens left for the other record."""
+    p = _Pool()
+    rec, work, _ = p.build([(p.stream(p.prefix(prefix_len), B.KIND_ACTION), chunk) for _ in range(n)])
+    p.close()
+    assert len(rec) > len(work)
+    halved = 0
+    for q in _by_size(p.launched):
+        most = max(r[4] - r[3] for r in q)
+        kind = [0 if r[4] - r[3] < most else 2 if r[1] > 4 else int(r[1] > 2) for r in q]   # 0: all others
+        kind = "".join(str(k) for k in kind)
+        assert kind == "2" * kind.count("2") + kind.lstrip("2") and "1" * kind.count("1") in kind
+        halved += kind.count("1")
+    assert halved
 
 
 @pytest.mark.parametrize("seed", range(30))
