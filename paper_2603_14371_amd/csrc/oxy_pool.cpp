@@ -795,7 +795,7 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       struct Rec {
         int64_t key;     // readers of shared pages: (table, split begin); others: unique
         int32_t idx, cost, load;   // cost: what shares a CU; load: which XCD
-        bool tile, wide;   // reads pages that others may read too; of more than four tokens
+        bool tile;       // reads pages that others may read too
       };
       // What an item takes on a CU of its own, in half microseconds, from timelines of launches (start and end of
       // every workgroup with its CU): 8 tokens x 64 or 128 keys 8.0-8.1 us, x 192 12.3; 4 x 128 5.4, x 256 9.3; a
@@ -810,14 +810,15 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       // A fresh tile is dealt out before the pairs, not to become somebody's second workgroup.  (Behind them where a
       // third one comes to a CU: eight chunks on 500 tokens 16.85 / 16.6, six chunks and 48 requests 16.35 / 16.9.)
       // n: tokens that the record is launched with, which are four where it shares its item.
-      auto alone_cost = [](const int32_t* r, const int32_t n) {
-        const int32_t steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
-        const int32_t more = (steps + 3) / 4 - 1;   // rounds behind the first
+      auto steps_of = [](const int32_t* r) { return (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) >> 5; };
+      auto alone_cost = [&](const int32_t* r, const int32_t n) -> int32_t {
+        const int32_t steps = steps_of(r), more = (steps - 1) >> 2;   // rounds behind the first
         if (r[oxy::W_PATH] & oxy::kPathFresh) return 5 + 3 * steps + (n > 4 ? 2 : 0);
-        if (r[oxy::W_PATH] & oxy::kPathAppends) return 8 + 8 * more + steps / 2;
-        return n > 4 ? 14 + 8 * more + steps / 2 : n > 2 ? 9 + 8 * more + steps / 2 : 6 + 4 * more + steps / 2;
+        if (r[oxy::W_PATH] & oxy::kPathAppends) return 8 + 8 * more + (steps >> 1);
+        return (n > 4 ? 14 : n > 2 ? 9 : 6) + (n > 2 ? 8 : 4) * more + (steps >> 1);
       };
-      std::vector<Rec> recs(nw);
+      std::vector<Rec> recs;
+      recs.reserve(nw);
       size_t shared = 0;   // of wide_tiles, which ascends
       for (int32_t i = 0; i < nw; ++i) {
         const int32_t* r = &hdr[(size_t)i * kHdr];
@@ -827,26 +828,24 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         // to a CU on one XCD), and streaming items on prefix pages
         const bool fresh = (r[oxy::W_PATH] & oxy::kPathFresh) != 0;
         const bool shares = fresh ? false : (tile || !(r[oxy::W_PATH] & oxy::kPathAppends));
-        recs[i].idx = i;
         int32_t n_tok = r[oxy::W_N_TOK];
         if (shared < wide_tiles.size() && wide_tiles[shared] == i) {
           n_tok = 4;
           ++shared;
         }
-        recs[i].cost = alone_cost(r, n_tok);
+        const int32_t cost = alone_cost(r, n_tok);
         // XCDs are balanced by steps, twice for several tokens, except where the time does not go with the keys
         // (fresh tiles, tiles of more than four tokens): an XCD whose items read few keys gets the records that
         // no CU is left for, and pairs them there.  us a step, by the cost / so, pages not in the caches: a chunk and
         // eight requests on eight observations 187 / 162, two chunks and eight 195.8 / 194.4; a chunk and 16 requests,
         // six requests with 13 new tokens +-0.7 %.
-        const int32_t steps = (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) / 32;
-        recs[i].load = fresh || (tile && r[oxy::W_N_TOK] > 4) ? recs[i].cost / 2
-                       : tile && r[oxy::W_N_TOK] > 2          ? 2 * steps
-                                                              : steps;
-        recs[i].tile = tile && !fresh;
-        recs[i].wide = recs[i].tile && r[oxy::W_N_TOK] > 4;
-        recs[i].key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
-                             : -(int64_t)i - 1;
+        const int32_t steps = steps_of(r);
+        const int32_t load = fresh || (tile && r[oxy::W_N_TOK] > 4) ? cost >> 1
+                             : tile && r[oxy::W_N_TOK] > 2          ? 2 * steps
+                                                                    : steps;
+        const int64_t key = shares ? (((int64_t)r[oxy::W_TBL_OFF] << 32) | (uint32_t)r[oxy::W_KV_BEGIN])
+                                   : -(int64_t)i - 1;
+        recs.push_back({key, i, cost, load, tile && !fresh});
       }
       std::stable_sort(recs.begin(), recs.end(),
                        [](const Rec& a, const Rec& b) { return a.key < b.key; });
@@ -874,7 +873,11 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       std::stable_sort(grps.begin(), grps.end(), [&](const Grp& a, const Grp& b) {
         return a.cost != b.cost ? a.cost > b.cost : recs[a.first].idx < recs[b.first].idx;
       });
-      std::vector<Rec> queue[kXcd];
+      // A record's place in its queue as one number: largest cost first, then the lowest index.  (The costs take many
+      // values and come in no order; as whole records, by comparisons, the queues of eight chunks on 832 tokens took
+      // 5.6 us to sort, now 2.3, and the build 40.2, now 36.2.)
+      auto place_of = [](int32_t cost, int32_t idx) { return (int64_t)-cost * (1ll << 32) + idx; };
+      std::vector<int64_t> queue[kXcd];
       int64_t qcost[kXcd] = {0};
       for (int x = 0; x < kXcd; ++x) queue[x].reserve(nw / kXcd + 16);
       for (const Grp& g : grps) {
@@ -886,60 +889,61 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
             if (queue[x].size() + g.count <= room && (best < 0 || qcost[x] < qcost[best])) best = x;
           if (best >= 0) break;
         }
-        queue[best].insert(queue[best].end(), recs.begin() + g.first,
-                           recs.begin() + g.first + g.count);
+        for (int32_t i = g.first; i < g.first + g.count; ++i)
+          queue[best].push_back(place_of(recs[i].cost, recs[i].idx));
         qcost[best] += g.cost;
       }
       // Chunks alone: an XCD's items of more than four tokens beyond one for each of its CUs would be what the launch
       // ends with, two on a CU, so two records of four tokens share each of them if all have a slot.  us per layer,
       // without / with: six chunks on 1500 tokens 20.2 / 17.5, on 2048 20.8 / 18.2, on 832 14.9 / 13.6, seven 16.0 / 14.1; beyond
       // 64 records of an XCD it loses (eight on 1000 17.4 / 18.1).
+      auto wide = [&](int64_t place) {   // of more than four tokens, on pages that others may read too
+        const int32_t* r = &hdr[(size_t)(int32_t)place * kHdr];
+        return r[oxy::W_N_TOK] > 4 && (r[oxy::W_PATH] & (oxy::kPathMask | oxy::kPathFresh)) == oxy::PATH_TILE;
+      };
       for (int x = 0; x < kXcd && !decodes; ++x) {
-        std::vector<Rec>& q = queue[x];
-        const size_t n_wide = std::count_if(q.begin(), q.end(), [](const Rec& e) { return e.wide; });
+        std::vector<int64_t>& q = queue[x];
+        if (q.size() <= (size_t)kCuPerXcd) continue;
+        const size_t n_wide = std::count_if(q.begin(), q.end(), wide);
         size_t beyond = n_wide > kCuPerXcd ? n_wide - kCuPerXcd : 0;
         if (q.size() + beyond > (size_t)2 * kCuPerXcd || hdr.size() / kHdr + beyond > (size_t)c.max_work_items) continue;
         for (size_t i = q.size(); beyond > 0 && i-- > 0;) {
-          if (!q[i].wide) continue;
-          Rec second = q[i];
-          second.idx = (int32_t)(hdr.size() / kHdr);
-          add_second_half(q[i].idx);
-          wide_tiles.push_back(q[i].idx);
-          second.wide = q[i].wide = false;
+          if (!wide(q[i])) continue;
+          const int32_t first = (int32_t)q[i], second = (int32_t)(hdr.size() / kHdr);
+          add_second_half(first);
+          wide_tiles.push_back(first);
           // two records read the item's pages now, so neither is a sole reader
-          const int32_t* r = &hdr[(size_t)second.idx * kHdr];
-          q[i].cost = alone_cost(r, 4);
-          second.cost = alone_cost(r, r[oxy::W_N_TOK]);
-          q.push_back(second);
+          const int32_t* r = &hdr[(size_t)second * kHdr];
+          q[i] = place_of(alone_cost(r, 4), first);
+          q.push_back(place_of(alone_cost(r, r[oxy::W_N_TOK]), second));
           --beyond;
         }
       }
+      std::vector<int64_t> r;
       size_t longest = 0;
       for (int x = 0; x < kXcd; ++x) {
-        std::stable_sort(queue[x].begin(), queue[x].end(), [](const Rec& a, const Rec& b) {
-          return a.cost != b.cost ? a.cost > b.cost : a.idx < b.idx;
-        });
+        std::vector<int64_t>& q = queue[x];
+        std::sort(q.begin(), q.end());
         // Inside an XCD the dispatcher hands workgroups to the 32 CUs in turn, so while at most
         // two are resident per CU, positions j and j + 32 of a class share a CU, and a CU's
         // share of the memory system is what bounds its workgroups.  Pair the largest of the
         // first round with the smallest of the second; first-round items without a partner are
         // the largest ones.  Anything past 64 follows in descending order (it back-fills).
-        std::vector<Rec>& q = queue[x];
         if (q.size() > (size_t)kCuPerXcd) {
           const size_t top = std::min(q.size(), (size_t)2 * kCuPerXcd), m = top - kCuPerXcd;
-          const std::vector<Rec> r(q.begin(), q.begin() + top);
+          r.assign(q.begin(), q.begin() + top);
           for (size_t j = 0; j < m; ++j) q[j] = r[kCuPerXcd - m + j];
           for (size_t j = m; j < (size_t)kCuPerXcd; ++j) q[j] = r[j - m];
           for (size_t j = 0; j < m; ++j) q[kCuPerXcd + j] = r[top - 1 - j];
         }
-        longest = std::max(longest, queue[x].size());
+        longest = std::max(longest, q.size());
       }
       order.reserve(longest * kXcd);
       size_t last_real = 0;
       for (size_t k = 0; k < longest; ++k)
         for (int x = 0; x < kXcd; ++x) {
           if (k < queue[x].size()) {
-            order.push_back(queue[x][k].idx);
+            order.push_back((int32_t)queue[x][k]);
             last_real = order.size();
           } else {
             order.push_back(-1);
