@@ -1359,7 +1359,7 @@ __global__ __launch_bounds__(64 * kBlockHeads) void merge_append_kernel(OXY_MERG
     merge_block<kBlockHeads>({part_acc, part_ml, out, lse, n_parts, part_off}, blockIdx.x);
     return;
   }
-  if (threadIdx.x >= 256) return;
+  if (threadIdx.x >= 256) return;   // whole wavefronts: a barrier waits for those of its workgroup that have not ended
   const int run = nx.runs ? nx.runs[i] : i << 4;
   const int tok = run >> 4, slot = nx.d_slots[tok];
   const uint16_t* k_row = (const uint16_t*)nx.k_new + (size_t)tok * kDim;

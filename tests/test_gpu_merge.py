@@ -15,12 +15,23 @@ pytestmark = pytest.mark.gpu
 def test_split_results_of_a_token(counts, fold):
     """Decode streams without a prefix: a history of 32 n tokens is n split results of 32 keys.  The
     chunk beside them has its own count (prefix and own tokens)."""
+    _compare(counts, 5, fold)
+
+
+@pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
+@pytest.mark.parametrize("counts", [[4, 5, 8, 9, 12, 13], [16, 17, 33, 15, 14, 1, 48]], ids=str)
+def test_split_results_of_a_token_among_many(counts, fold):
+    """The same in a launch of more than 256 tokens, whose merge workgroups take all heads of a token."""
+    _compare(counts, 260, fold)
+
+
+def _compare(counts, chunk, fold):
     b = _TraceBuilder()
     act = b.stream(b.prefix(70), ACTION)
     streams = [b.stream(-1, DECODE) for _ in counts]
     hist = [(s, 32 * n - 1) for s, n in zip(streams, counts)]
     b.step([h for h in hist if h[1]], attend=False)
-    b.step([(s, 1) for s in streams] + [(act, 5)])
+    b.step([(s, 1) for s in streams] + [(act, chunk)])
     w = _workload("merge", 5160, 1, 1024, b.trace)
     gw, _, _, _ = run_both(w, poison=True, split_tokens=32, stream_split_tokens=32, max_partials=8192,
                            fold_append=fold)

@@ -210,3 +210,41 @@ def test_recordings_of_both_merge_forms_beyond_the_cache(fold):
             B.oxy_batch_destroy(f[0])
     finally:
         gw.close()
+
+
+def test_fused_steps_of_many_tokens_equal_per_layer_calls():
+    """More than 256 query tokens: the merge of layer l, a workgroup for all heads of a token, and the append of
+    layer l+1 in one launch, with up to 17 split results a token."""
+    import torch
+    from paper_2603_14371_amd import binding as B
+    from paper_2603_14371_amd.harness import GpuWorld, bits_of, to_device_bf16
+    b = synth._TraceBuilder()
+    pid = b.prefix(200)
+    act, dec = b.stream(pid, synth.ACTION), b.stream(pid, synth.DECODE)
+    b.step([(dec, 77)], attend=False)
+    w = synth._workload("many_tokens_fused", 5172, 3, 256, b.trace)
+    data, items, n = synth.DataSource(1621), [(act, 290), (dec, 1)], 291
+    got = []
+    for flags in (None, B.STEP_FUSE_ACROSS_LAYERS, B.STEP_FUSE_ACROSS_LAYERS | B.STEP_GRAPH):
+        gw = GpuWorld(w, data, split_tokens=32, max_q_tokens=n, max_append_tokens=n, max_partials=8192, poison=True)
+        gw.run(w["trace"])
+        L, stream = gw.n_layers, torch.cuda.current_stream(gw.device).cuda_stream
+        k, v, q = (torch.stack([to_device_bf16(data({"tag": 911, "tok0": 0, "n_total": n}, l, what, n), gw.device)
+                                for l in range(L)]) for what in "kvq")
+        o = torch.zeros_like(q)
+        batch = B.oxy_batch_build(gw.pool, items, 0, stream)
+        if flags is None:
+            for l in range(L):
+                B.oxy_stream_append(gw.pool, batch, l, k[l].data_ptr(), v[l].data_ptr(), stream)
+                B.oxy_mixed_attention(gw.pool, batch, l, q[l].data_ptr(), o[l].data_ptr(), 0, gw.scale, stream)
+        else:
+            B.oxy_step_layers(gw.pool, batch, 0, L, k.data_ptr(), v.data_ptr(), k.stride(0) * 2, q.data_ptr(),
+                              o.data_ptr(), q.stride(0) * 2, 0, 0, gw.scale, flags, None, stream)
+        torch.cuda.synchronize()
+        B.oxy_batch_destroy(batch)
+        got.append([bits_of(o)] + [x for sid in (act, dec) for l in range(L) for x in gw.gather(l, gw.stream_slots(sid))])
+        gw.close()
+    assert np.any(got[0][0] != 0)
+    for other in got[1:]:
+        for x, y in zip(got[0], other):
+            assert np.array_equal(x, y)

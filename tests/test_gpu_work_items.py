@@ -94,6 +94,25 @@ def test_items_of_chunks_that_two_records_share_equal_the_chunk_alone(n, prefix_
         assert np.array_equal(whole[key][0], np.concatenate([r[key][0] for r in alone]))
 
 
+@pytest.mark.parametrize("n,prefix_len,hist,n_new", [(3, 64, 1700, 100), (5, 64, 1500, 53)])
+def test_causal_items_that_two_records_share_equal_the_request_alone(n, prefix_len, hist, n_new):
+    """Several new tokens behind long histories, some splits past the diagonal of an item's first four tokens:
+    the oracle's values, and the bits of each request by itself."""
+    b = _TraceBuilder()
+    sids = [b.stream(b.prefix(prefix_len), DECODE) for _ in range(n)]
+    b.step([(s, hist + 7 * i) for i, s in enumerate(sids)], attend=False)
+    b.step([(s, n_new) for s in sids], recipe=b.recipe(n * n_new, tag=902))
+    w = _workload("shared_causal_items", 5154, 1, 1024, b.trace)
+    gw, res, _, _ = run_both(w, poison=True, max_q_tokens=512, max_partials=16384)
+    for i, s in enumerate(sids):
+        gw.apply({"op": "stream_rewind", "sid": s, "len": hist + 7 * i})
+    alone = [gw.step({"op": "step", "items": [(s, n_new)], "data": {"tag": 902, "tok0": i * n_new, "n_total": n * n_new}})
+             for i, s in enumerate(sids)]
+    gw.close()
+    for key in ("O", "LSE"):
+        assert np.array_equal(res[-1][key][0], np.concatenate([r[key][0] for r in alone]))
+
+
 @pytest.mark.parametrize("n_prefix,prefix_len,width", [(3, 832, 4), (9, 832, 8), (9, 190, 4)])
 @pytest.mark.parametrize("fold", [False, True], ids=["separate_append", "folded_append"])
 def test_items_in_a_launch_of_many_equal_items_alone(n_prefix, prefix_len, width, fold):
@@ -133,6 +152,25 @@ def test_items_in_a_launch_of_many_equal_items_alone(n_prefix, prefix_len, width
     gw.close()
     assert np.array_equal(np.concatenate([o for o, _ in alone]), r["O"][0])
     assert np.array_equal(np.concatenate([l for _, l in alone]), r["LSE"][0])
+
+
+@pytest.mark.parametrize("n,prefix_len,hist,n_new", [(3, 64, 1700, 100), (5, 64, 1500, 53)])
+def test_causal_items_that_two_records_share_equal_the_request_alone(n, prefix_len, hist, n_new):
+    """Several new tokens behind long histories, some splits past the diagonal of an item's first four tokens:
+    the oracle's values, and the bits of each request by itself."""
+    b = _TraceBuilder()
+    sids = [b.stream(b.prefix(prefix_len), DECODE) for _ in range(n)]
+    b.step([(s, hist + 7 * i) for i, s in enumerate(sids)], attend=False)
+    b.step([(s, n_new) for s in sids], recipe=b.recipe(n * n_new, tag=902))
+    w = _workload("shared_causal_items", 5154, 1, 1024, b.trace)
+    gw, res, _, _ = run_both(w, poison=True, max_q_tokens=512, max_partials=16384)
+    for i, s in enumerate(sids):
+        gw.apply({"op": "stream_rewind", "sid": s, "len": hist + 7 * i})
+    alone = [gw.step({"op": "step", "items": [(s, n_new)], "data": {"tag": 902, "tok0": i * n_new, "n_total": n * n_new}})
+             for i, s in enumerate(sids)]
+    gw.close()
+    for key in ("O", "LSE"):
+        assert np.array_equal(res[-1][key][0], np.concatenate([r[key][0] for r in alone]))
 
 
 @pytest.mark.parametrize("n_prefix,prefix_len,width", [(2, 1100, 4), (3, 2048, 4), (9, 1300, 8)])

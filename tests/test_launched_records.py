@@ -159,6 +159,26 @@ def test_chunks_alone_share_items_beyond_one_for_each_cu(n, prefix_len, chunk, s
         assert len(mixed) == len(listed)
 
 
+@pytest.mark.parametrize("n,prefix_len,hist,n_new", [
+    (3, 0, 1700, 100), (3, 64, 1700, 100), (3, 0, 1700, 101), (5, 64, 1500, 53), (4, 832, 1500, 50)])
+def test_causal_items_on_long_histories_are_shared_too(n, prefix_len, hist, n_new):
+    """Several new tokens behind a long history: of a shared item the second record's causal base is four further on,
+    and the first one keeps the keys of both."""
+    p = _Pool()
+    pid = p.prefix(prefix_len) if prefix_len else -1
+    rec, work, _ = p.build([(p.stream(pid, B.KIND_DECODE, hist + 7 * i), n_new) for i in range(n)])
+    p.close()
+    listed = {tuple(w[[0, 2, 3, 4, 6]]): w for w in work}
+    second = [r for r in rec if tuple(r[[0, 2, 3, 4, 6]]) not in listed]
+    assert second and len(second) == len(rec) - len(work)
+    for r in second:
+        at = (r[0] - 4, *r[[2, 3, 4, 6]])
+        first = [f for f in rec if tuple(f[[0, 2, 3, 4, 6]]) == at]
+        assert len(first) == 1 and first[0][1] == 4 and r[1] == listed[at][1] - 4 and r[7] == first[0][7]
+        assert r[5] == (NO_CAUSAL if first[0][5] == NO_CAUSAL else first[0][5] + 4)
+    assert any(r[5] != NO_CAUSAL for r in second)
+
+
 def _by_size(records):
     """The records of every XCD in the order of their size: of more than 32, the largest of the first 32 is
     dealt out with the smallest of the next 32."""
