@@ -787,8 +787,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
     }
     // Order of the work list.  Workgroup i runs on XCD i % 8 and every XCD has its own L2, so
     // tiles that read the same pages (same table, same split) are given indices of one residue
-    // class; within a class the longest work comes first, and the classes are balanced by cost
-    // (longest-processing-time rule over the groups).  Padding records keep the pattern intact.
+    // class; within a class the longest work comes first, and the classes are balanced by load
+    // (the largest group first, each to the class with the least).  Padding records keep the pattern intact.
     {
       const int32_t nw = (int32_t)(hdr.size() / kHdr);
       constexpr int kXcd = 8, kCuPerXcd = 32;
@@ -800,15 +800,20 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       // What an item takes on a CU of its own, in half microseconds, from timelines of launches (start and end of
       // every workgroup with its CU): 8 tokens x 64 or 128 keys 8.0-8.1 us, x 192 12.3; 4 x 128 5.4, x 256 9.3; a
       // pair x 128 4.2, x 192 6.5; own pages of a request, read from HBM, 256 keys 9.6, up to 128 4.0-4.4; a
-      // fresh tile 4.4-5.  Two on one CU take as long as the longer one if the other has half its cost, 8 + 8
-      // tokens 11.2, 8 tokens + own 256 11.9, two own 256 15.  (With a cost of twice the steps for every tile and of
-      // the steps for everything else, 2-token tiles stood among the 8-token ones and own pages below them.  us per
-      // layer, that / this: two chunks and 40 requests on 832 tokens 16.7 / 12.1, six chunks and 48 on 700 19.1 / 16.3, five
-      // chunks on 1500 19.3 / 16.6, on 832 14.4 / 12.8, eight on 300 14.8 / 13.0, one of 300 queries 22.6 / 21.3, a chunk
-      // and 16 requests 9.93 / 9.34, two and 8 10.4 / 9.6, six requests with 13 new tokens 11.58 / 11.16, 64 requests and
-      // two chunks 22.2 / 22.1, eight chunks on 832 16.6 / 16.7.)
-      // A fresh tile is dealt out before the pairs, not to become somebody's second workgroup.  (Behind them where a
-      // third one comes to a CU: eight chunks on 500 tokens 16.85 / 16.6, six chunks and 48 requests 16.35 / 16.9.)
+      // fresh tile 4.4-5.  The formula is within a microsecond of these except at 4 x 256 (10.5).  Two on one CU take as
+      // long as the longer one if the other has half its cost, 8 + 8 tokens 11.2, 8 tokens + own 256 11.9, two own
+      // 256 15.  (With cost and load of twice the steps for every tile, one more for a fresh one, and of the steps for
+      // everything else, pairs stood among the tiles of 8 and own pages below them.  us per layer, that / this, launches
+      // queued ahead: two chunks and 40 requests on 832 tokens 16.8 / 12.1, six chunks and 48 on 700 18.9 / 16.2, five chunks
+      // on 1500 19.6 / 16.3, on 832 14.2 / 12.7, eight on 300 14.6 / 13.0, a chunk of 300 22.4 / 21.3, a chunk and 16
+      // requests 9.92 / 9.29, two and 8 10.4 / 9.7, twelve requests with 13 new tokens 16.1 / 14.7, six 11.5 / 11.3, 64
+      // requests and two chunks 22.1 / 22.0, one request 6.28 / 6.27; slower are eight chunks on 832 tokens 16.3 / 16.45,
+      // on 500 16.6 / 16.8, 24 requests on 512 10.66 / 10.73, and six requests with 13 new tokens behind a read of 512 MB
+      // and other kernels, work items 8.4 / 8.9.)
+      // A fresh tile is dealt out before the pairs, not to become somebody's second workgroup.  (Behind them, at 3 + 3
+      // per step, + 1 beyond four tokens, this / that: a chunk and eight requests on eight observations 8.23 / 8.95, two
+      // and 8 9.7 / 10.25, a chunk and 16 9.29 / 9.97, six and 48 16.2 / 17.0, a chunk of 300 21.3 / 21.7; where a third
+      // one comes to a CU that is better, eight chunks on 500 tokens 16.8 / 16.5, on 150 11.1 / 10.85.)
       // n: tokens that the record is launched with, which are four where it shares its item.
       auto steps_of = [](const int32_t* r) { return (r[oxy::W_KV_END] - r[oxy::W_KV_BEGIN] + 31) >> 5; };
       auto alone_cost = [&](const int32_t* r, const int32_t n) -> int32_t {
@@ -836,9 +841,10 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
         const int32_t cost = alone_cost(r, n_tok);
         // XCDs are balanced by steps, twice for several tokens, except where the time does not go with the keys
         // (fresh tiles, tiles of more than four tokens): an XCD whose items read few keys gets the records that
-        // no CU is left for, and pairs them there.  us a step, by the cost / so, pages not in the caches: a chunk and
-        // eight requests on eight observations 187 / 162, two chunks and eight 195.8 / 194.4; a chunk and 16 requests,
-        // six requests with 13 new tokens +-0.7 %.
+        // no CU is left for, and pairs them there.  By the cost / so, us a step of 18 layers, pages not in the caches: a
+        // chunk and eight requests on eight observations 199 / 163, two and 8 196.9 / 195.5, others within 0.5 %; us per
+        // layer, launches queued ahead: a chunk and 16 requests 9.43 / 9.29, but one request 6.12 / 6.27, six with 13 new
+        // tokens 11.1 / 11.3, a chunk of 300 21.0 / 21.3.
         const int32_t steps = steps_of(r);
         const int32_t load = fresh || (tile && r[oxy::W_N_TOK] > 4) ? cost >> 1
                              : tile && r[oxy::W_N_TOK] > 2          ? 2 * steps
@@ -895,8 +901,8 @@ int32_t oxy_batch_build(oxy_pool* p, const oxy_item* items, int32_t n_items, int
       }
       // Chunks alone: an XCD's items of more than four tokens beyond one for each of its CUs would be what the launch
       // ends with, two on a CU, so two records of four tokens share each of them if all have a slot.  us per layer,
-      // without / with: six chunks on 1500 tokens 20.2 / 17.5, on 2048 20.8 / 18.2, on 832 14.9 / 13.6, seven 16.0 / 14.1; beyond
-      // 64 records of an XCD it loses (eight on 1000 17.4 / 18.1).
+      // without / with: six chunks on 1500 tokens 20.2 / 17.2, on 2048 20.9 / 17.8, on 832 14.9 / 13.4, seven 15.8 / 13.85; beyond
+      // 64 records of an XCD it loses (eight on 1000 17.3 / 20.3, on 2048 22.2 / 24.9, on 832 16.3 / 16.95).
       auto wide = [&](int64_t place) {   // of more than four tokens, on pages that others may read too
         const int32_t* r = &hdr[(size_t)(int32_t)place * kHdr];
         return r[oxy::W_N_TOK] > 4 && (r[oxy::W_PATH] & (oxy::kPathMask | oxy::kPathFresh)) == oxy::PATH_TILE;
