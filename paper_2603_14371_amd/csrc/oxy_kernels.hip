@@ -1137,12 +1137,12 @@ __device__ __forceinline__ void attend_fresh_any(const AttnArgs& a, const WorkIt
     attend_fresh<false, true, 4>(a, wi, sm, row0);
 }
 
-// The narrowest comes last, and with it the four-step instance that every decode step runs: the compiler
-// lays the instances out in the order of these tests, and the last one lies next to the kernel's common
-// exit.  With two-step instances between them a launch whose code has left the caches (other kernels and a
-// read of 512 MB in front of every launch) fetched one more line from memory at its end: one request on
-// 832 tokens 7.3-7.5 us, now 6.9-7.1, three 7.1-7.2 / 7.0, one with a chunk 7.6-7.8 / 7.3-7.5; larger launches and
-// launches that follow each other within 1 %.
+// The narrowest is tested last, and with it the four-step instance that every decode step runs: the compiler
+// lays the instance that is tested last out first and the widest at the kernel's end.  With the narrowest tested first
+// and laid out last a launch whose code has left the caches (other kernels and a read of 512 MB in front of every
+// launch) took, one request on 832 tokens 7.3-7.5 us, now 6.9-7.1, three 7.1-7.2 / 7.0, one with a chunk 7.6-7.8 / 7.3-7.5;
+// larger launches and launches that follow each other within 1 %.  Where code lies is worth that much for no reason that
+// shows in it: the whole kernel 4 KiB further on took 0.2 us more.
 __device__ __forceinline__ void attend_shared(const AttnArgs& a, const WorkItem& wi, WorkLds& sm) {
   const bool few_keys = wi.kv_end - wi.kv_begin <= 64;
   if (wi.n_tok > 4)
